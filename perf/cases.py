@@ -362,3 +362,87 @@ def tolerance(case):
     # bf16 operands and intermediates, fp32 accumulation: 2.4e-3 to 3.8e-3 against the same path in
     # 64 bits, so up to 5e-3 between two implementations
     return {"rel": 1e-2}
+
+
+# ---------------------------------------------------------------------------------------------
+# What `run` returns, in 64 bits.  Inputs are the state's (drawn once more from the seed); the
+# rows' order is spelled out from the plan's tables, which the program has in hand.
+def _rows_by_definition(s, mb):
+    """Expert of every assignment and its row: an expert's assignments in ascending order fill its instances one after the other."""
+    ids = s.ids[mb].reshape(-1).long()
+    t = {key: s.tabs[key][mb].cpu().tolist() for key in ("inst_ptr", "inst_rows", "inst_group", "group_offset")}
+    row_of = torch.empty_like(ids)
+    for e in range(s.case["E"]):
+        at, taken = torch.nonzero(ids == e).reshape(-1), 0
+        for i in range(t["inst_ptr"][e], t["inst_ptr"][e + 1]):
+            n, first = t["inst_rows"][i], t["group_offset"][t["inst_group"][i]]
+            row_of[at[taken:taken + n]] = first + torch.arange(n, device=DEV)
+            taken += n
+    return ids, row_of
+
+
+def _exact_layer(s, backward):
+    c = s.case
+    E, k, h, hff, T, n_mb, N = c["E"], c["k"], c["h"], c["hff"], c["T"], c["n_mb"], s.N
+    f64 = lambda *shape: torch.zeros(shape, dtype=torch.float64, device=DEV)
+    Out, dX, dgate = f64(n_mb, T, h), f64(n_mb, T, h), f64(n_mb, N)
+    saved = None if backward else [f64(N, hff) for _ in range(3)]
+    dW = [f64(E, hff, h), f64(E, hff, h), f64(E, h, hff)] if backward else None
+    routes = [s.ids[mb].reshape(-1).long() if backward else _rows_by_definition(s, mb) for mb in range(n_mb)]
+    for e in range(E):
+        Wg, Wu, Wd = (w[e].double() for w in s.W)
+        for mb in range(n_mb):
+            at = torch.nonzero((routes[mb] if backward else routes[mb][0]) == e).reshape(-1)
+            if at.numel() == 0:
+                continue
+            tok, gate = at // k, s.gates[mb].reshape(-1)[at].double()[:, None]
+            x = s.X[mb][tok].double()
+            G, U = x @ Wg.T, x @ Wu.T
+            sig = torch.sigmoid(G)
+            A = G * sig * U
+            Y = A @ Wd.T
+            Out[mb].index_add_(0, tok, gate * Y)
+            if not backward:
+                for whole, part in zip(saved, (G, U, A)):
+                    whole[routes[mb][1][at]] = part
+                continue
+            dO = s.dOut[mb][tok].double()
+            dgate[mb][at] = (dO * Y).sum(1)
+            dY = gate * dO
+            dA = dY @ Wd
+            dG, dU = dA * U * sig * (1 + G * (1 - sig)), dA * G * sig
+            dX[mb].index_add_(0, tok, dG @ Wg + dU @ Wu)
+            for whole, part in zip(dW, (dG.T @ x, dU.T @ x, dY.T @ A)):
+                whole[e] += part
+    if not backward:
+        return dict(Out=Out, Gt=saved[0], U=saved[1], A=saved[2], err=None)
+    return dict(Out=Out, dX=dX, dgate=dgate.view(n_mb, T, k), dWg=dW[0], dWu=dW[1], dWd=dW[2], err=None)
+
+
+def exact(case, seed):
+    do, E, k, T, n_mb = (case[x] for x in ("do", "E", "k", "T", "n_mb"))
+    s = prepare(case, seed)
+    if do in ("train", "forward"):
+        return _exact_layer(s, do == "train")
+    if do in ("plan", "hist"):
+        counts = torch.stack([torch.bincount(s.ids[mb].reshape(-1), minlength=E) for mb in range(n_mb)]).int()
+        return dict(counts=counts, err=None)
+    if do == "dispatch":
+        _, row_of = _rows_by_definition(s, 0)
+        tok = torch.arange(s.N, device=DEV) // k
+        src_of = torch.empty_like(row_of)
+        src_of[row_of] = torch.arange(s.N, device=DEV)
+        gate, y, dO = s.gates[0].reshape(-1).double()[:, None], s.Y[row_of].double(), s.dOut[tok].double()
+        dY = torch.empty((s.N, case["h"]), dtype=torch.float64, device=DEV)
+        dY[row_of] = gate * dO
+        return dict(row_of=row_of.int(), src_of=src_of.int(), Xrows=s.X[0][tok[src_of]].double(),
+                    Out=(gate * y).view(T, k, -1).sum(1)[None], dY=dY, dgate=(dO * y).sum(1).view(T, k), err=None)
+    table = s.replica_expert.cpu().tolist()
+    W, dW = [w.clone() for w in s.W], [g.double() for g in s.dW]
+    for slot, e in enumerate(table):
+        if e >= 0:
+            for w, g in zip(W, dW):
+                w[E + slot] = w[e]
+                g[e] += g[E + slot]
+    W = [w.double() for w in W]
+    return dict(Wg=W[0], Wu=W[1], Wd=W[2], dWg=dW[0], dWu=dW[1], dWd=dW[2], err=None)
