@@ -595,6 +595,33 @@ def test_replica_push_flags_bad_table_and_leaves_empty_slots():
         assert torch.equal(w[:E], b[:E])
 
 
+@pytest.mark.parametrize("E,slots,h,hff,n_wg", [
+    (1, 1, 8, 8, 1),             # one vector short of a thread's share
+    (5, 7, 192, 320, 3),         # chunks that the block does not fill, several slots of one expert
+    (3, 1100, 64, 72, 5),        # two lists of slots: an expert's sum goes on across them
+    (40, 16, 256, 520, 64),      # more workgroups than chunks of an expert
+])
+def test_replica_push_and_pull_at_list_and_chunk_edges(E, slots, h, hff, n_wg):
+    rng = np.random.default_rng(slots)
+    table = rng.integers(-1, E, slots).astype(np.int32)
+    table[0] = 0
+    gen = torch.Generator().manual_seed(slots)
+    W = [torch.randn((E + slots, h * hff), generator=gen).to(torch.bfloat16) for _ in range(3)]
+    dW = [torch.randn((E + slots, h * hff), generator=gen) for _ in range(3)]
+    Wd, dWd = [w.to(DEV) for w in W], [d.to(DEV) for d in dW]
+    shape = lambda ts: [t.view(E + slots, h, hff) for t in ts]
+    err = rl.relibra_replica_push(*shape(Wd), dev_i32(table), E, slots, 1, n_workgroups=n_wg)
+    rl.relibra_replica_pull(*shape(dWd), dev_i32(table), E, slots, 1, n_workgroups=n_wg, err_flag=err)
+    assert err.item() == 0
+    for s, e in enumerate(table):
+        if e >= 0:
+            for w, d in zip(W, dW):
+                w[E + s] = w[e]
+                d[e] += d[E + s]                 # ascending slots, one fp32 addition each: the defined order
+    for got, want in zip(Wd + dWd, W + dW):
+        assert torch.equal(got.cpu(), want)
+
+
 # ------------------------------------------------------------------ batched weight gradients
 def test_batched_weight_gradients_match_oracle_and_per_microbatch_path():
     """dW of a whole batch in one pass (Section 2.1: gradients accumulate over micro-batches):
