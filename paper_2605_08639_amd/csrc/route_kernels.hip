@@ -144,28 +144,30 @@ struct SrcSplit {
     int EP, k, tokens_per_src;
 };
 
-__global__ void __launch_bounds__(kPermThreads)
-perm_rank_kernel(const int32_t *__restrict__ ids, int N, int E, int G, int ebits,
-                 const int32_t *__restrict__ unit_base,
-                 const int32_t *__restrict__ inst_ptr, const int32_t *__restrict__ inst_rows,
-                 const int32_t *__restrict__ inst_group, const int32_t *__restrict__ group_offset,
-                 int32_t *__restrict__ row_of, int32_t *__restrict__ src_of, int32_t *err_flag,
-                 SrcSplit sp)
+// What the ranking step needs of the plan's tables.
+struct PlanTables {
+    const int32_t *__restrict__ inst_ptr, *__restrict__ inst_rows, *__restrict__ inst_group, *__restrict__ group_offset;
+};
+// First instance of an expert, kept in LDS by the one-block permutation: its rows and its first row.
+struct FirstInst {
+    int32_t rows, row0;
+};
+
+// Ranks assignments lo .. hi-1 (one wave, 64 at a time, in order).  next[e]: next ordinal of expert e
+// in this range (LDS, private to the wave).  first: null, or every expert's first instance.
+__device__ __forceinline__ int rank_range(const int32_t *__restrict__ ids, int lo, int hi, int N, int E, int G, int ebits, int32_t *next,
+                                          const FirstInst *first, const PlanTables &t, int32_t *__restrict__ row_of,
+                                          int32_t *__restrict__ src_of, const SrcSplit &sp)
 {
-    extern __shared__ int32_t lds[];
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    int32_t *next = lds + wave * E;        // next ordinal of each expert, private to the wave
-    const int unit = blockIdx.x * (kPermThreads / 64) + wave;
-    const int lo = unit * kUnit, hi = min(N, lo + kUnit);
-    if (lo < N)
-        for (int e = lane; e < E; e += 64) next[e] = unit_base[(size_t)unit * E + e];
-    __builtin_amdgcn_wave_barrier();
+    const int lane = threadIdx.x & 63;
     const uint64_t lt_mask = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
     int flags = 0;
+    int e_next = lo + lane < hi ? ids[lo + lane] : -1;
     for (int base = lo; base < hi; base += 64) {
         const int a = base + lane;
         const bool live = a < hi;
-        const int e_raw = live ? ids[a] : -1;
+        const int e_raw = e_next;
+        e_next = a + 64 < hi ? ids[a + 64] : -1;
         const bool ok = live && (unsigned)e_raw < (unsigned)E;
         const int e = ok ? e_raw : 0;
         // lanes with the same expert: intersect ballots bit by bit
@@ -188,29 +190,33 @@ perm_rank_kernel(const int32_t *__restrict__ ids, int N, int E, int G, int ebits
         }
         __builtin_amdgcn_wave_barrier();
         if (ok) {
-            int i = inst_ptr[e];
-            const int end = inst_ptr[e + 1];
             int skipped = 0, row = -1;
             if (sp.src_first) {
                 // source-aware split: ordinal among the source's own tokens of e, runs of
                 // inst_src_rows[i][j], rows of an instance laid out source after source
+                int i = t.inst_ptr[e];
+                const int end = t.inst_ptr[e + 1];
                 const int j = min((a / sp.k) / sp.tokens_per_src, sp.EP - 1);
                 const int qj = q - sp.src_first[(size_t)j * E + e];
                 for (; qj >= 0 && i < end; ++i) {
                     const int n = sp.inst_src_rows[(size_t)i * sp.EP + j];
                     if (qj < skipped + n) {
-                        const int g = inst_group[i];
-                        if ((unsigned)g < (unsigned)G) row = group_offset[g] + sp.inst_src_base[(size_t)i * sp.EP + j] + (qj - skipped);
+                        const int g = t.inst_group[i];
+                        if ((unsigned)g < (unsigned)G) row = t.group_offset[g] + sp.inst_src_base[(size_t)i * sp.EP + j] + (qj - skipped);
                         break;
                     }
                     skipped += n;
                 }
+            } else if (first && q < first[e].rows) {
+                row = first[e].row0 + q;
             } else {
+                int i = t.inst_ptr[e];
+                const int end = t.inst_ptr[e + 1];
                 for (; i < end; ++i) {
-                    const int n = inst_rows[i];
+                    const int n = t.inst_rows[i];
                     if (q < skipped + n) {
-                        const int g = inst_group[i];
-                        if ((unsigned)g < (unsigned)G) row = group_offset[g] + (q - skipped);
+                        const int g = t.inst_group[i];
+                        if ((unsigned)g < (unsigned)G) row = t.group_offset[g] + (q - skipped);
                         break;
                     }
                     skipped += n;
@@ -228,6 +234,72 @@ perm_rank_kernel(const int32_t *__restrict__ ids, int N, int E, int G, int ebits
             flags |= RELIBRA_ERR_ID_RANGE;
         }
     }
+    return flags;
+}
+
+__global__ void __launch_bounds__(kPermThreads)
+perm_rank_kernel(const int32_t *__restrict__ ids, int N, int E, int G, int ebits,
+                 const int32_t *__restrict__ unit_base, PlanTables t,
+                 int32_t *__restrict__ row_of, int32_t *__restrict__ src_of, int32_t *err_flag,
+                 SrcSplit sp)
+{
+    extern __shared__ int32_t lds[];
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    int32_t *next = lds + wave * E;        // next ordinal of each expert, private to the wave
+    const int unit = blockIdx.x * (kPermThreads / 64) + wave;
+    const int lo = unit * kUnit, hi = min(N, lo + kUnit);
+    if (lo < N)
+        for (int e = lane; e < E; e += 64) next[e] = unit_base[(size_t)unit * E + e];
+    __builtin_amdgcn_wave_barrier();
+    const int flags = rank_range(ids, lo, hi, N, E, G, ebits, next, nullptr, t, row_of, src_of, sp);
+    if (flags) atomicOr(err_flag, flags);
+}
+
+// The three passes in one block, for small micro-batches: the three launches cost more than the work
+// (each is a launch and a few dependent memory round trips).  Every wave takes a sixteenth of the
+// assignments; counts, their scan over the waves and the experts' first instances stay in LDS, so that a
+// round of 64 assignments reads memory only where an expert is split over several instances.  The block's
+// time grows by about 2 us per 1024 assignments: 3.5 us at 1024, 6.3 at 2048, 7.5 at 3108 against 6.5 us
+// and two more launches for the three kernels, which are the faster ones from there on (at 32768 the block
+// would take 79 us, they take 10).
+constexpr int kSmallThreads = 1024, kSmallWaves = kSmallThreads / 64;
+constexpr int kSmallN = 4096, kSmallE = 512;               // (kSmallWaves + 2) * kSmallE ints of LDS
+__global__ void __launch_bounds__(kSmallThreads)
+perm_small_kernel(const int32_t *__restrict__ ids, int N, int E, int G, int ebits, PlanTables t,
+                  int32_t *__restrict__ row_of, int32_t *__restrict__ src_of, int32_t *err_flag, SrcSplit sp)
+{
+    extern __shared__ int32_t lds[];
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    int32_t *bins = lds + wave * E;
+    FirstInst *first = reinterpret_cast<FirstInst *>(lds + kSmallWaves * E);
+    for (int i = tid; i < kSmallWaves * E; i += kSmallThreads) lds[i] = 0;
+    for (int i = tid; i < N; i += kSmallThreads) src_of[i] = -1;       // rows nobody claims stay marked
+    int inst0 = 0, inst1 = 0;
+    if (tid < E) { inst0 = t.inst_ptr[tid]; inst1 = t.inst_ptr[tid + 1]; }
+    const int per_wave = ((N + kSmallThreads - 1) / kSmallThreads) * 64;
+    const int lo = min(wave * per_wave, N), hi = min(lo + per_wave, N);
+    __syncthreads();
+    for (int a = lo + lane; a < hi; a += 64) {
+        const int e = ids[a];
+        if ((unsigned)e < (unsigned)E) atomicAdd(&bins[e], 1);         // ids out of range are flagged by the ranking
+    }
+    __syncthreads();
+    if (tid < E) {                         // exclusive scan over the waves
+        int at = 0;
+        for (int w = 0; w < kSmallWaves; ++w) {
+            const int c = lds[w * E + tid];
+            lds[w * E + tid] = at;
+            at += c;
+        }
+        FirstInst f{0, 0};
+        if (at > 0 && inst0 < inst1 && !sp.src_first) {
+            const int g = t.inst_group[inst0];
+            if ((unsigned)g < (unsigned)G) f = FirstInst{t.inst_rows[inst0], t.group_offset[g]};
+        }
+        first[tid] = f;
+    }
+    __syncthreads();
+    const int flags = rank_range(ids, lo, hi, N, E, G, ebits, bins, sp.src_first ? nullptr : first, t, row_of, src_of, sp);
     if (flags) atomicOr(err_flag, flags);
 }
 
@@ -457,20 +529,27 @@ static int permute_impl(const int32_t *ids_dev, const int32_t *inst_ptr_dev, con
     if (with_rows && (!X_dev || !Xrows_dev || h < 8 || h % 8 || !aligned16(X_dev) || !aligned16(Xrows_dev)))
         return RELIBRA_EINVAL;
     if (workspace_bytes < relibra_workspace_bytes(RELIBRA_WS_PERMUTE, T, k, E, G, h, 0)) return RELIBRA_EWORKSPACE;
-    int32_t *unit_cnt = (int32_t *)workspace_dev;
-    const int n_units = (N + kUnit - 1) / kUnit;
-    const int blocks = (n_units + 3) / 4;
-    const size_t lds = (size_t)4 * E * sizeof(int32_t);
     int ebits = 0;
     while ((1 << ebits) < E) ++ebits;
-    RELIBRA_LAUNCH(RELIBRA_K_PERM_COUNT, stream, perm_count_kernel<<<blocks, kPermThreads, lds, stream>>>(ids_dev, N, E, unit_cnt, src_of_dev, err_flag_dev));
-    RELIBRA_HIP_TRY(launch_check());
-    RELIBRA_LAUNCH(RELIBRA_K_PERM_SCAN, stream, perm_scan_kernel<<<E, 256, 0, stream>>>(unit_cnt, n_units, E));
-    RELIBRA_HIP_TRY(launch_check());
-    RELIBRA_LAUNCH(RELIBRA_K_PERM_RANK, stream, perm_rank_kernel<<<blocks, kPermThreads, lds, stream>>>(ids_dev, N, E, G, ebits, unit_cnt, inst_ptr_dev,
-                                                            inst_rows_dev, inst_group_dev, group_offset_dev,
-                                                            row_of_dev, src_of_dev, err_flag_dev, split));
-    RELIBRA_HIP_TRY(launch_check());
+    const PlanTables tables{inst_ptr_dev, inst_rows_dev, inst_group_dev, group_offset_dev};
+    if (N <= kSmallN && E <= kSmallE) {
+        const size_t lds = (size_t)(kSmallWaves + 2) * E * sizeof(int32_t);
+        RELIBRA_LAUNCH(RELIBRA_K_PERM_RANK, stream, perm_small_kernel<<<1, kSmallThreads, lds, stream>>>(ids_dev, N, E, G, ebits, tables,
+                                                                row_of_dev, src_of_dev, err_flag_dev, split));
+        RELIBRA_HIP_TRY(launch_check());
+    } else {
+        int32_t *unit_cnt = (int32_t *)workspace_dev;
+        const int n_units = (N + kUnit - 1) / kUnit;
+        const int blocks = (n_units + 3) / 4;
+        const size_t lds = (size_t)4 * E * sizeof(int32_t);
+        RELIBRA_LAUNCH(RELIBRA_K_PERM_COUNT, stream, perm_count_kernel<<<blocks, kPermThreads, lds, stream>>>(ids_dev, N, E, unit_cnt, src_of_dev, err_flag_dev));
+        RELIBRA_HIP_TRY(launch_check());
+        RELIBRA_LAUNCH(RELIBRA_K_PERM_SCAN, stream, perm_scan_kernel<<<E, 256, 0, stream>>>(unit_cnt, n_units, E));
+        RELIBRA_HIP_TRY(launch_check());
+        RELIBRA_LAUNCH(RELIBRA_K_PERM_RANK, stream, perm_rank_kernel<<<blocks, kPermThreads, lds, stream>>>(ids_dev, N, E, G, ebits, unit_cnt, tables,
+                                                                row_of_dev, src_of_dev, err_flag_dev, split));
+        RELIBRA_HIP_TRY(launch_check());
+    }
     if (with_rows) {
         const int vpr = h / 8, lpr_log2 = lanes_per_row_log2(vpr, 4);
         const int grid = grid_for((size_t)T, kRowThreads >> lpr_log2, 256 * 32);

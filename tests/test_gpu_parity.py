@@ -210,6 +210,23 @@ def test_timed_plan_drives_the_device_path():
     assert rel_l2(Y, Y_o) <= TOL
 
 
+@pytest.mark.parametrize("E,k,T,EP", [(4, 1, 1, 4), (8, 1, 1025, 4), (8, 2, 2048, 4), (8, 1, 4097, 4), (512, 4, 1024, 8),
+                                      (516, 2, 300, 4), (32, 4, 511, 8)])
+def test_permute_at_the_one_block_limits(E, k, T, EP):
+    """Sizes around a wave's share and around the largest ones that one block permutes."""
+    cfg = wl.small_config(E=E, k=k, EP=EP, r=1, T=T, n_mb=1, h=8)
+    ids, _ = routing(cfg)
+    p = plan_both(cfg, oracle.route_hist(ids, cfg.E)[0])
+    X = torch.randn((T, 8), generator=torch.Generator().manual_seed(T)).to(torch.bfloat16)
+    err = rl.new_err_flag()
+    row_of, src_of, Xrows = rl.relibra_permute(torch.from_numpy(ids[0]).to(DEV), *(dev_i32(p[key][0]) for key in (
+        "inst_ptr", "inst_rows", "inst_group", "group_offset")), X.to(DEV), cfg.E, cfg.G, err_flag=err)
+    want_row, want_src = oracle.permute(ids[0], cfg.E, *(p[key][0] for key in ("inst_ptr", "inst_rows", "inst_group", "group_offset")))
+    assert err.item() == 0
+    assert np.array_equal(row_of.cpu().numpy(), want_row) and np.array_equal(src_of.cpu().numpy(), want_src)
+    assert torch.equal(Xrows.cpu(), X[torch.from_numpy(want_src).long() // k])
+
+
 def test_permute_flags_a_plan_that_does_not_cover_the_routing():
     cfg = wl.small_config(E=8, k=2, EP=4, r=1, T=200, n_mb=1, h=64)
     ids, _ = routing(cfg)
