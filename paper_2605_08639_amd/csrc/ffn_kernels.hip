@@ -8,7 +8,8 @@
 // for twice the columns).  A group's tail of at most 64 rows runs as a 64-row tile.  Operand slabs
 // of 32 k-values go global -> LDS directly (global_load_lds, 16 bytes per lane) through a ring of
 // three slabs (four in the wide weight-gradient tile); the wide row tiles stage their rows 64
-// k-values deep (full 128-byte lines) in a ring of their own, 144 KiB of LDS in all; see gemm_tile.h
+// k-values deep (full 128-byte lines) in a ring of their own, 144 KiB of LDS in all, and weights that lie
+// k-contiguous too, half of their columns (or the gate, the up projection) at a time; see gemm_tile.h
 // for the tile layouts and the pipeline.
 //
 // MFMA operand roles: the lanes carry the index that is contiguous in the output's memory
@@ -375,8 +376,9 @@ __device__ __forceinline__ void fwd_gate_up_body(const RowTile &t, const bf16_t 
 {
     constexpr int NWV = AW == 128 ? NWAVES : kWideRowWaves;
     using WV = Waves<BB, NWV>;
-    using WTile = typename std::conditional<WT, KsTile<AW>, KcTile<AW>>::type;
-    using KL = KLoop<WTile, KcTile<BB, (AW == 128 ? BK : kRowDepthWide)>, 2, 1, AW, BB, WV::A, WV::B, 1, false, NSTAGES, kSpreadLoads>;
+    constexpr bool ALT = !WT && AW != 128;                    // k-contiguous weights in the wide tile: gate and up slabs in turn
+    using WTile = typename std::conditional<WT, KsTile<AW>, KcTile<AW, (ALT ? kRowDepthWide : BK), ALT>>::type;
+    using KL = KLoop<WTile, KcTile<BB, (AW == 128 ? BK : kRowDepthWide)>, 2, 1, AW, BB, WV::A, WV::B, 1, false, NSTAGES, kSpreadLoads, false, ALT>;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const size_t wofs = (size_t)t.expert * hff * h;
     const int ldw = WT ? hff : h;                             // (n in h', k in h) at [n*h + k], or at [k*h' + n]
@@ -465,21 +467,26 @@ __device__ __forceinline__ void row_gemm_body(const RowTile &t, const bf16_t *P0
 {
     constexpr int NWV = AW == 256 ? NWAVES : kWideRowWaves;
     using WV = Waves<BB, NWV>;
-    using WT = typename std::conditional<W_KS, KsTile<AW>, KcTile<AW>>::type;
-    using KL = KLoop<WT, KcTile<BB, (AW == 256 ? BK : kRowDepthWide)>, 1, 1, AW, BB, WV::A, WV::B, NPH, false, NSTAGES, kSpreadLoads>;
+    // k-contiguous weights in the wide tile: every wave's columns in two halves that take turns (KLoop, ALT)
+    constexpr bool ALT = !W_KS && AW != 256;
+    constexpr int NA = ALT ? 2 : 1, BA = AW / NA, SEG = ALT ? BA / WV::A : 0;
+    using WT = typename std::conditional<W_KS, KsTile<BA>, KcTile<BA, (ALT ? kRowDepthWide : BK), ALT>>::type;
+    using KL = KLoop<WT, KcTile<BB, (AW == 256 ? BK : kRowDepthWide)>, NA, 1, BA, BB, WV::A, WV::B, NPH, false, NSTAGES, kSpreadLoads, false, ALT>;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    Operand A[NPH][1], B[NPH][1];
-    A[0][0] = {W0, ldw, t.col0, n_dim - 1};
+    Operand A[NPH][NA], B[NPH][1];
+#pragma unroll
+    for (int a = 0; a < NA; ++a) A[0][a] = {W0, ldw, t.col0 + a * SEG, n_dim - 1, nullptr, 0, SEG};
     B[0][0] = {P0, ldp, t.row0, t.row0 + t.rows - 1};
     if (EPI == 2 && gf.row_tok) B[0][0] = {P0, ldp, t.row0, t.row0 + t.rows - 1, gf.row_tok, gf.tok_last};
     if (NPH == 2) {
-        A[NPH - 1][0] = {W1, ldw, t.col0, n_dim - 1};
+#pragma unroll
+        for (int a = 0; a < NA; ++a) A[NPH - 1][a] = {W1, ldw, t.col0 + a * SEG, n_dim - 1, nullptr, 0, SEG};
         B[NPH - 1][0] = {P1, ldp, t.row0, t.row0 + t.rows - 1};
     }
     typename KL::Acc acc;
     KL::zero(acc);
     KL::run(acc, A, B, k_dim / BK, k_dim, lds, tid);
-    constexpr int WCOLS = AW / WV::A;
+    constexpr int WCOLS = AW / WV::A, TALL = NA * KL::TA;     // a wave's columns: MFMA tile ta of TALL is tile ta % TA of half ta / TA
     using ST = WaveStage<WCOLS>;
     static_assert(KL::TB == 2, "a wave owns 64 rows");
     __syncthreads();                                          // every wave is done with the operand slabs
@@ -490,19 +497,19 @@ __device__ __forceinline__ void row_gemm_body(const RowTile &t, const bf16_t *P0
 #pragma unroll
         for (int tb = 0; tb < KL::TB; ++tb)
 #pragma unroll
-            for (int ta = 0; ta < KL::TA; ++ta)
+            for (int ta = 0; ta < TALL; ++ta)
 #pragma unroll
                 for (int q = 0; q < 4; ++q)
                     ST::put(buf, tb * 32 + (lane & 31), ta * 32 + q * 8 + (lane >> 5) * 4,
-                            pack4bf(acc[0][ta][tb][q * 4], acc[0][ta][tb][q * 4 + 1], acc[0][ta][tb][q * 4 + 2],
-                                    acc[0][ta][tb][q * 4 + 3]));
+                            pack4bf(acc[ta / KL::TA][ta % KL::TA][tb][q * 4], acc[ta / KL::TA][ta % KL::TA][tb][q * 4 + 1],
+                                    acc[ta / KL::TA][ta % KL::TA][tb][q * 4 + 2], acc[ta / KL::TA][ta % KL::TA][tb][q * 4 + 3]));
         wave_lds_fence();
         ST::flush(buf, out0, n_dim, wrow0, row_end, wcol0, n_dim, lane);
     } else {
         // dA (in the accumulators) -> dGt, dU, half of the wave's columns at a time: Gt and U come
         // in through two staging areas and are overwritten in place by dGt and dU.
         using SH = WaveStage<WCOLS / 2>;
-        constexpr int TAH = KL::TA / 2;
+        constexpr int TAH = TALL / 2;
         static_assert(TAH >= 1, "at least 64 columns per wave");
         char *buf_g = buf, *buf_u = buf + SH::BYTES;
         float gate[KL::TB], dsum[KL::TB];
@@ -534,7 +541,7 @@ __device__ __forceinline__ void row_gemm_body(const RowTile &t, const bf16_t *P0
                         unpack4bf(SH::get(buf_u, row, col), u);
 #pragma unroll
                         for (int e = 0; e < 4; ++e) {
-                            const float da = acc[0][ta][tb][q * 4 + e];
+                            const float da = acc[ta / KL::TA][ta % KL::TA][tb][q * 4 + e];
                             const float sg = sigmoidf_(g[e]);
                             if (EPI == 2) {
                                 pa[e] = da * (g[e] * sg * u[e]);

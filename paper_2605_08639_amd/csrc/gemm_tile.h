@@ -81,6 +81,10 @@ struct Operand {
     // gathered copy.  KcTile: r = the tile row.  KsTile: r = the contraction index.
     const int32_t *gather = nullptr;
     int gather_last = 0;
+    // Interleaved rows (KcTile, optional): the tile's rows are runs of `seg`, every second run of the
+    // operand's (row r of the tile is row0 + (r / seg) * 2 * seg + r % seg).
+    int seg = 0;
+    __device__ __forceinline__ int row_at(int r) const { return row0 + (seg ? r + r / seg * seg : r); }
 };
 
 // k-contiguous operand: LDS [row][BKT].
@@ -89,7 +93,9 @@ struct Operand {
 // BKT = 64: 128 bytes per row, 8 rows per block; g(r) = (r&7) ^ ((r>>3)&1).
 // Either way the 16-byte reads of any 8 (or 16) consecutive rows at one k offset fall into
 // distinct 16-byte bank groups.
-template <int ROWS, int BKT = BK>
+// WHOLE: every row of the tile exists and none is looked up.  A wave's load blocks then lie a fixed
+// number of rows apart, so that a lane's address is a uniform base plus one 32-bit offset.
+template <int ROWS, int BKT = BK, bool WHOLE = false>
 struct KcTile {
     static_assert(BKT == 32 || BKT == 64, "slab depth");
     static constexpr int DEPTH = BKT;
@@ -114,19 +120,30 @@ struct KcTile {
     // do not change along k, and a gathered row costs its index lookup once per tile.
     template <int NW>
     struct Lanes {
-        const bf16_t *p[per_wave<NW>()];
+        const bf16_t *p[WHOLE ? 1 : per_wave<NW>()];
+        long long step;                                // WHOLE: p[0] is uniform, block i starts i * step elements behind it
+        uint32_t lane_off;                             // and a lane's piece lies lane_off bytes from there
     };
     template <int NW>
     static __device__ __forceinline__ Lanes<NW> prepare(const Operand &op, int wave, int lane)
     {
         static_assert(BLOCKS % NW == 0 || NW % BLOCKS == 0, "rows must split evenly over the waves");
         Lanes<NW> ln;
+        if constexpr (WHOLE) {
+            static_assert(BKT == 64 && BLOCKS % NW == 0 && NW % 2 == 0, "the swizzle is the same in a wave's blocks");
+            const int r = wave * RPB + lane / PIECES;
+            // NW * RPB rows to the next block; interleaved runs (which that is a multiple of) are twice as far apart
+            ln.p[0] = op.base + (long long)op.row0 * op.ld;
+            ln.step = (long long)(op.seg ? 2 * NW * RPB : NW * RPB) * op.ld;
+            ln.lane_off = (uint32_t)((op.row_at(r) - op.row0) * op.ld + ((lane % PIECES) ^ swz(r)) * 8) * 2u;
+            return ln;
+        }
 #pragma unroll
         for (int i = 0; i < per_wave<NW>(); ++i) {
             const int j = (wave + i * NW) % BLOCKS;
             const int r = j * RPB + lane / PIECES;
             const int c = (lane % PIECES) ^ swz(r);
-            int grow = min(op.row0 + r, op.row_last);
+            int grow = min(op.row_at(r), op.row_last);
             if (op.gather) grow = min(max(op.gather[grow], 0), op.gather_last);
             ln.p[i] = op.base + (size_t)grow * op.ld + c * 8;
         }
@@ -141,7 +158,8 @@ struct KcTile {
     static __device__ __forceinline__ void load_one(char *lds, const Lanes<NW> &ln, const Idx<NW> &, int k0, int /*k_last*/, int wave,
                                                     int /*lane*/, int i)
     {
-        load_lds16(ln.p[i] + k0, lds + ((wave + i * NW) % BLOCKS) * 1024);
+        if constexpr (WHOLE) load_lds16_sv(ln.p[0] + (i * ln.step + k0), ln.lane_off, lds + (wave + i * NW) * 1024);
+        else load_lds16(ln.p[i] + k0, lds + ((wave + i * NW) % BLOCKS) * 1024);
     }
     template <int NW>
     static __device__ __forceinline__ void load(char *lds, const Lanes<NW> &ln, const Idx<NW> &ix, int k0, int k_last, int wave,
@@ -353,8 +371,15 @@ __device__ __forceinline__ bf16x8_t mask_frag(bf16x8_t f, int k_first, int k_val
 //   meets the other waves: slab t+1 is complete and nobody reads slab t any more,
 //   so it issues the loads of slab t+STAGES into slab t's place, runs half of the step's MFMAs,
 //   requests the first fragments of slab t+1 and runs the other half, which covers them.
+// ALT: two A operands that take turns, both sides 64 k-values deep.  Slab t holds 64 k-values of operand
+// t % 2 only, so that k-contiguous weights are fetched in full 128-byte lines with slabs (and a ring) of the
+// same size as 32 k-values of both would need; a slab pair shares one B tile.  n slabs cover n * 32 k-values.
+// Half lines cost the address units and the L1 as much as whole ones.  Forward on weights as stored, groups of
+// 100 to 2400 rows, 32 k-values of both operands -> 64 of each in turn: 64 experts of 7168 x 2048, 1200 rows
+// each, gate/up 5.08 -> 4.01 ms, down 2.45 -> 2.22; 128 of 2048 x 768, 300 rows each, 391 -> 325 and 205 -> 176 us:
+// what the same kernels take on transposed weight copies (4.09, 2.21 ms; 326, 170 us).
 template <class AT, class BT, int NA, int NB, int BA, int BB, int WA, int WB, int NPH, bool RAGGED_K, int STAGES = 4,
-          bool SPREAD = false, bool B_FIRST = false>
+          bool SPREAD = false, bool B_FIRST = false, bool ALT = false>
 struct KLoop {
     static constexpr int NW = WA * WB;
     static constexpr int DEPTH = AT::DEPTH;           // k-values per slab
@@ -366,11 +391,14 @@ struct KLoop {
     // period, so that a wave issues the same number of loads in every period: the period that
     // fills the A slab of slab w also fetches half (w+1) % 2 of B tile (w+1) / 2.  Row kernels only:
     // no ragged contraction, an even number of slabs per phase, spread loads.
-    static constexpr bool BD = BT::DEPTH == 2 * AT::DEPTH;
+    // ALT has the same B side: a B tile serves the slabs of both A operands.
+    static constexpr bool BD = ALT || BT::DEPTH == 2 * AT::DEPTH;
     static_assert((AT::DEPTH == BT::DEPTH || BD) && KSTEPS >= 2 && KSTEPS % 2 == 0, "slab depth");
     static_assert(!BD || (!RAGGED_K && SPREAD && STAGES >= 3), "deep B side: row kernels");
+    static_assert(!ALT || (NA == 2 && NB == 1 && AT::DEPTH == 64 && BT::DEPTH == 64 && STAGES % 2 == 1), "two operands in turn");
+    static constexpr int NS = ALT ? 1 : NA;            // A operands of one slab
     static constexpr int TA = BA / WA / 32, TB = BB / WB / 32;
-    static constexpr int A_STAGE = NA * AT::BYTES, B_STAGE = NB * BT::BYTES;
+    static constexpr int A_STAGE = NS * AT::BYTES, B_STAGE = NB * BT::BYTES;
     static constexpr int STAGE_BYTES = BD ? A_STAGE : A_STAGE + B_STAGE;      // stride of the (A) ring
     static constexpr int SB = (STAGES + 3) / 2;        // B ring depth (BD): tile U - SB is dead when tile U's first half is issued
     static constexpr int B_RING = STAGES * A_STAGE;    // offset of the B ring (BD)
@@ -378,11 +406,11 @@ struct KLoop {
     template <class T, bool DEEP> struct PerWaveB { static constexpr int N = T::template per_wave<NW>(); };
     template <class T> struct PerWaveB<T, true> { static constexpr int N = T::template per_wave_half<NW>(); };
     static constexpr int LA = AT::template per_wave<NW>(), LB = PerWaveB<BT, BD>::N;
-    static constexpr int LOADS = NA * LA + NB * LB;   // per wave per slab
+    static constexpr int LOADS = NS * LA + NB * LB;   // per wave per slab
     typedef f32x16_t Acc[NA * NB][TA][TB];
 
     struct Frags {
-        bf16x8_t a[NA][TA], b[NB][TB];
+        bf16x8_t a[NS][TA], b[NB][TB];
     };
 
     template <class T, bool DEEP> struct LanesOfB { typedef typename T::template Lanes<NW> type; };
@@ -400,7 +428,7 @@ struct KLoop {
     };
     static __device__ __forceinline__ Where where(char *lds, int slot, int t)
     {
-        if (BD) return Where{lds + slot * A_STAGE, lds + B_RING + ((t >> 1) % SB) * B_STAGE, (t & 1) * KSTEPS};
+        if (BD) return Where{lds + slot * A_STAGE, lds + B_RING + ((t >> 1) % SB) * B_STAGE, ALT ? 0 : (t & 1) * KSTEPS};
         return Where{lds + slot * STAGE_BYTES, lds + slot * STAGE_BYTES + A_STAGE, 0};
     }
     // BD: the B loads of the period that fills slab w's A tiles: half (w+1) % 2 of B tile (w+1) / 2; past the last
@@ -409,8 +437,15 @@ struct KLoop {
         char *tile;
         int k0, half, q;
     };
+    // POS >= 0: w % (2 * SB), and the tile exists: ring place and half are constants.
+    template <int POS = -1>
     static __device__ __forceinline__ BWindow b_window(char *lds, int w, int steps_per_phase, int n)
     {
+        if constexpr (POS >= 0) {
+            const int u = (w + 1) >> 1, ph = (NPH == 1) ? 0 : (2 * u >= steps_per_phase ? 1 : 0);
+            return BWindow{lds + B_RING + (((POS + 1) >> 1) % SB) * B_STAGE, (u - ph * (steps_per_phase >> 1)) * BT::DEPTH, (POS + 1) & 1,
+                           (NPH == 1 || ph == 0) ? 0 : NPH - 1};
+        }
         const int tiles = n >> 1;
         const int u = min((w + 1) >> 1, tiles - 1);
         const int ph = (NPH == 1) ? 0 : (2 * u >= steps_per_phase ? 1 : 0);
@@ -488,7 +523,7 @@ struct KLoop {
     static __device__ __forceinline__ void read_frags(Frags &f, const Where &at, int kk, int wa, int wb, int lane)
     {
 #pragma unroll
-        for (int a = 0; a < NA; ++a)
+        for (int a = 0; a < NS; ++a)
 #pragma unroll
             for (int t = 0; t < TA; ++t) f.a[a][t] = AT::frag(at.a + a * AT::BYTES, wa * (BA / WA) + t * 32, kk, lane);
 #pragma unroll
@@ -501,7 +536,7 @@ struct KLoop {
     static __device__ __forceinline__ void mask_frags(Frags &f, int k_first, int k_valid)
     {
 #pragma unroll
-        for (int a = 0; a < NA; ++a)
+        for (int a = 0; a < NS; ++a)
 #pragma unroll
             for (int t = 0; t < TA; ++t) f.a[a][t] = mask_frag(f.a[a][t], k_first, k_valid);
 #pragma unroll
@@ -514,22 +549,23 @@ struct KLoop {
     // B_FIRST, last (an operand gathered through per-slab row lookups belongs in the later part of
     // the window, where its lookups have had time to arrive).
     // stage: the ring slot of slab t's A tiles; lds: the ring's base; n: slabs of the whole loop (BD only).
-    template <bool STEADY = false>
+    // PAR: parity of slab t; POS: t % TRIP where that is a constant (both ALT).
+    template <bool STEADY = false, int PAR = 0, int POS = -1>
     static __device__ __forceinline__ void issue_one(char *stage, const LanesA (&PA)[NPH][NA], const LanesB (&PB)[NPH][NB],
                                                      const Lookups &lk, int t, int steps_per_phase, int k_last, int wave, int lane, int j,
                                                      char *lds = nullptr, int n = 0)
     {
         const int ph = (NPH == 1) ? 0 : (t >= steps_per_phase ? 1 : 0);
-        const int k0 = (t - ph * steps_per_phase) * DEPTH;
+        const int k0 = ALT ? ((t - ph * steps_per_phase) >> 1) * DEPTH : (t - ph * steps_per_phase) * DEPTH;
         const int q = (NPH == 1 || ph == 0) ? 0 : NPH - 1;
-        const bool a_side = B_FIRST ? j >= NB * LB : j < NA * LA;
+        const bool a_side = B_FIRST ? j >= NB * LB : j < NS * LA;
         if (a_side) {
-            const int ja = B_FIRST ? j - NB * LB : j, a = ja / LA;
-            AT::template load_one<NW, STEADY>(stage + a * AT::BYTES, PA[q][a], lk.a[a], k0, k_last, wave, lane, ja % LA);
+            const int ja = B_FIRST ? j - NB * LB : j, at = ja / LA, a = ALT ? PAR : at;
+            AT::template load_one<NW, STEADY>(stage + at * AT::BYTES, PA[q][a], lk.a[a], k0, k_last, wave, lane, ja % LA);
         } else {
-            const int jb = B_FIRST ? j : j - NA * LA, b = jb / LB;
+            const int jb = B_FIRST ? j : j - NS * LA, b = jb / LB;
             if constexpr (BD) {
-                const BWindow bw = b_window(lds, t, steps_per_phase, n);
+                const BWindow bw = b_window<POS>(lds, t, steps_per_phase, n);
                 BT::template load_half_one<NW>(bw.tile + b * BT::BYTES, PB[bw.q][b], bw.k0, wave, bw.half, jb % LB);
             } else {
                 BT::template load_one<NW, STEADY>(stage + NA * AT::BYTES + b * BT::BYTES, PB[q][b], lk.b[b], k0, k_last, wave, lane, jb % LB);
@@ -538,20 +574,20 @@ struct KLoop {
     }
 
     // Fragment number j (0 .. N_FRAGS-1) of MFMA step kk: A side first.
-    static constexpr int N_FRAGS = NA * TA + NB * TB;
+    static constexpr int N_FRAGS = NS * TA + NB * TB;
     static __device__ __forceinline__ void read_frag_one(Frags &f, const Where &at, int kk, int wa, int wb, int lane, int j)
     {
-        if (j < NA * TA) {
+        if (j < NS * TA) {
             const int a = j / TA, t = j % TA;
             f.a[a][t] = AT::frag(at.a + a * AT::BYTES, wa * (BA / WA) + t * 32, kk, lane);
         } else {
-            const int b = (j - NA * TA) / TB, t = (j - NA * TA) % TB;
+            const int b = (j - NS * TA) / TB, t = (j - NS * TA) % TB;
             f.b[b][t] = BT::frag(at.b + b * BT::BYTES, wb * (BB / WB) + t * 32, at.kb + kk, lane);
         }
     }
 
-    // MFMAs number lo .. hi-1 of the NA*NB*TA*TB of one k16 step (all of them: 0 .. N_MFMA)
-    static constexpr int N_MFMA = NA * NB * TA * TB;
+    // MFMAs number lo .. hi-1 of the NS*NB*TA*TB of one k16 step (all of them: 0 .. N_MFMA)
+    static constexpr int N_MFMA = NS * NB * TA * TB;
     template <int LO, int HI>
     static __device__ __forceinline__ void mfma_range(Acc &acc, const Frags &f)
     {
@@ -571,10 +607,11 @@ struct KLoop {
     }
     static __device__ __forceinline__ void mfma_all(Acc &acc, const Frags &f) { mfma_range<0, N_MFMA>(acc, f); }
 
+    template <int PAR = 0>
     static __device__ __forceinline__ void mfma_one(Acc &acc, const Frags &f, int idx)
     {
-        const int tb = idx % TB, ta = (idx / TB) % TA, ab = idx / (TA * TB);
-        acc[ab][ta][tb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.a[ab / NB][ta], f.b[ab % NB][tb], acc[ab][ta][tb], 0, 0, 0);
+        const int tb = idx % TB, ta = (idx / TB) % TA, ab = ALT ? PAR : idx / (TA * TB);
+        acc[ab][ta][tb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.a[ALT ? 0 : ab / NB][ta], f.b[ab % NB][tb], acc[ab][ta][tb], 0, 0, 0);
     }
 
     // Spread loads (SPREAD): a slab's loads go out one by one between the MFMAs of a slab period
@@ -589,14 +626,15 @@ struct KLoop {
     // when the step ends), then the loads whose window position falls behind this MFMA.
     // part = 0 for the last step of a slab, s + 1 for step s < KSTEPS - 1.
     // ALWAYS: the loads are issued unconditionally (steady state); otherwise if do_load.
-    template <bool ALWAYS, class LoadFn>
+    // A step of ALT is only half as many MFMAs, so its fragment reads go out in the first half.
+    template <bool ALWAYS, int PAR = 0, class LoadFn>
     static __device__ __forceinline__ void step_spread(Acc &acc, const Frags &fc, Frags &fn, const Where &rd_stage, int rd_kk, int wa,
                                                        int wb, int lane, int part, bool do_load, const LoadFn &load_j)
     {
-        constexpr int SPAN = N_MFMA >= 4 ? N_MFMA - N_MFMA / 4 : N_MFMA;
+        constexpr int SPAN = ALT ? (N_MFMA + 1) / 2 : N_MFMA >= 4 ? N_MFMA - N_MFMA / 4 : N_MFMA;
 #pragma unroll
         for (int m = 0; m < N_MFMA; ++m) {
-            mfma_one(acc, fc, m);
+            mfma_one<PAR>(acc, fc, m);
 #pragma unroll
             for (int j = 0; j < N_FRAGS; ++j)
                 if (j * SPAN / N_FRAGS == m) read_frag_one(fn, rd_stage, rd_kk, wa, wb, lane, j);
@@ -624,12 +662,15 @@ struct KLoop {
         }
     }
 
-    // One trip of the steady state: slabs t .. t+STAGES-1 in ring slots 1, 2, .., 0 (t % STAGES == 1).
+    // One trip of the steady state: slabs t .. t+TRIP-1 in ring slots 1, 2, .., 0 (t % TRIP == 1).  ALT: a trip
+    // is a whole turn of both rings, so that every place in them is a constant.
+    static constexpr int TRIP = ALT ? 2 * STAGES : STAGES;
+    static_assert(!ALT || TRIP == 2 * SB, "a trip turns both rings");
     template <class Slab, int U>
     static __device__ __forceinline__ void steady_trip(const Slab &slab, int t, std::integral_constant<int, U>)
     {
-        if constexpr (U < STAGES) {
-            slab(std::true_type{}, std::integral_constant<int, (1 + U) % STAGES>{}, t + U);
+        if constexpr (U < TRIP) {
+            slab(std::true_type{}, std::integral_constant<int, (1 + U) % TRIP>{}, std::integral_constant<int, ALT ? (1 + U) & 1 : 0>{}, t + U);
             steady_trip(slab, t, std::integral_constant<int, U + 1>{});
         }
     }
@@ -653,12 +694,15 @@ struct KLoop {
             // the first half of B tile 0 belongs to no period of the loop: it goes first
 #pragma unroll
             for (int j = 0; j < LOADS; ++j)
-                if ((B_FIRST ? j < NB * LB : j >= NA * LA)) issue_one(lds, PA, PB, lk, -1, steps_per_phase, k_last, wave, lane, j, lds, n);
+                if ((B_FIRST ? j < NB * LB : j >= NS * LA)) issue_one(lds, PA, PB, lk, -1, steps_per_phase, k_last, wave, lane, j, lds, n);
 #pragma unroll
             for (int i = 0; i < STAGES; ++i)
                 if (i < n) {
 #pragma unroll
-                    for (int j = 0; j < LOADS; ++j) issue_one(lds + i * STAGE_BYTES, PA, PB, lk, i, steps_per_phase, k_last, wave, lane, j, lds, n);
+                    for (int j = 0; j < LOADS; ++j) {
+                        if (ALT && (i & 1)) issue_one<false, 1>(lds + i * STAGE_BYTES, PA, PB, lk, i, steps_per_phase, k_last, wave, lane, j, lds, n);
+                        else issue_one(lds + i * STAGE_BYTES, PA, PB, lk, i, steps_per_phase, k_last, wave, lane, j, lds, n);
+                    }
                 }
         } else {
 #pragma unroll
@@ -681,16 +725,20 @@ struct KLoop {
             // instruction on addresses) - one copy per ring slot, run STAGES slabs per trip - and the
             // general one (ring slot in a register) for the first slab and the last few.
             char *prv = lds;
-            auto slab = [&](auto steady, auto slot_c, int t) __attribute__((always_inline)) {
+            auto slab = [&](auto steady, auto pos_c, auto par_c, int t) __attribute__((always_inline)) {
                 constexpr bool SS = decltype(steady)::value;
-                constexpr int SLOT = decltype(slot_c)::value;          // -1: the ring slot is the variable `slot`
+                constexpr int PAR = decltype(par_c)::value;            // ALT: parity of t
+                constexpr int PREV = ALT ? (PAR + STAGES + 1) & 1 : 0, NEXT = ALT ? (PAR + STAGES) & 1 : 0;   // of the slabs loaded
+                constexpr int POS = decltype(pos_c)::value;            // t % TRIP; -1: the ring slot is the variable `slot`
+                constexpr int SLOT = POS < 0 ? -1 : POS % STAGES;
+                constexpr int BPOS = ALT ? POS : -1, PPOS = BPOS < 0 ? -1 : (POS - 1 + STAGES) % TRIP, NPOS = BPOS < 0 ? -1 : (POS + STAGES) % TRIP;
                 const bool ls = SS || (t >= 1 && t - 1 + STAGES < n), ll = SS || t + STAGES < n;
                 char *cur, *before;
                 Where cur_at, nxt_at;
                 if (SLOT >= 0) {
                     cur = lds + SLOT * STAGE_BYTES;
-                    cur_at = where(lds, SLOT, t);
-                    nxt_at = where(lds, (SLOT + 1) % STAGES, t + 1);
+                    cur_at = where(lds, SLOT, ALT ? POS : t);
+                    nxt_at = where(lds, (SLOT + 1) % STAGES, ALT ? (POS + 1) % TRIP : t + 1);
                     before = lds + ((SLOT + STAGES - 1) % STAGES) * STAGE_BYTES;
                 } else {
                     cur = lds + slot * STAGE_BYTES;
@@ -702,14 +750,14 @@ struct KLoop {
                 const bool tail = !SS && RAGGED_K && (t + 1) * DEPTH > k_valid;
                 const int kf = t * DEPTH + (lane >> 5) * 8;
                 // steps 0 .. KSTEPS-2: the rest of the loads of slab t-1+STAGES, into slab t-1's place
-                auto load_prev = [&](int j) __attribute__((always_inline)) { issue_one<SS>(before, PA, PB, lk, t - 1 + STAGES, steps_per_phase, k_last, wave, lane, j, lds, n); };
+                auto load_prev = [&](int j) __attribute__((always_inline)) { issue_one<SS, PREV, PPOS>(before, PA, PB, lk, t - 1 + STAGES, steps_per_phase, k_last, wave, lane, j, lds, n); };
 #pragma unroll
                 for (int s = 0; s < KSTEPS - 1; ++s) {
                     __builtin_amdgcn_s_waitcnt(0xC07F);          // lgkmcnt(0): f[s & 1] is there
                     __builtin_amdgcn_sched_barrier(0);
                     if (tail) mask_frags(f[s & 1], kf + s * 16, k_valid);
                     __builtin_amdgcn_sched_barrier(0);
-                    step_spread<SS>(acc, f[s & 1], f[(s + 1) & 1], cur_at, s + 1, wa, wb, lane, s + 1, ls, load_prev);
+                    step_spread<SS, PAR>(acc, f[s & 1], f[(s + 1) & 1], cur_at, s + 1, wa, wb, lane, s + 1, ls, load_prev);
                 }
                 if (SS) wait_younger(STAGES);  // slab t+1 has landed; later slabs may still be in flight
                 else wait_younger(n - t - 2);
@@ -720,22 +768,27 @@ struct KLoop {
                 // side has its loads in the later part of the window, a step's MFMAs from here.
                 if (ll) fetch(lk, PA, PB, t + STAGES, steps_per_phase, k_last, wave);
                 // last step: the first loads of slab t+STAGES, into this slab's place
-                auto load_cur = [&](int j) __attribute__((always_inline)) { issue_one<SS>(cur, PA, PB, lk, t + STAGES, steps_per_phase, k_last, wave, lane, j, lds, n); };
+                auto load_cur = [&](int j) __attribute__((always_inline)) { issue_one<SS, NEXT, NPOS>(cur, PA, PB, lk, t + STAGES, steps_per_phase, k_last, wave, lane, j, lds, n); };
                 constexpr int L = (KSTEPS - 1) & 1;
                 if (tail) mask_frags(f[L], kf + (KSTEPS - 1) * 16, k_valid);
-                step_spread<SS>(acc, f[L], f[0], nxt_at, 0, wa, wb, lane, 0, ll, load_cur);
+                step_spread<SS, PAR>(acc, f[L], f[0], nxt_at, 0, wa, wb, lane, 0, ll, load_cur);
                 if (SLOT < 0) prv = cur;
             };
             constexpr auto dyn = std::integral_constant<int, -1>{};
-            slab(std::false_type{}, dyn, 0);
+            constexpr auto even = std::integral_constant<int, 0>{};
+            constexpr auto odd = std::integral_constant<int, ALT ? 1 : 0>{};
+            slab(std::false_type{}, dyn, even, 0);
             int t = 1;
             // Steady trips: slab t sits in ring slot t % STAGES (t = 1 in slot 1); a trip leaves `slot`
             // and `prv` as they are.  The loads a steady slab issues are those of slabs t-1+STAGES and
             // t+STAGES, which must be whole (no clamped k-rows): the last slab of a ragged contraction
-            // is left to the general copy.
-            const int steady_end = n - STAGES - (RAGGED_K ? 1 : 0);
-            for (; t + STAGES <= steady_end; t += STAGES) steady_trip(slab, t, std::integral_constant<int, 0>{});
-            for (; t < n; ++t) slab(std::false_type{}, dyn, t);
+            // is left to the general copy; so is ALT's last period, which loads no new B tile.
+            const int steady_end = n - STAGES - (RAGGED_K || ALT ? 1 : 0);
+            for (; t + TRIP <= steady_end; t += TRIP) steady_trip(slab, t, std::integral_constant<int, 0>{});
+            for (; t < n; ++t) {
+                if (ALT && (t & 1)) slab(std::false_type{}, dyn, odd, t);
+                else slab(std::false_type{}, dyn, even, t);
+            }
         } else {
         for (int t = 0; t < n; ++t) {
             char *cur = lds + slot * STAGE_BYTES;

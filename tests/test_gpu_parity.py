@@ -783,6 +783,69 @@ def test_forward_with_transposed_weights_is_bit_identical(case):
     assert rel_l2(swapped[3][lv], Y_o[live]) <= TOL
 
 
+def many_group_case(seed, h, hff):
+    """Rows of every kind of tile in the first groups, then enough short groups that the wide tiles are taken."""
+    rng = np.random.default_rng(seed)
+    first = (300, 64, 65, 1, 0, 130)
+    rows = (*first, *rng.integers(1, 9, 160).tolist())
+    case = ffn_case(seed=seed, E=3, h=h, hff=hff, rows=rows, experts=(1, 0, 2, 1, -1, 0, *rng.integers(0, 3, 160).tolist()))
+    return len(first), case
+
+
+@pytest.mark.parametrize("h,hff", [(k, 512) for k in (64, 128, 192, 256, 320, 384, 448, 512, 832)]
+                         + [(1024, k) for k in (64, 128, 192, 320, 384)] + [(960, 1472), (1472, 704), (512, 960)])
+def test_wide_tiles_on_weights_as_stored(h, hff):
+    """The wide tiles take k-contiguous weights 64 k-values of one half of their columns at a time.  Contractions
+    of every remainder of a trip through the LDS rings, row tiles of both heights, output widths that the tiles
+    do not divide: bit for bit what the same products on transposed copies give, and within the bar of the oracle."""
+    n_first, (go, ge, X, dY, Wg, Wu, Wd) = many_group_case(h + hff, h, hff)
+    Xd, dYd, W_d = X.to(DEV), dY.to(DEV), [W.to(DEV) for W in (Wg, Wu, Wd)]
+    W_t = [rl.relibra_transpose_experts(W) for W in W_d]
+    go_d, ge_d, sl_d = dev_i32(go), dev_i32(ge), dev_i32(np.maximum(ge, 0))
+    err = rl.new_err_flag()
+    mk = lambda cols: torch.zeros((X.shape[0], cols), dtype=torch.bfloat16, device=DEV)
+    outs = []
+    for W3, ffl, bfl in ((W_d, 0, 0), (W_t, rl.FWD_TRANSPOSED_WEIGHTS, rl.BWD_TRANSPOSED_WEIGHTS)):
+        out = rl.relibra_moe_ffn_fwd(Xd, go_d, ge_d, *W3, Gt=mk(hff), U=mk(hff), A=mk(hff), Yrows=mk(h), err_flag=err, flags=ffl)
+        dX = rl.relibra_moe_ffn_bwd(dYd, None, *out[:3], go_d, ge_d, sl_d, *W3, None, None, None, dXrows=mk(h), err_flag=err, E=3,
+                                    flags=bfl | rl.BWD_DEFER_WGRAD)
+        outs.append((*out, dX))
+    assert err.item() == 0
+    for plain, swapped in zip(*outs):
+        assert torch.equal(plain, swapped)
+    # the short groups are checked through the transposed copies' kernels, the first ones against the oracle
+    n = go[n_first]
+    go_o, ge_o = go[:n_first + 1], ge[:n_first]
+    for got, want in zip(outs[0], (*oracle.ffn_fwd(X[:n], go_o, ge_o, Wg, Wu, Wd), oracle.ffn_bwd(X[:n], dY[:n], go_o, ge_o, Wg, Wu, Wd)[0])):
+        assert rel_l2(got[:n], want) <= TOL
+
+
+@pytest.mark.parametrize("h,hff", [(512, 1024), (960, 1472), (512, 960)])
+def test_gate_fused_backward_on_wide_tiles(h, hff):
+    """Gates that are powers of two scale without rounding: the gate-fused data gradients then equal, bit for bit,
+    the unfused ones on the scaled rows; dgate = <dOut, Y> within the bar.  Wide tiles, also where they reach
+    beyond the columns."""
+    _, (go, ge, X, dY, Wg, Wu, Wd) = many_group_case(7 * h + hff, h, hff)
+    N = X.shape[0]
+    gate = torch.from_numpy(np.random.default_rng(h).choice([0.25, 0.5, 1.0, 2.0], N).astype(np.float32)).to(DEV)
+    tok = torch.arange(N, dtype=torch.int32, device=DEV)
+    Xd, dO, W_d = X.to(DEV), dY.to(DEV), [W.to(DEV) for W in (Wg, Wu, Wd)]
+    go_d, ge_d, sl_d = dev_i32(go), dev_i32(ge), dev_i32(np.maximum(ge, 0))
+    err = rl.new_err_flag()
+    Gt, U, A, Y = rl.relibra_moe_ffn_fwd(Xd, go_d, ge_d, *W_d, err_flag=err)
+    guard = 1 << 16
+    need = rl.workspace_bytes(rl.WS_DGATE, N, 1, 3, len(ge), h, hff)
+    scratch = torch.full((need + guard,), 99, dtype=torch.uint8, device=DEV)
+    got, dgate = rl.relibra_moe_ffn_bwd_gated(dO, tok, gate, Gt, U, go_d, ge_d, sl_d, *W_d, E=3, dgate_scratch=scratch, err_flag=err)
+    want = rl.relibra_moe_ffn_bwd((gate[:, None] * dO.float()).to(torch.bfloat16), None, Gt, U, A, go_d, ge_d, sl_d, *W_d, None, None, None,
+                                  E=3, flags=rl.BWD_DEFER_WGRAD, err_flag=err)
+    assert err.item() == 0
+    live = torch.from_numpy(np.concatenate([np.arange(go[g], go[g + 1]) for g in range(len(ge)) if ge[g] >= 0])).to(DEV)
+    assert torch.equal(got[live], want[live])
+    assert rel_l2(dgate[live], (dO.double() * Y.double()).sum(1)[live].cpu().numpy()) <= TOL
+    assert (scratch[need:] == 99).all()
+
+
 # ------------------------------------------------------------------ row gather fused into the GEMMs
 def test_forward_with_fused_row_gather_is_bit_identical():
     """relibra_moe_ffn_fwd_gather reads row `row` as X[row_tok[row]]: the same operands in the same
