@@ -287,8 +287,9 @@ struct WaveStage {
     // row-major side: stage -> global, rows grow0.. of a tensor with leading dimension ld.
     // All LDS reads first, then the (predicated) stores: left to itself the compiler moves every
     // read into the branch of its store, and each store then waits for its own read in turn.
+    // Only columns col_from <= c < n_dim are stored.
     static __device__ __forceinline__ void flush(const char *buf, bf16_t *out, int ld, int grow0, int row_end,
-                                                 int gcol0, int n_dim, int lane)
+                                                 int gcol0, int n_dim, int lane, int col_from = 0)
     {
         uint4 v[PASSES];
 #pragma unroll
@@ -302,7 +303,7 @@ struct WaveStage {
 #pragma unroll
         for (int p = 0; p < PASSES; ++p) {
             const int r = p * ROWS_PER_PASS + lane / PIECES, piece = lane % PIECES;
-            if (grow0 + r < row_end && gcol0 + piece * 8 < n_dim)
+            if (grow0 + r < row_end && gcol0 + piece * 8 < n_dim && gcol0 + piece * 8 >= col_from)
                 *reinterpret_cast<uint4 *>(out + (size_t)(grow0 + r) * ld + gcol0 + piece * 8) = v[p];
         }
     }
@@ -382,7 +383,8 @@ __device__ __forceinline__ void fwd_gate_up_body(const RowTile &t, const bf16_t 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const size_t wofs = (size_t)t.expert * hff * h;
     const int ldw = WT ? hff : h;                             // (n in h', k in h) at [n*h + k], or at [k*h' + n]
-    const Operand A[1][2] = {{{Wg + wofs, ldw, t.col0, hff - 1}, {Wu + wofs, ldw, t.col0, hff - 1}}};
+    const int col0 = ALT ? min(t.col0, hff - AW) : t.col0;    // ALT tiles are whole: the last one starts earlier and stores its own columns only
+    const Operand A[1][2] = {{{Wg + wofs, ldw, col0, hff - 1}, {Wu + wofs, ldw, col0, hff - 1}}};
     // rows of the group: a gathered copy (row_tok == nullptr), or token rows fetched through row_tok
     const Operand B[1][1] = {{{X, h, t.row0, t.row0 + t.rows - 1, row_tok, tok_last}}};
     typename KL::Acc acc;
@@ -395,7 +397,7 @@ __device__ __forceinline__ void fwd_gate_up_body(const RowTile &t, const bf16_t 
     __syncthreads();                                          // every wave is done with the operand slabs
     char *buf = lds + wave * ST::BYTES;
     const int wrow0 = t.row0 + (wave % WV::B) * 64, row_end = t.row0 + t.rows;
-    const int wcol0 = t.col0 + (wave / WV::B) * WCOLS;
+    const int wcol0 = col0 + (wave / WV::B) * WCOLS;
     // With row gates: the activations scaled by the gate of the row's assignment, as a fourth tensor
     // (Agout) or, with Agout == Aout, in place of the plain ones (the down projection then yields
     // gated rows and the combine is a plain sum).
@@ -422,7 +424,7 @@ __device__ __forceinline__ void fwd_gate_up_body(const RowTile &t, const bf16_t 
                     ST::put(buf, tb * 32 + (lane & 31), ta * 32 + q * 8 + (lane >> 5) * 4, pack4bf(v[0], v[1], v[2], v[3]));
                 }
         wave_lds_fence();
-        ST::flush(buf, which == 0 ? Gt : which == 1 ? U : which == 2 ? Aout : Agout, hff, wrow0, row_end, wcol0, hff, lane);
+        ST::flush(buf, which == 0 ? Gt : which == 1 ? U : which == 2 ? Aout : Agout, hff, wrow0, row_end, wcol0, hff, lane, t.col0);
         wave_lds_fence();
     }
 }
@@ -474,13 +476,14 @@ __device__ __forceinline__ void row_gemm_body(const RowTile &t, const bf16_t *P0
     using KL = KLoop<WT, KcTile<BB, (AW == 256 ? BK : kRowDepthWide)>, NA, 1, BA, BB, WV::A, WV::B, NPH, false, NSTAGES, kSpreadLoads, false, ALT>;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     Operand A[NPH][NA], B[NPH][1];
+    const int col0 = ALT ? min(t.col0, n_dim - AW) : t.col0;  // ALT tiles are whole: the last one starts earlier and stores its own columns only
 #pragma unroll
-    for (int a = 0; a < NA; ++a) A[0][a] = {W0, ldw, t.col0 + a * SEG, n_dim - 1, nullptr, 0, SEG};
+    for (int a = 0; a < NA; ++a) A[0][a] = {W0, ldw, col0 + a * SEG, n_dim - 1, nullptr, 0, SEG};
     B[0][0] = {P0, ldp, t.row0, t.row0 + t.rows - 1};
     if (EPI == 2 && gf.row_tok) B[0][0] = {P0, ldp, t.row0, t.row0 + t.rows - 1, gf.row_tok, gf.tok_last};
     if (NPH == 2) {
 #pragma unroll
-        for (int a = 0; a < NA; ++a) A[NPH - 1][a] = {W1, ldw, t.col0 + a * SEG, n_dim - 1, nullptr, 0, SEG};
+        for (int a = 0; a < NA; ++a) A[NPH - 1][a] = {W1, ldw, col0 + a * SEG, n_dim - 1, nullptr, 0, SEG};
         B[NPH - 1][0] = {P1, ldp, t.row0, t.row0 + t.rows - 1};
     }
     typename KL::Acc acc;
@@ -492,7 +495,7 @@ __device__ __forceinline__ void row_gemm_body(const RowTile &t, const bf16_t *P0
     __syncthreads();                                          // every wave is done with the operand slabs
     char *buf = lds + wave * ST::BYTES;
     const int wrow0 = t.row0 + (wave % WV::B) * 64, row_end = t.row0 + t.rows;
-    const int wcol0 = t.col0 + (wave / WV::B) * WCOLS;
+    const int wcol0 = col0 + (wave / WV::B) * WCOLS;
     if (EPI == 0) {
 #pragma unroll
         for (int tb = 0; tb < KL::TB; ++tb)
@@ -504,7 +507,7 @@ __device__ __forceinline__ void row_gemm_body(const RowTile &t, const bf16_t *P0
                             pack4bf(acc[ta / KL::TA][ta % KL::TA][tb][q * 4], acc[ta / KL::TA][ta % KL::TA][tb][q * 4 + 1],
                                     acc[ta / KL::TA][ta % KL::TA][tb][q * 4 + 2], acc[ta / KL::TA][ta % KL::TA][tb][q * 4 + 3]));
         wave_lds_fence();
-        ST::flush(buf, out0, n_dim, wrow0, row_end, wcol0, n_dim, lane);
+        ST::flush(buf, out0, n_dim, wrow0, row_end, wcol0, n_dim, lane, t.col0);
     } else {
         // dA (in the accumulators) -> dGt, dU, half of the wave's columns at a time: Gt and U come
         // in through two staging areas and are overwritten in place by dGt and dU.
@@ -1139,9 +1142,21 @@ static int ensure_lds_limits()
 
 static inline unsigned grid8(long long tiles) { return (unsigned)((tiles + 7) / 8 * 8); }
 
-// The wide column tiles are taken where they divide the output (a ragged last tile of that width
-// would idle half a workgroup).
-static inline bool row_tiles_wide(int n_dim, int width) { return n_dim % width == 0; }
+// The wide column tiles are taken where they pad the output's columns no further than the narrow ones do
+// (half of all widths), and where there are more narrow tiles than the compute units can take one each (and an
+// eighth): fewer tiles leave units idle that tiles of half the width would use.  Row tiles are estimated: half a
+// tile per group for its tail.  Measured, narrow -> wide, us: 64 groups, 4032 x 1472 (pads alike), 100 rows each:
+// gate/up 394 -> 324, down 186 -> 174, dA 200 -> 176, dX 329 -> 311; 1200 rows each: 2146 -> 1723, 1076 -> 948,
+// 1056 -> 980, 1820 -> 1694.  3136 columns (8 % more padding): down 521 -> 534.  8 groups of 512 x 1024, 200
+// rows each (few tiles): gate/up 17 -> 22, down 19 -> 26, dA 20 -> 28, dX 27 -> 42; 8 of 4096 x 14336, dX at 32
+// rows 416 -> 608, at 200 rows 536 -> 676, at 300 rows (384 narrow tiles) 918 -> 684.
+constexpr int kComputeUnits = 256;
+static inline bool row_tiles_wide(int n_dim, int width, int n_rows, int groups)
+{
+    const long long wide = (n_dim + width - 1) / width, narrow = (n_dim + width / 2 - 1) / (width / 2);
+    const long long row_tiles = std::max((long long)groups, (long long)n_rows / BM + groups / 2);
+    return n_dim >= width && 2 * wide == narrow && row_tiles * narrow > kComputeUnits + kComputeUnits / 8;
+}
 
 // Launch of a row-tiled GEMM kernel template <bool WT, int AW>: narrow (four waves, two workgroups
 // per compute unit) or wide (eight waves, one) column tiles.
@@ -1186,9 +1201,8 @@ static int ffn_fwd_impl(const void *Xrows, const int32_t *row_tok, int T, int n_
     RELIBRA_LAUNCH(RELIBRA_K_SCHED, stream, sched_kernel<<<1, 256, (size_t)(Gr + 1) * sizeof(int32_t), stream>>>(group_offset, group_expert, nullptr, g_begin, Gr, n_rows, E, 0, s, err_flag));
     RELIBRA_HIP_TRY(launch_check());
     const long long R = max_row_tiles(n_rows, Gr);
-    // column tiles: the wide ones where they divide the output
-    const bool wide1 = row_tiles_wide(hff, 256), wide2 = row_tiles_wide(h, 512);
-    const int ct1 = wide1 ? hff / 256 : (hff + 127) / 128, ct2 = wide2 ? h / 512 : (h + 255) / 256;
+    const bool wide1 = row_tiles_wide(hff, 256, n_rows, Gr), wide2 = row_tiles_wide(h, 512, n_rows, Gr);
+    const int ct1 = wide1 ? (hff + 255) / 256 : (hff + 127) / 128, ct2 = wide2 ? (h + 511) / 512 : (h + 255) / 256;
     RELIBRA_ROW_LAUNCH(RELIBRA_K_FWD_GATE_UP, fwd_gate_up_kernel, wt, wide1, 128, 256, R * ct1,
                        s, (const bf16_t *)Xrows, row_tok, T - 1, (const bf16_t *)Wg, (const bf16_t *)Wu, h, hff, ct1,
                        (bf16_t *)Gt_save, (bf16_t *)U_save, (bf16_t *)A_save, row_gate, (bf16_t *)Ag_save);
@@ -1287,9 +1301,10 @@ static int ffn_bwd_impl(const void *dYrows, const void *Xrows,
                                         n_dw_slots, s, err_flag));
     RELIBRA_HIP_TRY(launch_check());
     const long long R = max_row_tiles(n_rows, Gr);
-    const bool wide_h = row_tiles_wide(h, 512);
-    const bool wide_ff = row_tiles_wide(hff, 512);
-    const int ct_ff = wide_ff ? hff / 512 : (hff + 255) / 256, ct_h = wide_h ? h / 512 : (h + 255) / 256;
+    const bool wide_h = row_tiles_wide(h, 512, n_rows, Gr);
+    // (the activation backward on transposed weight copies keeps whole tiles: its partial gate sums belong to columns)
+    const bool wide_ff = row_tiles_wide(hff, 512, n_rows, Gr) && (hff % 512 == 0 || !(flags & RELIBRA_BWD_TRANSPOSED_WEIGHTS));
+    const int ct_ff = wide_ff ? (hff + 511) / 512 : (hff + 255) / 256, ct_h = wide_h ? (h + 511) / 512 : (h + 255) / 256;
     const int accumulate = (flags & RELIBRA_BWD_ACCUMULATE) ? 1 : 0;
     const int w_from_slot = (flags & RELIBRA_BWD_REPLICA_WEIGHTS) ? 1 : 0;
     if (n_rows > 0) {
