@@ -1150,9 +1150,16 @@ static inline unsigned grid8(long long tiles) { return (unsigned)((tiles + 7) / 
 // 1056 -> 980, 1820 -> 1694.  3136 columns (8 % more padding): down 521 -> 534.  8 groups of 512 x 1024, 200
 // rows each (few tiles): gate/up 17 -> 22, down 19 -> 26, dA 20 -> 28, dX 27 -> 42; 8 of 4096 x 14336, dX at 32
 // rows 416 -> 608, at 200 rows 536 -> 676, at 300 rows (384 narrow tiles) 918 -> 684.
+// Short contractions (k_dim, over both products where there are two) stay narrow too: two workgroups per unit
+// then hide each other's start and epilogue, which weigh more than the loads the wide tile saves.  16 groups of
+// 800 rows, 4096 columns, narrow -> wide: down over 64 28 -> 32 us, 128 38 -> 48, 256 59 -> 65, 512 82 -> 92; 64
+// groups of 300 rows, 1536 columns: dA over 128 63 -> 73, 512 92 -> 106; gate/up over 128 53 -> 60, over 512 117
+// and 121 (its two projections have twice the work per value).  dX over 2 x 512: 115 -> 105.
 constexpr int kComputeUnits = 256;
-static inline bool row_tiles_wide(int n_dim, int width, int n_rows, int groups)
+constexpr int kShortDot = 512;
+static inline bool row_tiles_wide(int n_dim, int width, int n_rows, int groups, int k_dim)
 {
+    if (k_dim <= kShortDot) return false;
     const long long wide = (n_dim + width - 1) / width, narrow = (n_dim + width / 2 - 1) / (width / 2);
     const long long row_tiles = std::max((long long)groups, (long long)n_rows / BM + groups / 2);
     return n_dim >= width && 2 * wide == narrow && row_tiles * narrow > kComputeUnits + kComputeUnits / 8;
@@ -1201,7 +1208,7 @@ static int ffn_fwd_impl(const void *Xrows, const int32_t *row_tok, int T, int n_
     RELIBRA_LAUNCH(RELIBRA_K_SCHED, stream, sched_kernel<<<1, 256, (size_t)(Gr + 1) * sizeof(int32_t), stream>>>(group_offset, group_expert, nullptr, g_begin, Gr, n_rows, E, 0, s, err_flag));
     RELIBRA_HIP_TRY(launch_check());
     const long long R = max_row_tiles(n_rows, Gr);
-    const bool wide1 = row_tiles_wide(hff, 256, n_rows, Gr), wide2 = row_tiles_wide(h, 512, n_rows, Gr);
+    const bool wide1 = row_tiles_wide(hff, 256, n_rows, Gr, 2 * h), wide2 = row_tiles_wide(h, 512, n_rows, Gr, hff);
     const int ct1 = wide1 ? (hff + 255) / 256 : (hff + 127) / 128, ct2 = wide2 ? (h + 511) / 512 : (h + 255) / 256;
     RELIBRA_ROW_LAUNCH(RELIBRA_K_FWD_GATE_UP, fwd_gate_up_kernel, wt, wide1, 128, 256, R * ct1,
                        s, (const bf16_t *)Xrows, row_tok, T - 1, (const bf16_t *)Wg, (const bf16_t *)Wu, h, hff, ct1,
@@ -1301,9 +1308,9 @@ static int ffn_bwd_impl(const void *dYrows, const void *Xrows,
                                         n_dw_slots, s, err_flag));
     RELIBRA_HIP_TRY(launch_check());
     const long long R = max_row_tiles(n_rows, Gr);
-    const bool wide_h = row_tiles_wide(h, 512, n_rows, Gr);
+    const bool wide_h = row_tiles_wide(h, 512, n_rows, Gr, 2 * hff);
     // (the activation backward on transposed weight copies keeps whole tiles: its partial gate sums belong to columns)
-    const bool wide_ff = row_tiles_wide(hff, 512, n_rows, Gr) && (hff % 512 == 0 || !(flags & RELIBRA_BWD_TRANSPOSED_WEIGHTS));
+    const bool wide_ff = row_tiles_wide(hff, 512, n_rows, Gr, h) && (hff % 512 == 0 || !(flags & RELIBRA_BWD_TRANSPOSED_WEIGHTS));
     const int ct_ff = wide_ff ? (hff + 511) / 512 : (hff + 255) / 256, ct_h = wide_h ? (h + 511) / 512 : (h + 255) / 256;
     const int accumulate = (flags & RELIBRA_BWD_ACCUMULATE) ? 1 : 0;
     const int w_from_slot = (flags & RELIBRA_BWD_REPLICA_WEIGHTS) ? 1 : 0;

@@ -792,8 +792,8 @@ def many_group_case(seed, h, hff):
     return len(first), case
 
 
-@pytest.mark.parametrize("h,hff", [(k, 512) for k in (64, 128, 192, 256, 320, 384, 448, 512, 832)]
-                         + [(1024, k) for k in (64, 128, 192, 320, 384)] + [(960, 1472), (1472, 704), (512, 960)])
+@pytest.mark.parametrize("h,hff", [(k, 512) for k in (64, 256, 320, 384, 448, 512, 576, 640, 704, 768, 832, 896)]
+                         + [(1024, k) for k in (256, 320, 384, 512, 576, 640, 704, 768, 832)] + [(960, 1472), (1472, 704), (512, 960)])
 def test_wide_tiles_on_weights_as_stored(h, hff):
     """The wide tiles take k-contiguous weights 64 k-values of one half of their columns at a time.  Contractions
     of every remainder of a trip through the LDS rings, row tiles of both heights, output widths that the tiles
