@@ -12,10 +12,14 @@
 #include "../../include/relibra.h"
 
 #include <algorithm>
+#include <atomic>
 #include <cstdint>
 #include <cstring>
+#include <exception>
 #include <iterator>
+#include <mutex>
 #include <numeric>
+#include <system_error>
 #include <thread>
 #include <vector>
 
@@ -86,8 +90,10 @@ Cost cost_of(const std::vector<i64> &L)
 // A swap of a (rank p) and b (rank q) moves d = l_b - l_a tokens from q to p: the sum of squares
 // changes by 2 d (L_p - L_q + d), so candidates are compared by (new peak, that change).  Over
 // all integer d the change is at least -floor((L_p - L_q)^2 / 4): a pair of ranks that cannot
-// lower the peak and whose bound cannot reach the best change found so far is skipped whole,
-// which leaves a handful of rank pairs to enumerate once the loads are nearly level.
+// lower the peak and whose bound cannot reach the best change found so far is skipped whole.  The pairs
+// with a rank at the peak come first; if one of their swaps lowers it, no other pair can do better, else the
+// others follow by descending gap, whose bounds rise, until one cannot reach the best change: a handful
+// once the loads are nearly level.  (The best swap does not depend on the order of the pairs.)
 // D = the integer type of the change: 64 bits when the loads are small enough, else 128.
 template <class D>
 Cost swap_descent_t(const std::vector<i64> &load_of, int EP, std::vector<int> &where)
@@ -103,26 +109,16 @@ Cost swap_descent_t(const std::vector<i64> &load_of, int EP, std::vector<int> &w
     for (;;) {
         const Cost cur = cost_of(L);
         top.build(L);
-        pairs.clear();
-        for (int p = 0; p < EP; ++p)
-            for (int q = p + 1; q < EP; ++q) pairs.push_back({p, q, L[p] > L[q] ? L[p] - L[q] : L[q] - L[p]});
-        std::stable_sort(pairs.begin(), pairs.end(), [](const RankPair &x, const RankPair &y) { return x.gap > y.gap; });
         bool have = false;
         i64 best_peak = 0;
         D best_delta = 0;
         int pa = -1, pb = -1;
-        for (const RankPair &rp : pairs) {
-            const bool touches_peak = L[rp.p] == cur.peak || L[rp.q] == cur.peak;
-            if (have && !touches_peak) {
-                if (best_peak < cur.peak) continue;                          // cannot lower the peak, the best one does
-                const D bound = -((D)(rp.gap / 2) * (D)(rp.gap - rp.gap / 2));
-                if (bound > best_delta) continue;                            // cannot reach the best change
-            }
-            const i64 rest = top.max_excluding(rp.p, rp.q);
-            for (int x : on[rp.p])
-                for (int y : on[rp.q]) {
+        auto visit = [&](int p, int q) {
+            const i64 rest = top.max_excluding(p, q);
+            for (int x : on[p])
+                for (int y : on[q]) {
                     const int a = x < y ? x : y, b = x < y ? y : x;
-                    const int ga = x < y ? rp.p : rp.q, gb = x < y ? rp.q : rp.p;
+                    const int ga = x < y ? p : q, gb = x < y ? q : p;
                     const i64 d = load_of[b] - load_of[a];                  // rank ga gains d, rank gb loses d
                     const i64 peak = std::max(std::max(L[ga] + d, L[gb] - d), rest);
                     if (have && peak > best_peak) continue;
@@ -131,6 +127,23 @@ Cost swap_descent_t(const std::vector<i64> &load_of, int EP, std::vector<int> &w
                                         (delta == best_delta && (a < pa || (a == pa && b < pb)));
                     if (better) { have = true; best_peak = peak; best_delta = delta; pa = a; pb = b; }
                 }
+        };
+        pairs.clear();
+        for (int p = 0; p < EP; ++p)
+            for (int q = p + 1; q < EP; ++q) {
+                if (L[p] == cur.peak || L[q] == cur.peak) visit(p, q);
+                else pairs.push_back({p, q, L[p] > L[q] ? L[p] - L[q] : L[q] - L[p]});
+            }
+        while (!pairs.empty() && (!have || best_peak >= cur.peak)) {
+            size_t at = 0;
+            for (size_t i = 1; i < pairs.size(); ++i)
+                if (pairs[i].gap > pairs[at].gap) at = i;
+            const RankPair rp = pairs[at];
+            pairs[at] = pairs.back();
+            pairs.pop_back();
+            const D bound = -((D)(rp.gap / 2) * (D)(rp.gap - rp.gap / 2));
+            if (have && bound > best_delta) break;                           // cannot reach the best change
+            visit(rp.p, rp.q);
         }
         if (!have || !(best_peak < cur.peak || (best_peak == cur.peak && best_delta < 0))) return cur;
         const int ga = where[pa], gb = where[pb];
@@ -153,14 +166,25 @@ Cost swap_descent(const std::vector<i64> &load_of, int EP, std::vector<int> &whe
 }
 
 // ---------------------------------------------------------------- stage 2
+// tokens of expert e served on local rank g, at [e][g]
+struct Shares {
+    int n = 0;
+    std::vector<i64> v;
+    void reset(int experts, int ranks) { n = ranks; v.assign((size_t)experts * ranks, 0); }
+    i64 *operator[](size_t e) { return v.data() + e * n; }
+    const i64 *operator[](size_t e) const { return v.data() + e * n; }
+};
+
 // One node: n ranks, experts listed in ascending global id.
 struct Node {
     int n = 0, r = 0;
     std::vector<i64> cnt;                  // tokens of each expert in this micro-batch
     std::vector<int> home;                 // local home rank
     std::vector<uint32_t> allowed;         // bit g set: expert may be served on local rank g
-    std::vector<std::vector<i64>> share;   // share[e][g]: tokens of e served on g
+    Shares share;
     std::vector<i64> L;                    // rank loads
+    std::vector<int> spread;               // balance(): experts with more than one rank
+    std::vector<char> tried;               // solve(): candidates without a feasible target
 
     void recompute_loads()
     {
@@ -177,38 +201,41 @@ struct Node {
     // lowest expert id per hop; sink = lightest reached rank, lower id first.
     void balance()
     {
+        // Only an expert that may be served on several ranks can carry tokens from one to another.
         const int ne = (int)cnt.size();
-        std::vector<int> by_load(n), parent(n), via(n), bfs;
-        bfs.reserve(n);
+        spread.clear();
+        for (int e = 0; e < ne; ++e)
+            if (allowed[e] & (allowed[e] - 1)) spread.push_back(e);
+        int by_load[32], parent[32], via[32], queue[32];
+        recompute_loads();
         for (;;) {
-            recompute_loads();
-            std::iota(by_load.begin(), by_load.end(), 0);
-            std::stable_sort(by_load.begin(), by_load.end(), [&](int a, int b) { return L[a] > L[b]; });
+            for (int g = 0; g < n; ++g) {                 // descending load, ties in ascending rank
+                int at = g;
+                for (; at > 0 && L[by_load[at - 1]] < L[g]; --at) by_load[at] = by_load[at - 1];
+                by_load[at] = g;
+            }
             bool moved = false;
-            for (int u : by_load) {
+            for (int i = 0; i < n && !moved; ++i) {
+                const int u = by_load[i];
                 uint32_t seen = 1u << u;
                 parent[u] = -1;
-                bfs.clear();
-                bfs.push_back(u);
-                for (size_t head = 0; head < bfs.size(); ++head) {
-                    const int w = bfs[head];
+                int queued = 0;
+                queue[queued++] = u;
+                for (int head = 0; head < queued; ++head) {
+                    const int w = queue[head];
                     uint32_t fresh = 0;
-                    for (int e = 0; e < ne; ++e) {        // ascending id: first hit = lowest expert
-                        if (share[e][w] <= 0) continue;
+                    for (int e : spread) {                // ascending id: first hit = lowest expert
                         uint32_t reach = allowed[e] & ~seen;
-                        while (reach) {
+                        if (!reach || share[e][w] <= 0) continue;
+                        seen |= reach;
+                        fresh |= reach;
+                        for (; reach; reach &= reach - 1) {
                             const int v = __builtin_ctz(reach);
-                            reach &= reach - 1;
-                            seen |= 1u << v;
-                            fresh |= 1u << v;
                             parent[v] = w;
                             via[v] = e;
                         }
                     }
-                    while (fresh) {                        // neighbours join the queue in ascending rank
-                        bfs.push_back(__builtin_ctz(fresh));
-                        fresh &= fresh - 1;
-                    }
+                    for (; fresh; fresh &= fresh - 1) queue[queued++] = __builtin_ctz(fresh);   // neighbours in ascending rank
                 }
                 int sink = -1;
                 for (int g = 0; g < n; ++g)
@@ -220,8 +247,9 @@ struct Node {
                     share[via[x]][parent[x]] -= d;
                     share[via[x]][x] += d;
                 }
+                L[u] -= d;                                // the ranks between pass on what they get
+                L[sink] += d;
                 moved = true;
-                break;
             }
             if (!moved) return;
         }
@@ -230,7 +258,7 @@ struct Node {
     i64 solve()
     {
         const int ne = (int)cnt.size();
-        share.assign(ne, std::vector<i64>(n, 0));
+        share.reset(ne, n);
         allowed.assign(ne, 0);
         L.assign(n, 0);
         i64 total = 0;
@@ -240,24 +268,25 @@ struct Node {
             total += cnt[e];
         }
         const i64 floor_load = (total + n - 1) / n;
-        std::vector<int> slots_used(n, 0);
-        std::vector<int> cand;
+        int slots_used[32] = {};
+        recompute_loads();
         for (;;) {
-            recompute_loads();
             const int gb = (int)(std::max_element(L.begin(), L.end()) - L.begin());   // first max
             if (L[gb] <= floor_load) break;
-            cand.clear();
-            for (int e = 0; e < ne; ++e)
-                if (share[e][gb] > 0) cand.push_back(e);
-            std::stable_sort(cand.begin(), cand.end(),
-                             [&](int a, int b) { return share[a][gb] > share[b][gb]; });
+            // experts served on gb, most tokens first (ties: lower id), until one has a feasible target
             int e_pick = -1, g_pick = -1;
-            for (int e : cand) {
+            tried.assign(ne, 0);
+            for (;;) {
+                int e = -1;
+                for (int i = 0; i < ne; ++i)
+                    if (!tried[i] && share[i][gb] > 0 && (e < 0 || share[i][gb] > share[e][gb])) e = i;
+                if (e < 0) break;
                 for (int g = 0; g < n; ++g) {
                     if ((allowed[e] >> g & 1) || slots_used[g] >= r) continue;
                     if (g_pick < 0 || L[g] < L[g_pick]) g_pick = g;
                 }
                 if (g_pick >= 0) { e_pick = e; break; }
+                tried[e] = 1;
             }
             if (e_pick < 0) break;
             allowed[e_pick] |= 1u << g_pick;
@@ -272,21 +301,41 @@ struct Node {
     }
 };
 
-// Result of stage 2 for one micro-batch under a given placement.
+// Result of stage 2 for one micro-batch under a given placement: per expert the ranks that serve it
+// (bits of ranks[e] count from rank base[e]) and, from rows[first[e]] on, the rows on each, ascending.
 struct MbPlan {
     i64 peak = 0;
-    std::vector<std::vector<std::pair<int, i64>>> inst;   // per expert: (rank, rows), ascending rank
+    std::vector<uint32_t> ranks;
+    std::vector<int> base, first;
+    std::vector<i64> rows;
+    void start(int E)
+    {
+        ranks.resize(E);
+        base.resize(E);
+        first.resize(E);
+        rows.reserve((size_t)E + E / 2);
+    }
+    void put(int e, int node_base, uint32_t allowed, const i64 *share)
+    {
+        ranks[e] = allowed;
+        base[e] = node_base;
+        first[e] = (int)rows.size();
+        for (; allowed; allowed &= allowed - 1) rows.push_back(share[__builtin_ctz(allowed)]);
+    }
 };
 
 MbPlan replicate_microbatch(const int32_t *cnt, const std::vector<int> &where, int E, int EP, int rpn, int r)
 {
     MbPlan out;
-    out.inst.resize(E);
+    out.start(E);
+    Node nd;
+    std::vector<int> members;
+    nd.n = rpn;
+    nd.r = r;
     for (int base = 0; base < EP; base += rpn) {
-        Node nd;
-        nd.n = rpn;
-        nd.r = r;
-        std::vector<int> members;
+        members.clear();
+        nd.cnt.clear();
+        nd.home.clear();
         for (int e = 0; e < E; ++e)
             if (where[e] >= base && where[e] < base + rpn) {
                 members.push_back(e);
@@ -294,32 +343,59 @@ MbPlan replicate_microbatch(const int32_t *cnt, const std::vector<int> &where, i
                 nd.home.push_back(where[e] - base);
             }
         out.peak = std::max(out.peak, nd.solve());
-        for (size_t i = 0; i < members.size(); ++i)
-            for (int g = 0; g < rpn; ++g)
-                if (nd.allowed[i] >> g & 1) out.inst[members[i]].push_back({base + g, nd.share[i][g]});
+        for (size_t i = 0; i < members.size(); ++i) out.put(members[i], base, nd.allowed[i], nd.share[i]);
     }
     return out;
 }
+
+// Threads for `tasks` independent pieces of work of about `us` microseconds each: a thread costs about
+// 20 us to start, so each should have several times that to do.
+int workers_for(int tasks, double us)
+{
+    const unsigned hw = std::thread::hardware_concurrency();
+    const int want = (int)(tasks * us / 100.0) + 1;
+    return std::max(1, std::min({want, (int)(hw ? hw : 1u), tasks, 16}));
+}
+
+// 32 micro-batches, 128 experts on 16 ranks, histogram and copies included: 1566 us with two pools of 16 threads
+// and a descent that sorted all pairs of ranks in every step, 550 us like this.
+// Runs fn on `workers` threads, the calling one among them.  An exception of a worker (std::bad_alloc) is
+// handed to the caller after all threads have ended.
+template <class Fn> void run_workers(int workers, const Fn &fn)
+{
+    std::exception_ptr failed;
+    std::mutex m;
+    auto guarded = [&]() {
+        try {
+            fn();
+        } catch (...) {
+            std::lock_guard<std::mutex> lock(m);
+            failed = std::current_exception();
+        }
+    };
+    std::vector<std::thread> pool;
+    pool.reserve(workers);
+    try {
+        for (int w = 1; w < workers; ++w) pool.emplace_back(guarded);
+    } catch (const std::system_error &) {      // no more threads to be had: the ones there are share the work
+    }
+    guarded();
+    for (auto &t : pool) t.join();
+    if (failed) std::rethrow_exception(failed);
+}
+
+// About what one micro-batch costs in stage 2.
+double replicate_us(int E, int EP, int r) { return 2.0 + 0.02 * E + 0.06 * EP * r * 8; }
 
 std::vector<MbPlan> replicate_batch(const int32_t *counts, int n_mb, const std::vector<int> &where,
                                     int E, int EP, int rpn, int r)
 {
     std::vector<MbPlan> plans(n_mb);
-    unsigned hw = std::thread::hardware_concurrency();
-    int workers = (int)std::min<unsigned>(hw ? hw : 1u, (unsigned)n_mb);
-    workers = std::min(workers, 16);
-    if (workers <= 1) {
-        for (int mb = 0; mb < n_mb; ++mb)
+    std::atomic<int> next{0};
+    run_workers(workers_for(n_mb, replicate_us(E, EP, r)), [&]() {
+        for (int mb; (mb = next.fetch_add(1)) < n_mb;)
             plans[mb] = replicate_microbatch(counts + (size_t)mb * E, where, E, EP, rpn, r);
-        return plans;
-    }
-    std::vector<std::thread> pool;
-    for (int w = 0; w < workers; ++w)
-        pool.emplace_back([&, w]() {
-            for (int mb = w; mb < n_mb; mb += workers)
-                plans[mb] = replicate_microbatch(counts + (size_t)mb * E, where, E, EP, rpn, r);
-        });
-    for (auto &t : pool) t.join();
+    });
     return plans;
 }
 
@@ -396,7 +472,7 @@ MbPlan replicate_microbatch_timed(const int64_t *x, const relibra_cost_model *mo
         nd.n = rpn;
         nd.r = r;
         const int ne = (int)nd.cnt.size();
-        nd.share.assign(ne, std::vector<i64>(rpn, 0));
+        nd.share.reset(ne, rpn);
         nd.allowed.assign(ne, 0);
         nd.L.assign(rpn, 0);
         for (int i = 0; i < ne; ++i) {
@@ -429,7 +505,7 @@ MbPlan replicate_microbatch_timed(const int64_t *x, const relibra_cost_model *mo
                 if (gt < 0 || per[base + g] < per[base + gt]) gt = g;
             }
             if (gt < 0) continue;
-            const std::vector<std::vector<i64>> share_before = nd.share;
+            const Shares share_before = nd.share;
             nd.allowed[i] |= 1u << gt;
             nd.balance();
             const double T_try = st.time(per_try), S_try = squares(per_try);
@@ -447,14 +523,14 @@ MbPlan replicate_microbatch_timed(const int64_t *x, const relibra_cost_model *mo
         if (!kept) break;
     }
     MbPlan out;
-    out.inst.resize(E);
+    out.start(E);
     for (size_t n = 0; n < nodes.size(); ++n) {
         Node &nd = nodes[n];
-        for (size_t i = 0; i < members[n].size(); ++i)
-            for (int g = 0; g < rpn; ++g) {
+        for (size_t i = 0; i < members[n].size(); ++i) {
+            for (int g = 0; g < rpn; ++g)
                 if (g != nd.home[i] && (nd.allowed[i] >> g & 1) && nd.share[i][g] == 0) nd.allowed[i] &= ~(1u << g);
-                if (nd.allowed[i] >> g & 1) out.inst[members[n][i]].push_back({(int)n * rpn + g, nd.share[i][g]});
-            }
+            out.put(members[n][i], (int)n * rpn, nd.allowed[i], nd.share[i]);
+        }
         nd.recompute_loads();
         out.peak = std::max(out.peak, *std::max_element(nd.L.begin(), nd.L.end()));
     }
@@ -508,18 +584,40 @@ static int plan_impl(const int32_t *counts, int n_mb, int E, int k, int EP, int 
         }
         chosen_plans = replicate_batch(counts, n_mb, chosen, E, EP, rpn, r);
     } else {
-        // stage 1: descent from the unplanned layout and from LPT; ties keep the unplanned one
+        // Stage 1: descent from the unplanned layout and from LPT; ties keep the unplanned one.  Stage 2 under
+        // both placements; the reordering must pay for itself over the batch.  The two descents and the
+        // micro-batches under the unplanned placement are independent: the workers take them first, and then
+        // the micro-batches under the reordered placement.
         std::vector<int> from_id = unplanned, from_lpt = lpt_start(batch_load, EP);
-        Cost c_id{0, 0};
-        std::thread other([&]() { c_id = swap_descent(batch_load, EP, from_id); });     // the two starts are independent
-        const Cost c_lpt = swap_descent(batch_load, EP, from_lpt);
-        other.join();
-        const std::vector<int> &reordered = (c_lpt < c_id) ? from_lpt : from_id;
-        // stage 2 under both placements; the reordering must pay for itself over the batch
+        Cost c_id{0, 0}, c_lpt{0, 0};
+        std::vector<MbPlan> with_new(n_mb);
         chosen = unplanned;
-        chosen_plans = replicate_batch(counts, n_mb, unplanned, E, EP, rpn, r);
+        chosen_plans.resize(n_mb);
+        std::atomic<int> first{0}, second{0}, descents{0};
+        const double us = replicate_us(E, EP, r);
+        run_workers(workers_for(2 * n_mb + 2, us), [&]() {
+            struct Done {                                  // also when a descent throws: nobody waits for ever
+                std::atomic<int> *n = nullptr;
+                ~Done() { if (n) n->fetch_add(1, std::memory_order_release); }
+            };
+            for (int i; (i = first.fetch_add(1)) < n_mb + 2;) {
+                if (i < 2) {
+                    Done done;
+                    done.n = &descents;
+                    if (i == 0) c_id = swap_descent(batch_load, EP, from_id);
+                    else c_lpt = swap_descent(batch_load, EP, from_lpt);
+                } else {
+                    chosen_plans[i - 2] = replicate_microbatch(counts + (size_t)(i - 2) * E, unplanned, E, EP, rpn, r);
+                }
+            }
+            while (descents.load(std::memory_order_acquire) < 2) std::this_thread::yield();
+            const std::vector<int> &to = (c_lpt < c_id) ? from_lpt : from_id;
+            if (to == unplanned) return;
+            for (int mb; (mb = second.fetch_add(1)) < n_mb;)
+                with_new[mb] = replicate_microbatch(counts + (size_t)mb * E, to, E, EP, rpn, r);
+        });
+        const std::vector<int> &reordered = (c_lpt < c_id) ? from_lpt : from_id;
         if (reordered != unplanned) {
-            std::vector<MbPlan> with_new = replicate_batch(counts, n_mb, reordered, E, EP, rpn, r);
             i64 j_id = 0, j_new = 0;
             for (int mb = 0; mb < n_mb; ++mb) { j_id += chosen_plans[mb].peak; j_new += with_new[mb].peak; }
             if (j_new < j_id) {
@@ -566,8 +664,9 @@ static void write_tables(const int32_t *counts, int n_mb, int E, int EP, int r, 
         int p = 0;
         for (int e = 0; e < E; ++e) {                      // ascending e fills replica slots in id order
             iptr[e] = p;
-            for (const auto &ir : P.inst[e]) {
-                const int rk = ir.first;
+            const i64 *served = P.rows.data() + P.first[e];
+            for (uint32_t left = P.ranks[e]; left; left &= left - 1, ++served) {
+                const int rk = P.base[e] + __builtin_ctz(left);
                 int grp;
                 if (rk == where[e]) {
                     grp = rk * S + expert_to_slot[e] % M;
@@ -578,9 +677,9 @@ static void write_tables(const int32_t *counts, int n_mb, int E, int EP, int r, 
                     rep[rk * r + j] = e;
                 }
                 gexp[grp] = e;
-                rows[grp] = ir.second;
+                rows[grp] = *served;
                 irank[p] = rk;
-                irows[p] = (int32_t)ir.second;
+                irows[p] = (int32_t)*served;
                 igrp[p] = grp;
                 ++p;
             }
