@@ -703,9 +703,11 @@ transpose_experts_kernel(const bf16_t *__restrict__ in, int rows, int cols, bf16
 // Weight-gradient epilogue.  The accumulators hold, per lane, one column n and 16 rows m of each
 // MFMA tile; each 32 x 64 fp32 block of the wave goes through this wave's 8 KiB of LDS and
 // leaves as 16 bytes per lane along n: 1 KiB per store (or load-add-store) instruction.
+// stream: gradients larger than the last-level cache leave with a streaming hint, so that they do not push
+// out operands that other tiles still read (128 experts of 2048 x 768: 1 to 3 % of the kernel).
 template <class KL, int NA, int BA, int NWV = NWAVES>
 __device__ __forceinline__ void wgrad_epilogue(typename KL::Acc &acc, char *lds, float *out0, float *out1, size_t base,
-                                               int m0, int n0, int m_dim, int n_dim, bool add, int wave, int lane)
+                                               int m0, int n0, int m_dim, int n_dim, bool add, bool stream, int wave, int lane)
 {
     static_assert(KL::TB % 2 == 0, "a wave owns a multiple of 64 columns");
     __syncthreads();                                          // every wave is done with the operand slabs
@@ -742,11 +744,21 @@ __device__ __forceinline__ void wgrad_epilogue(typename KL::Acc &acc, char *lds,
                     val[p].x += old[p].x; val[p].y += old[p].y; val[p].z += old[p].z; val[p].w += old[p].w;
                 }
             }
+            typedef float f32x4_t __attribute__((ext_vector_type(4)));
+            auto store = [&](auto streaming) __attribute__((always_inline)) {
 #pragma unroll
-            for (int p = 0; p < 8; ++p) {
-                const int r = wm0 + ta * 32 + p * 4 + (lane >> 4);
-                if (r < m_dim && gcol < n_dim) *reinterpret_cast<float4 *>(out + (size_t)r * n_dim + gcol) = val[p];
-            }
+                for (int p = 0; p < 8; ++p) {
+                    const int r = wm0 + ta * 32 + p * 4 + (lane >> 4);
+                    const f32x4_t v = {val[p].x, val[p].y, val[p].z, val[p].w};
+                    f32x4_t *to = reinterpret_cast<f32x4_t *>(out + (size_t)r * n_dim + gcol);
+                    if (r < m_dim && gcol < n_dim) {
+                        if (decltype(streaming)::value) __builtin_nontemporal_store(v, to);
+                        else *to = v;
+                    }
+                }
+            };
+            if (stream) store(std::true_type{});
+            else store(std::false_type{});
             wave_lds_fence();
         }
 }
@@ -756,21 +768,24 @@ __device__ __forceinline__ void wgrad_epilogue(typename KL::Acc &acc, char *lds,
 // Tile: (NA x BA) x WGN with BA = WGM / NA.  Two geometries: WGM = 256 (three slabs, two
 // workgroups per compute unit) for long groups, where the MFMA rate matters, and WGM = 128 (two
 // slabs, four workgroups per compute unit) for short groups, where the kernel is a stream of
-// fp32 read-add-writes and more waves in flight mean more HBM bandwidth.
-template <int WGM> struct WgradCfg {
-    static constexpr int STAGES = WGM == 256 ? NSTAGES : 2;
-    static constexpr int OCC = WGM == 256 ? 2 : 4;                  // waves per SIMD aimed at
+// fp32 read-add-writes and more waves in flight mean more HBM bandwidth.  DEEP, for calls of few
+// tiles: a unit has one or two workgroups at most, so nothing but a workgroup's own ring hides the
+// latency of its slabs.  24 groups of 130 rows, 256 x 192: both calls 27.6 -> 24.8 us (of which 9 are launches).
+template <int WGM, bool DEEP> struct WgradCfg {
+    static constexpr int STAGES = DEEP ? 4 : WGM == 256 ? NSTAGES : 2;
+    static constexpr int OCC = DEEP || WGM == 256 ? 2 : 4;          // waves per SIMD aimed at
     static constexpr int SLABS = STAGES * (WGM + WGN) * BK * 2;
     static constexpr int LDS = SLABS > NWAVES * 8192 ? SLABS : NWAVES * 8192;
 };
-template <int NA, int WGM>
-__global__ void __launch_bounds__(THREADS, WgradCfg<WGM>::OCC)
+template <int NA, int WGM, bool DEEP = false>
+__global__ void __launch_bounds__(THREADS, (WgradCfg<WGM, DEEP>::OCC))
 wgrad_kernel(Sched s, const bf16_t *__restrict__ L0, const bf16_t *__restrict__ L1,
-             const bf16_t *__restrict__ R, int m_dim, int n_dim, int E, int accumulate, int total,
+             const bf16_t *__restrict__ R, int m_dim, int n_dim, int E, int accumulate, int stream, int total,
              float *__restrict__ out0, float *__restrict__ out1)
 {
     constexpr int BA = WGM / NA;
-    using KL = KLoop<KsTile<BA>, KsTile<WGN>, NA, 1, BA, WGN, 2, NWAVES / 2, 1, true, WgradCfg<WGM>::STAGES, (kSpreadLoads && WgradCfg<WGM>::STAGES >= 3)>;
+    using KL = KLoop<KsTile<BA>, KsTile<WGN>, NA, 1, BA, WGN, 2, NWAVES / 2, 1, true, WgradCfg<WGM, DEEP>::STAGES,
+                     (kSpreadLoads && WgradCfg<WGM, DEEP>::STAGES >= 3)>;
     extern __shared__ __attribute__((aligned(1024))) char lds[];
     const int n_nt = (n_dim + WGN - 1) / WGN, n_mt = (m_dim + BA - 1) / BA;
     const int per_group = n_nt * n_mt;
@@ -795,7 +810,7 @@ wgrad_kernel(Sched s, const bf16_t *__restrict__ L0, const bf16_t *__restrict__ 
     typename KL::Acc acc;
     KL::zero(acc);
     KL::run(acc, A, B, (rows + BK - 1) / BK, rows, lds, tid);
-    wgrad_epilogue<KL, NA, BA>(acc, lds, out0, out1, (size_t)slot * m_dim * n_dim, m0, n0, m_dim, n_dim, add, wave, lane);
+    wgrad_epilogue<KL, NA, BA>(acc, lds, out0, out1, (size_t)slot * m_dim * n_dim, m0, n0, m_dim, n_dim, add, stream != 0, wave, lane);
 }
 
 // ---------------------------------------------------------------- batched weight gradients
@@ -1005,14 +1020,14 @@ struct WgradPieces {
 // waves per SIMD.  (Four waves of 128 x 128 on that tile, one per SIMD, were 5-10 % slower.)
 constexpr int kWideWaves = 8;
 template <int WN> struct WgradWide {
-    static constexpr int STAGES = WN == 256 ? 4 : WgradCfg<256>::STAGES;
-    static constexpr int OCC = WN == 256 ? 1 : WgradCfg<256>::OCC;
+    static constexpr int STAGES = WN == 256 ? 4 : NSTAGES;
+    static constexpr int OCC = WN == 256 ? 1 : 2;
     static constexpr int SLABS = STAGES * (256 + WN) * BK * 2;
     static constexpr int LDS = SLABS > 8 * 8192 ? SLABS : 8 * 8192;
 };
 template <int NA, int WN, int NWV = NWAVES>
 __global__ void __launch_bounds__(NWV * 64, WgradWide<WN>::OCC)
-wgrad_batched_kernel(int E, int m_dim, int n_dim, WgradPlan w, int accumulate,
+wgrad_batched_kernel(int E, int m_dim, int n_dim, WgradPlan w, int accumulate, int stream,
                      float *__restrict__ out0, float *__restrict__ out1)
 {
     constexpr int WGM = 256, BA = WGM / NA;
@@ -1044,7 +1059,7 @@ wgrad_batched_kernel(int E, int m_dim, int n_dim, WgradPlan w, int accumulate,
                               (const_i32_ptr)(uintptr_t)((NA == 1 ? w.rec_down + (size_t)s0 * kRecDownInts : w.rec_gu + (size_t)s0 * kRecGuInts)),
                               m_dim, n_dim, m0, n0};
     KL::run_pieces(acc, src, w.piece_ptr[e + 1] - s0, w.exp_slabs[e], lds, tid);
-    wgrad_epilogue<KL, NA, BA, NWV>(acc, lds, out0, out1, (size_t)e * m_dim * n_dim, m0, n0, m_dim, n_dim, add, wave, lane);
+    wgrad_epilogue<KL, NA, BA, NWV>(acc, lds, out0, out1, (size_t)e * m_dim * n_dim, m0, n0, m_dim, n_dim, add, stream != 0, wave, lane);
 }
 
 // Replica gradients return to the home copy (Section 5.1).  A thread owns element positions
@@ -1122,14 +1137,16 @@ static int set_lds_limits()
     RELIBRA_HIP_TRY(hipFuncSetAttribute((const void *)fwd_down_kernel<true, 512>, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytesWide));
     RELIBRA_HIP_TRY(hipFuncSetAttribute((const void *)bwd_dx_kernel<false, 512>, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytesWide));
     RELIBRA_HIP_TRY(hipFuncSetAttribute((const void *)bwd_dx_kernel<true, 512>, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytesWide));
-    RELIBRA_HIP_TRY(hipFuncSetAttribute((const void *)wgrad_kernel<1, 256>, hipFuncAttributeMaxDynamicSharedMemorySize, WgradCfg<256>::LDS));
-    RELIBRA_HIP_TRY(hipFuncSetAttribute((const void *)wgrad_kernel<2, 256>, hipFuncAttributeMaxDynamicSharedMemorySize, WgradCfg<256>::LDS));
+    RELIBRA_HIP_TRY(hipFuncSetAttribute((const void *)wgrad_kernel<1, 256>, hipFuncAttributeMaxDynamicSharedMemorySize, (WgradCfg<256, false>::LDS)));
+    RELIBRA_HIP_TRY(hipFuncSetAttribute((const void *)wgrad_kernel<2, 256>, hipFuncAttributeMaxDynamicSharedMemorySize, (WgradCfg<256, false>::LDS)));
     RELIBRA_HIP_TRY(hipFuncSetAttribute((const void *)wgrad_batched_kernel<1, 128>, hipFuncAttributeMaxDynamicSharedMemorySize, WgradWide<128>::LDS));
     RELIBRA_HIP_TRY(hipFuncSetAttribute((const void *)wgrad_batched_kernel<2, 128>, hipFuncAttributeMaxDynamicSharedMemorySize, WgradWide<128>::LDS));
     RELIBRA_HIP_TRY(hipFuncSetAttribute((const void *)wgrad_batched_kernel<1, 256, kWideWaves>, hipFuncAttributeMaxDynamicSharedMemorySize, WgradWide<256>::LDS));
     RELIBRA_HIP_TRY(hipFuncSetAttribute((const void *)wgrad_batched_kernel<2, 256, kWideWaves>, hipFuncAttributeMaxDynamicSharedMemorySize, WgradWide<256>::LDS));
-    RELIBRA_HIP_TRY(hipFuncSetAttribute((const void *)wgrad_kernel<1, 128>, hipFuncAttributeMaxDynamicSharedMemorySize, WgradCfg<128>::LDS));
-    RELIBRA_HIP_TRY(hipFuncSetAttribute((const void *)wgrad_kernel<2, 128>, hipFuncAttributeMaxDynamicSharedMemorySize, WgradCfg<128>::LDS));
+    RELIBRA_HIP_TRY(hipFuncSetAttribute((const void *)wgrad_kernel<1, 128>, hipFuncAttributeMaxDynamicSharedMemorySize, (WgradCfg<128, false>::LDS)));
+    RELIBRA_HIP_TRY(hipFuncSetAttribute((const void *)wgrad_kernel<1, 128, true>, hipFuncAttributeMaxDynamicSharedMemorySize, (WgradCfg<128, true>::LDS)));
+    RELIBRA_HIP_TRY(hipFuncSetAttribute((const void *)wgrad_kernel<2, 128>, hipFuncAttributeMaxDynamicSharedMemorySize, (WgradCfg<128, false>::LDS)));
+    RELIBRA_HIP_TRY(hipFuncSetAttribute((const void *)wgrad_kernel<2, 128, true>, hipFuncAttributeMaxDynamicSharedMemorySize, (WgradCfg<128, true>::LDS)));
     return RELIBRA_OK;
 }
 static int ensure_lds_limits()
@@ -1255,6 +1272,9 @@ extern "C" int relibra_moe_ffn_fwd_gated(const void *X, int T, const int32_t *ro
                         Gt_save, U_save, A_save, Yrows, flags, ws, ws_bytes, err_flag, stream_, row_gate, Ag_save);
 }
 
+// Whether the gradient tensors (fp32, `values` in each) are larger than the 256 MB last-level cache together.
+static inline int streams_dw(size_t values) { return 3 * values * sizeof(float) > ((size_t)256 << 20) ? 1 : 0; }
+
 // Gate-fused form of the backward call: the upstream gradient comes from the token tensor.
 struct GatedBwd {
     const void *dOut;
@@ -1354,21 +1374,20 @@ static int ffn_bwd_impl(const void *dYrows, const void *Xrows,
     const int wgm = small_tiles ? 128 : 256;
     const long long t_down = (long long)Gr * ((h + wgm - 1) / wgm) * ((hff + WGN - 1) / WGN);              // dWd: m in h, n in h'
     const long long t_gu = (long long)Gr * ((hff + wgm / 2 - 1) / (wgm / 2)) * ((h + WGN - 1) / WGN);      // dWg, dWu: m in h', n in h
-    if (small_tiles) {
-        RELIBRA_LAUNCH(RELIBRA_K_WGRAD_DOWN, stream, wgrad_kernel<1, 128><<<grid8(t_down), THREADS, WgradCfg<128>::LDS, stream>>>(
-            s, (const bf16_t *)dYrows, nullptr, (const bf16_t *)A_save, h, hff, E, accumulate, (int)t_down, dWd, nullptr));
-        RELIBRA_HIP_TRY(launch_check());
-        RELIBRA_LAUNCH(RELIBRA_K_WGRAD_GATE_UP, stream, wgrad_kernel<2, 128><<<grid8(t_gu), THREADS, WgradCfg<128>::LDS, stream>>>(
-            s, s.dGt, s.dU, (const bf16_t *)Xrows, hff, h, E, accumulate, (int)t_gu, dWg, dWu));
-        RELIBRA_HIP_TRY(launch_check());
-    } else {
-        RELIBRA_LAUNCH(RELIBRA_K_WGRAD_DOWN, stream, wgrad_kernel<1, 256><<<grid8(t_down), THREADS, WgradCfg<256>::LDS, stream>>>(
-            s, (const bf16_t *)dYrows, nullptr, (const bf16_t *)A_save, h, hff, E, accumulate, (int)t_down, dWd, nullptr));
-        RELIBRA_HIP_TRY(launch_check());
-        RELIBRA_LAUNCH(RELIBRA_K_WGRAD_GATE_UP, stream, wgrad_kernel<2, 256><<<grid8(t_gu), THREADS, WgradCfg<256>::LDS, stream>>>(
-            s, s.dGt, s.dU, (const bf16_t *)Xrows, hff, h, E, accumulate, (int)t_gu, dWg, dWu));
-        RELIBRA_HIP_TRY(launch_check());
-    }
+    const int stream_dw = streams_dw((size_t)n_dw_slots * h * hff);
+#define RELIBRA_WGRAD(WGM_, DEEP_)                                                                                                         \
+    do {                                                                                                                                   \
+        RELIBRA_LAUNCH(RELIBRA_K_WGRAD_DOWN, stream, (wgrad_kernel<1, WGM_, DEEP_><<<grid8(t_down), THREADS, WgradCfg<WGM_, DEEP_>::LDS, stream>>>( \
+            s, (const bf16_t *)dYrows, nullptr, (const bf16_t *)A_save, h, hff, E, accumulate, stream_dw, (int)t_down, dWd, nullptr)));    \
+        RELIBRA_HIP_TRY(launch_check());                                                                                                   \
+        RELIBRA_LAUNCH(RELIBRA_K_WGRAD_GATE_UP, stream, (wgrad_kernel<2, WGM_, DEEP_><<<grid8(t_gu), THREADS, WgradCfg<WGM_, DEEP_>::LDS, stream>>>( \
+            s, s.dGt, s.dU, (const bf16_t *)Xrows, hff, h, E, accumulate, stream_dw, (int)t_gu, dWg, dWu)));                               \
+        RELIBRA_HIP_TRY(launch_check());                                                                                                   \
+    } while (0)
+    if (!small_tiles) RELIBRA_WGRAD(256, false);
+    else if (std::max(t_down, t_gu) <= 2 * kComputeUnits) RELIBRA_WGRAD(128, true);
+    else RELIBRA_WGRAD(128, false);
+#undef RELIBRA_WGRAD
     if (!(flags & RELIBRA_BWD_NO_REPLICA_SUM) && n_dw_slots > E) {
         const size_t vec4 = (size_t)h * hff / 4;
         const int grid = (int)((vec4 + 255) / 256 < 4096 ? (vec4 + 255) / 256 : 4096);
@@ -1476,20 +1495,21 @@ extern "C" int relibra_moe_ffn_wgrad_batched(const relibra_wgrad_mb *mbs, int n_
     const int wn_down = wide_down ? 256 : 128, wn_gu = wide_gu ? 256 : 128;
     const unsigned g_down = grid_of((long long)((h + 255) / 256) * ((hff + wn_down - 1) / wn_down));  // dWd: m in h, n in h'
     const unsigned g_gu = grid_of((long long)((hff + 127) / 128) * ((h + wn_gu - 1) / wn_gu));        // dWg, dWu: m in h', n in h
+    const int stream_dw = streams_dw((size_t)E * h * hff);
     if (wide_down) {
         RELIBRA_LAUNCH(RELIBRA_K_WGRAD_DOWN, stream, (wgrad_batched_kernel<1, 256, kWideWaves><<<g_down, kWideWaves * 64, WgradWide<256>::LDS, stream>>>(
-            E, h, hff, w, accumulate, dWd, nullptr)));
+            E, h, hff, w, accumulate, stream_dw, dWd, nullptr)));
     } else {
         RELIBRA_LAUNCH(RELIBRA_K_WGRAD_DOWN, stream, wgrad_batched_kernel<1, 128><<<g_down, THREADS, WgradWide<128>::LDS, stream>>>(
-            E, h, hff, w, accumulate, dWd, nullptr));
+            E, h, hff, w, accumulate, stream_dw, dWd, nullptr));
     }
     RELIBRA_HIP_TRY(launch_check());
     if (wide_gu) {
         RELIBRA_LAUNCH(RELIBRA_K_WGRAD_GATE_UP, stream, (wgrad_batched_kernel<2, 256, kWideWaves><<<g_gu, kWideWaves * 64, WgradWide<256>::LDS, stream>>>(
-            E, hff, h, w, accumulate, dWg, dWu)));
+            E, hff, h, w, accumulate, stream_dw, dWg, dWu)));
     } else {
         RELIBRA_LAUNCH(RELIBRA_K_WGRAD_GATE_UP, stream, wgrad_batched_kernel<2, 128><<<g_gu, THREADS, WgradWide<128>::LDS, stream>>>(
-            E, hff, h, w, accumulate, dWg, dWu));
+            E, hff, h, w, accumulate, stream_dw, dWg, dWu));
     }
     RELIBRA_HIP_TRY(launch_check());
     return RELIBRA_OK;

@@ -820,6 +820,24 @@ def test_wide_tiles_on_weights_as_stored(h, hff):
         assert rel_l2(got[:n], want) <= TOL
 
 
+@pytest.mark.parametrize("groups", [20, 166], ids=["few-tiles", "many-tiles"])
+def test_weight_gradients_of_short_groups(groups):
+    """Both rings of the small weight-gradient tile: calls of few tiles, and of more than two per compute unit."""
+    _, (go, ge, X, dY, Wg, Wu, Wd) = many_group_case(groups, 256, 320)
+    go, ge = go[:groups + 1], ge[:groups]
+    N = int(go[-1])
+    X, dY = X[:N], dY[:N]
+    slots, n_slots = dw_slots(ge, 3)
+    go_d, ge_d, W_d, err = dev_i32(go), dev_i32(ge), [W.to(DEV) for W in (Wg, Wu, Wd)], rl.new_err_flag()
+    Gt, U, A, _ = rl.relibra_moe_ffn_fwd(X.to(DEV), go_d, ge_d, *W_d, err_flag=err)
+    dW = [torch.full((n_slots, *W.shape[1:]), 3.0, dtype=torch.float32, device=DEV) for W in (Wg, Wu, Wd)]
+    rl.relibra_moe_ffn_bwd(dY.to(DEV), X.to(DEV), Gt, U, A, go_d, ge_d, dev_i32(slots), *W_d, *dW, err_flag=err, E=3)
+    assert err.item() == 0
+    for got, want in zip(dW, oracle.ffn_bwd(X, dY, go, ge, Wg, Wu, Wd)[1:]):
+        for e in range(3):
+            assert rel_l2(got[e], want[e]) <= TOL
+
+
 @pytest.mark.parametrize("h,hff", [(512, 1024), (960, 1472), (512, 960)])
 def test_gate_fused_backward_on_wide_tiles(h, hff):
     """Gates that are powers of two scale without rounding: the gate-fused data gradients then equal, bit for bit,
