@@ -73,8 +73,16 @@ def _check(fn, rc):
         raise RelibraError(fn, rc)
 
 
+# The current stream of the current device as a plain handle.  Small calls are bound by what the host spends
+# on them, and building torch's stream object for every call was a fifth of it.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream():
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    if _raw_stream is None or _device is None or not torch.cuda.is_initialized():
+        return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    return C.c_void_p(_raw_stream(_device()))
 
 
 def _dp(t, dtype=None):
@@ -276,8 +284,8 @@ def relibra_permute(ids, inst_ptr, inst_rows, inst_group, group_offset, X, E, G,
         src_of = torch.empty(N, dtype=torch.int32, device=dev)
     if Xrows is None and X is not None:
         Xrows = torch.empty((N, h), dtype=torch.bfloat16, device=dev)
-    need = workspace_bytes(WS_PERMUTE, T, k, E, G, h, 0)
     if workspace is None:
+        need = workspace_bytes(WS_PERMUTE, T, k, E, G, h, 0)
         workspace = torch.empty(max(need, 1), dtype=torch.uint8, device=dev)
     if err_flag is None:
         err_flag = new_err_flag(dev)
@@ -581,6 +589,7 @@ def relibra_moe_ffn_wgrad_batched(mbs, E, dWg, dWu, dWd, accumulate=False, works
     inst_cap = first["inst_group"].shape[0]
     dev = dWg.device
     arr = (WgradMb * n_mb)()
+    bwd_bytes = workspace_bytes(WS_FFN_BWD, max(n_rows, 1), 1, E, G, h, hff)
     for i, m in enumerate(mbs):
         assert m["A"].shape == (n_rows, hff)
         if m.get("dYrows") is not None:
@@ -590,7 +599,7 @@ def relibra_moe_ffn_wgrad_batched(mbs, E, dWg, dWu, dWd, accumulate=False, works
             assert m.get("Xrows") is None and m["dOut"].shape == m["X"].shape
             dy, dout = C.c_void_p(0), _dp(m["dOut"], torch.bfloat16)
         assert m["group_offset"].shape[0] == G + 1 and m["inst_group"].shape[0] == inst_cap and m["inst_ptr"].shape[0] == E + 1
-        assert m["bwd_workspace"].numel() >= workspace_bytes(WS_FFN_BWD, max(n_rows, 1), 1, E, G, h, hff)
+        assert m["bwd_workspace"].numel() >= bwd_bytes
         if m.get("Xrows") is not None:          # group-ordered rows
             assert m["Xrows"].shape == (n_rows, h)
             x_rows, x_tok, rtok, n_tok = _dp(m["Xrows"], torch.bfloat16), C.c_void_p(0), C.c_void_p(0), 0
