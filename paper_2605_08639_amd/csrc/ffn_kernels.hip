@@ -777,20 +777,18 @@ template <int WGM, bool DEEP> struct WgradCfg {
     static constexpr int SLABS = STAGES * (WGM + WGN) * BK * 2;
     static constexpr int LDS = SLABS > NWAVES * 8192 ? SLABS : NWAVES * 8192;
 };
-template <int NA, int WGM, bool DEEP = false>
-__global__ void __launch_bounds__(THREADS, (WgradCfg<WGM, DEEP>::OCC))
-wgrad_kernel(Sched s, const bf16_t *__restrict__ L0, const bf16_t *__restrict__ L1,
-             const bf16_t *__restrict__ R, int m_dim, int n_dim, int E, int accumulate, int stream, int total,
-             float *__restrict__ out0, float *__restrict__ out1)
+template <int NA, int WGM, bool DEEP>
+__device__ __forceinline__ void wgrad_tile(const Sched &s, const bf16_t *__restrict__ L0, const bf16_t *__restrict__ L1,
+                                           const bf16_t *__restrict__ R, int m_dim, int n_dim, int E, int accumulate, int stream,
+                                           int total, float *__restrict__ out0, float *__restrict__ out1, int block, char *lds)
 {
     constexpr int BA = WGM / NA;
     using KL = KLoop<KsTile<BA>, KsTile<WGN>, NA, 1, BA, WGN, 2, NWAVES / 2, 1, true, WgradCfg<WGM, DEEP>::STAGES,
                      (kSpreadLoads && WgradCfg<WGM, DEEP>::STAGES >= 3)>;
-    extern __shared__ __attribute__((aligned(1024))) char lds[];
     const int n_nt = (n_dim + WGN - 1) / WGN, n_mt = (m_dim + BA - 1) / BA;
     const int per_group = n_nt * n_mt;
     const int per_xcd = (total + 7) >> 3;
-    const int logical = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+    const int logical = (block & 7) * per_xcd + (block >> 3);
     if (logical >= total) return;
     const int gi = logical / per_group, rem = logical % per_group;
     const int e = s.grp_expert[gi];
@@ -811,6 +809,28 @@ wgrad_kernel(Sched s, const bf16_t *__restrict__ L0, const bf16_t *__restrict__ 
     KL::zero(acc);
     KL::run(acc, A, B, (rows + BK - 1) / BK, rows, lds, tid);
     wgrad_epilogue<KL, NA, BA>(acc, lds, out0, out1, (size_t)slot * m_dim * n_dim, m0, n0, m_dim, n_dim, add, stream != 0, wave, lane);
+}
+template <int NA, int WGM>
+__global__ void __launch_bounds__(THREADS, (WgradCfg<WGM, false>::OCC))
+wgrad_kernel(Sched s, const bf16_t *__restrict__ L0, const bf16_t *__restrict__ L1,
+             const bf16_t *__restrict__ R, int m_dim, int n_dim, int E, int accumulate, int stream, int total,
+             float *__restrict__ out0, float *__restrict__ out1)
+{
+    extern __shared__ __attribute__((aligned(1024))) char lds[];
+    wgrad_tile<NA, WGM, false>(s, L0, L1, R, m_dim, n_dim, E, accumulate, stream, total, out0, out1, blockIdx.x, lds);
+}
+// dWd and dWg, dWu in one launch, for calls of few tiles: neither fills the chip, and both take the time of
+// one tile, which they then spend side by side.  Blocks 0 .. blocks_gu - 1 do dWg, dWu.  24 groups of 130 rows,
+// 256 x 192: 24.5 -> 13 us a call with the launches; 8 experts, 1024 rows, 128 x 256, batched: 39 -> 22.
+template <int WGM>
+__global__ void __launch_bounds__(THREADS, (WgradCfg<WGM, true>::OCC))
+wgrad_pair_kernel(Sched s, const bf16_t *__restrict__ dY, const bf16_t *__restrict__ A, const bf16_t *__restrict__ X, int h, int hff, int E,
+                  int accumulate, int stream, int total_down, int total_gu, int blocks_gu,
+                  float *__restrict__ dWg, float *__restrict__ dWu, float *__restrict__ dWd)
+{
+    extern __shared__ __attribute__((aligned(1024))) char lds[];
+    if ((int)blockIdx.x < blocks_gu) wgrad_tile<2, WGM, true>(s, s.dGt, s.dU, X, hff, h, E, accumulate, stream, total_gu, dWg, dWu, blockIdx.x, lds);
+    else wgrad_tile<1, WGM, true>(s, dY, nullptr, A, h, hff, E, accumulate, stream, total_down, dWd, nullptr, blockIdx.x - blocks_gu, lds);
 }
 
 // ---------------------------------------------------------------- batched weight gradients
@@ -1025,22 +1045,20 @@ template <int WN> struct WgradWide {
     static constexpr int SLABS = STAGES * (256 + WN) * BK * 2;
     static constexpr int LDS = SLABS > 8 * 8192 ? SLABS : 8 * 8192;
 };
-template <int NA, int WN, int NWV = NWAVES>
-__global__ void __launch_bounds__(NWV * 64, WgradWide<WN>::OCC)
-wgrad_batched_kernel(int E, int m_dim, int n_dim, WgradPlan w, int accumulate, int stream,
-                     float *__restrict__ out0, float *__restrict__ out1)
+template <int NA, int WN, int NWV>
+__device__ __forceinline__ void wgrad_batched_tile(int E, int m_dim, int n_dim, const WgradPlan &w, int accumulate, int stream,
+                                                   float *__restrict__ out0, float *__restrict__ out1, int block, char *lds)
 {
     constexpr int WGM = 256, BA = WGM / NA;
     // NA = 1: the A side (dY) may be gathered; its loads go last in the window (see KLoop)
     // the operand that may come through a row table: dY of dWd (A side), X of dWg, dWu (B side)
     using KL = KLoop<KsTile<BA, BK, NA == 1>, KsTile<WN, BK, NA == 2>, NA, 1, BA, WN, 2, NWV / 2, 1, true, WgradWide<WN>::STAGES, kSpreadLoads, NA == 1>;
-    extern __shared__ __attribute__((aligned(1024))) char lds[];
     const int n_nt = (n_dim + WN - 1) / WN, n_mt = (m_dim + BA - 1) / BA;
     const int per_expert = n_nt * n_mt;
     // Tile list: experts in descending order of rows, each expert's tiles in band order, cut into
     // chunks of kWgradChunk tiles (an 8 x 8 patch sharing operand tiles).  The chunks are dealt to
     // the XCDs back and forth (0..7, 7..0, ...), so every L2 gets near-equal work, heaviest first.
-    const int x = blockIdx.x & 7, t = blockIdx.x >> 3;
+    const int x = block & 7, t = block >> 3;
     const int q = t / kWgradChunk;
     const long long tile = ((long long)q * 8 + ((q & 1) ? 7 - x : x)) * kWgradChunk + t % kWgradChunk;
     if (tile >= (long long)E * per_expert) return;
@@ -1060,6 +1078,24 @@ wgrad_batched_kernel(int E, int m_dim, int n_dim, WgradPlan w, int accumulate, i
                               m_dim, n_dim, m0, n0};
     KL::run_pieces(acc, src, w.piece_ptr[e + 1] - s0, w.exp_slabs[e], lds, tid);
     wgrad_epilogue<KL, NA, BA, NWV>(acc, lds, out0, out1, (size_t)e * m_dim * n_dim, m0, n0, m_dim, n_dim, add, stream != 0, wave, lane);
+}
+template <int NA, int WN, int NWV = NWAVES>
+__global__ void __launch_bounds__(NWV * 64, WgradWide<WN>::OCC)
+wgrad_batched_kernel(int E, int m_dim, int n_dim, WgradPlan w, int accumulate, int stream,
+                     float *__restrict__ out0, float *__restrict__ out1)
+{
+    extern __shared__ __attribute__((aligned(1024))) char lds[];
+    wgrad_batched_tile<NA, WN, NWV>(E, m_dim, n_dim, w, accumulate, stream, out0, out1, blockIdx.x, lds);
+}
+// Both in one launch, for calls of few tiles, as wgrad_pair_kernel.
+template <int WN, int NWV = NWAVES>
+__global__ void __launch_bounds__(NWV * 64, WgradWide<WN>::OCC)
+wgrad_batched_pair_kernel(int E, int h, int hff, WgradPlan w, int accumulate, int stream, int blocks_gu,
+                          float *__restrict__ dWg, float *__restrict__ dWu, float *__restrict__ dWd)
+{
+    extern __shared__ __attribute__((aligned(1024))) char lds[];
+    if ((int)blockIdx.x < blocks_gu) wgrad_batched_tile<2, WN, NWV>(E, hff, h, w, accumulate, stream, dWg, dWu, blockIdx.x, lds);
+    else wgrad_batched_tile<1, WN, NWV>(E, h, hff, w, accumulate, stream, dWd, nullptr, blockIdx.x - blocks_gu, lds);
 }
 
 // Replica gradients return to the home copy (Section 5.1).  A thread owns element positions
@@ -1144,9 +1180,10 @@ static int set_lds_limits()
     RELIBRA_HIP_TRY(hipFuncSetAttribute((const void *)wgrad_batched_kernel<1, 256, kWideWaves>, hipFuncAttributeMaxDynamicSharedMemorySize, WgradWide<256>::LDS));
     RELIBRA_HIP_TRY(hipFuncSetAttribute((const void *)wgrad_batched_kernel<2, 256, kWideWaves>, hipFuncAttributeMaxDynamicSharedMemorySize, WgradWide<256>::LDS));
     RELIBRA_HIP_TRY(hipFuncSetAttribute((const void *)wgrad_kernel<1, 128>, hipFuncAttributeMaxDynamicSharedMemorySize, (WgradCfg<128, false>::LDS)));
-    RELIBRA_HIP_TRY(hipFuncSetAttribute((const void *)wgrad_kernel<1, 128, true>, hipFuncAttributeMaxDynamicSharedMemorySize, (WgradCfg<128, true>::LDS)));
+    RELIBRA_HIP_TRY(hipFuncSetAttribute((const void *)wgrad_pair_kernel<128>, hipFuncAttributeMaxDynamicSharedMemorySize, (WgradCfg<128, true>::LDS)));
     RELIBRA_HIP_TRY(hipFuncSetAttribute((const void *)wgrad_kernel<2, 128>, hipFuncAttributeMaxDynamicSharedMemorySize, (WgradCfg<128, false>::LDS)));
-    RELIBRA_HIP_TRY(hipFuncSetAttribute((const void *)wgrad_kernel<2, 128, true>, hipFuncAttributeMaxDynamicSharedMemorySize, (WgradCfg<128, true>::LDS)));
+    RELIBRA_HIP_TRY(hipFuncSetAttribute((const void *)wgrad_batched_pair_kernel<128>, hipFuncAttributeMaxDynamicSharedMemorySize, WgradWide<128>::LDS));
+    RELIBRA_HIP_TRY(hipFuncSetAttribute((const void *)wgrad_batched_pair_kernel<256, kWideWaves>, hipFuncAttributeMaxDynamicSharedMemorySize, WgradWide<256>::LDS));
     return RELIBRA_OK;
 }
 static int ensure_lds_limits()
@@ -1375,18 +1412,26 @@ static int ffn_bwd_impl(const void *dYrows, const void *Xrows,
     const long long t_down = (long long)Gr * ((h + wgm - 1) / wgm) * ((hff + WGN - 1) / WGN);              // dWd: m in h, n in h'
     const long long t_gu = (long long)Gr * ((hff + wgm / 2 - 1) / (wgm / 2)) * ((h + WGN - 1) / WGN);      // dWg, dWu: m in h', n in h
     const int stream_dw = streams_dw((size_t)n_dw_slots * h * hff);
-#define RELIBRA_WGRAD(WGM_, DEEP_)                                                                                                         \
+#define RELIBRA_WGRAD(WGM_)                                                                                                                \
     do {                                                                                                                                   \
-        RELIBRA_LAUNCH(RELIBRA_K_WGRAD_DOWN, stream, (wgrad_kernel<1, WGM_, DEEP_><<<grid8(t_down), THREADS, WgradCfg<WGM_, DEEP_>::LDS, stream>>>( \
+        RELIBRA_LAUNCH(RELIBRA_K_WGRAD_DOWN, stream, (wgrad_kernel<1, WGM_><<<grid8(t_down), THREADS, (WgradCfg<WGM_, false>::LDS), stream>>>( \
             s, (const bf16_t *)dYrows, nullptr, (const bf16_t *)A_save, h, hff, E, accumulate, stream_dw, (int)t_down, dWd, nullptr)));    \
         RELIBRA_HIP_TRY(launch_check());                                                                                                   \
-        RELIBRA_LAUNCH(RELIBRA_K_WGRAD_GATE_UP, stream, (wgrad_kernel<2, WGM_, DEEP_><<<grid8(t_gu), THREADS, WgradCfg<WGM_, DEEP_>::LDS, stream>>>( \
+        RELIBRA_LAUNCH(RELIBRA_K_WGRAD_GATE_UP, stream, (wgrad_kernel<2, WGM_><<<grid8(t_gu), THREADS, (WgradCfg<WGM_, false>::LDS), stream>>>( \
             s, s.dGt, s.dU, (const bf16_t *)Xrows, hff, h, E, accumulate, stream_dw, (int)t_gu, dWg, dWu)));                               \
         RELIBRA_HIP_TRY(launch_check());                                                                                                   \
     } while (0)
-    if (!small_tiles) RELIBRA_WGRAD(256, false);
-    else if (std::max(t_down, t_gu) <= 2 * kComputeUnits) RELIBRA_WGRAD(128, true);
-    else RELIBRA_WGRAD(128, false);
+    if (!small_tiles) {
+        RELIBRA_WGRAD(256);
+    } else if (std::max(t_down, t_gu) <= 2 * kComputeUnits) {
+        const unsigned blocks_gu = grid8(t_gu);
+        RELIBRA_LAUNCH(RELIBRA_K_WGRAD_GATE_UP, stream, (wgrad_pair_kernel<128><<<blocks_gu + grid8(t_down), THREADS, (WgradCfg<128, true>::LDS), stream>>>(
+            s, (const bf16_t *)dYrows, (const bf16_t *)A_save, (const bf16_t *)Xrows, h, hff, E, accumulate, stream_dw, (int)t_down, (int)t_gu,
+            (int)blocks_gu, dWg, dWu, dWd)));
+        RELIBRA_HIP_TRY(launch_check());
+    } else {
+        RELIBRA_WGRAD(128);
+    }
 #undef RELIBRA_WGRAD
     if (!(flags & RELIBRA_BWD_NO_REPLICA_SUM) && n_dw_slots > E) {
         const size_t vec4 = (size_t)h * hff / 4;
@@ -1496,6 +1541,15 @@ extern "C" int relibra_moe_ffn_wgrad_batched(const relibra_wgrad_mb *mbs, int n_
     const unsigned g_down = grid_of((long long)((h + 255) / 256) * ((hff + wn_down - 1) / wn_down));  // dWd: m in h, n in h'
     const unsigned g_gu = grid_of((long long)((hff + 127) / 128) * ((h + wn_gu - 1) / wn_gu));        // dWg, dWu: m in h', n in h
     const int stream_dw = streams_dw((size_t)E * h * hff);
+    const long long tiles = (long long)E * ((h + 255) / 256 * ((hff + wn_down - 1) / wn_down) + (hff + 127) / 128 * ((h + wn_gu - 1) / wn_gu));
+    if (wide_down == wide_gu && tiles <= kComputeUnits) {
+        if (wide_gu) RELIBRA_LAUNCH(RELIBRA_K_WGRAD_GATE_UP, stream, (wgrad_batched_pair_kernel<256, kWideWaves><<<g_gu + g_down, kWideWaves * 64, WgradWide<256>::LDS, stream>>>(
+            E, h, hff, w, accumulate, stream_dw, (int)g_gu, dWg, dWu, dWd)));
+        else RELIBRA_LAUNCH(RELIBRA_K_WGRAD_GATE_UP, stream, (wgrad_batched_pair_kernel<128><<<g_gu + g_down, THREADS, WgradWide<128>::LDS, stream>>>(
+            E, h, hff, w, accumulate, stream_dw, (int)g_gu, dWg, dWu, dWd)));
+        RELIBRA_HIP_TRY(launch_check());
+        return RELIBRA_OK;
+    }
     if (wide_down) {
         RELIBRA_LAUNCH(RELIBRA_K_WGRAD_DOWN, stream, (wgrad_batched_kernel<1, 256, kWideWaves><<<g_down, kWideWaves * 64, WgradWide<256>::LDS, stream>>>(
             E, h, hff, w, accumulate, stream_dw, dWd, nullptr)));
