@@ -33,6 +33,27 @@ __device__ __forceinline__ uint32_t pack2bf(float lo, float hi)
 
 __device__ __forceinline__ bf16_t f2bf(float f) { return (bf16_t)(pack2bf(f, 0.0f) & 0xffffu); }
 
+// Inclusive sum of v over a block of 256 threads (two barriers), and the block's total.  sums: 4 ints of LDS.
+__device__ __forceinline__ int block_scan256(int v, int32_t *sums, int &total)
+{
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const int below = __shfl_up(v, off);
+        if (lane >= off) v += below;
+    }
+    if (lane == 63) sums[wave] = v;
+    __syncthreads();
+    total = 0;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+        if (w < wave) v += sums[w];
+        total += sums[w];
+    }
+    __syncthreads();                       // sums may be used again
+    return v;
+}
+
 inline bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
 inline hipError_t launch_check() { return hipGetLastError(); }

@@ -121,12 +121,11 @@ sched_kernel(const int32_t *__restrict__ group_offset, const int32_t *__restrict
              Sched s, int32_t *err_flag)
 {
     extern __shared__ int32_t prefix[];        // [Gr + 1] tile_prefix, kept in LDS for the searches below
-    __shared__ int32_t scan[256];
-    __shared__ int32_t carry;
+    __shared__ int32_t sums[4];
     const int tid = threadIdx.x;
-    if (tid == 0) { carry = 0; s.tile_prefix[0] = 0; prefix[0] = 0; }
-    __syncthreads();
+    if (tid == 0) { s.tile_prefix[0] = 0; prefix[0] = 0; }
     bool bad_any = false;
+    int carry = 0;                             // tiles so far, the same in every thread
     for (int base = 0; base < Gr; base += 256) {
         const int i = base + tid;
         int tiles = 0;
@@ -144,18 +143,10 @@ sched_kernel(const int32_t *__restrict__ group_offset, const int32_t *__restrict
             s.grp_slot[i] = slot;
             tiles = (hi - lo + BM - 1) / BM;
         }
-        scan[tid] = tiles;
-        __syncthreads();
-        for (int off = 1; off < 256; off <<= 1) {
-            const int v = tid >= off ? scan[tid - off] : 0;
-            __syncthreads();
-            scan[tid] += v;
-            __syncthreads();
-        }
-        if (i < Gr) s.tile_prefix[i + 1] = prefix[i + 1] = carry + scan[tid];
-        __syncthreads();
-        if (tid == 255) carry += scan[255];
-        __syncthreads();
+        int all;
+        const int upto = block_scan256(tiles, sums, all);
+        if (i < Gr) s.tile_prefix[i + 1] = prefix[i + 1] = carry + upto;
+        carry += all;
     }
     if (bad_any) atomicOr(err_flag, RELIBRA_ERR_GROUP_TABLE);
     const int total = carry;
@@ -175,29 +166,19 @@ sched_kernel(const int32_t *__restrict__ group_offset, const int32_t *__restrict
         const int m = prefix[lo + 1] - prefix[lo], b0 = j / kBand * kBand;
         s.tile_band[t] = (prefix[lo] + b0) | (min(kBand, m - b0) << 24);
     }
-    // live replica slots, in group order (256 groups at a time; a running count in LDS)
-    if (tid == 0) carry = 0;
-    __syncthreads();
+    // live replica slots, in group order (256 groups at a time)
+    carry = 0;
     if (group_dw_slot) {
         for (int base = 0; base < Gr; base += 256) {
             const int i = base + tid;
             const bool live = i < Gr && s.grp_expert[i] >= 0 && s.grp_slot[i] >= E;
-            scan[tid] = live ? 1 : 0;
-            __syncthreads();
-            for (int off = 1; off < 256; off <<= 1) {
-                const int v = tid >= off ? scan[tid - off] : 0;
-                __syncthreads();
-                scan[tid] += v;
-                __syncthreads();
-            }
+            int all;
+            const int at = carry + block_scan256(live ? 1 : 0, sums, all) - 1;
             if (live) {
-                const int at = carry + scan[tid] - 1;
                 s.pair_slot[at] = s.grp_slot[i];
                 s.pair_expert[at] = s.grp_expert[i];
             }
-            __syncthreads();
-            if (tid == 255) carry += scan[255];
-            __syncthreads();
+            carry += all;
         }
     }
     if (tid == 0) s.hdr[1] = carry;
@@ -915,12 +896,11 @@ __global__ void __launch_bounds__(256)
 wgrad_order_kernel(MbTable tb, int n_mb, int G, int inst_cap, int n_rows, int E, int h, int hff, WgradPlan w, int32_t *err_flag)
 {
     extern __shared__ int32_t rows_of[];       // [E]
-    __shared__ int32_t scan[256];
-    __shared__ int32_t carry;
+    __shared__ int32_t sums[4];
     const int tid = threadIdx.x;
     bool bad = false;
-    if (tid == 0) { carry = 0; w.piece_ptr[0] = 0; }
-    __syncthreads();
+    int carry = 0;                             // pieces so far, the same in every thread
+    if (tid == 0) w.piece_ptr[0] = 0;
     // The piece arrays hold S entries: enough for every instance of every micro-batch of a well-formed
     // (monotone) instance table.  A corrupted table whose ranges overlap could list more; pieces
     // beyond S are left out (and flagged), so that nothing is written past the arrays.
@@ -940,18 +920,12 @@ wgrad_order_kernel(MbTable tb, int n_mb, int G, int inst_cap, int n_rows, int E,
             }
         }
         pieces = min(pieces, S + 1);                 // saturate: the sums below stay inside an int
-        scan[tid] = pieces;
-        __syncthreads();
-        for (int off = 1; off < 256; off <<= 1) {
-            const int v = tid >= off ? scan[tid - off] : 0;
-            __syncthreads();
-            scan[tid] += v;
-            __syncthreads();
-        }
+        int all;
+        const int upto = block_scan256(pieces, sums, all);
         if (e < E) {
-            int at = min(carry + scan[tid] - pieces, S);
-            const int end = min(carry + scan[tid], S);
-            if (carry + scan[tid] > S) bad = true;
+            int at = min(carry + upto - pieces, S);
+            const int end = min(carry + upto, S);
+            if (carry + upto > S) bad = true;
             w.piece_ptr[e + 1] = end;
             long long total = 0, slabs = 0;
             for (int mb = 0; mb < n_mb && at < end; ++mb) {
@@ -990,9 +964,7 @@ wgrad_order_kernel(MbTable tb, int n_mb, int G, int inst_cap, int n_rows, int E,
             w.exp_rows[e] = rows_of[e];
             w.exp_slabs[e] = (int32_t)(slabs > 0x7fffffffLL ? 0x7fffffffLL : slabs);
         }
-        __syncthreads();
-        if (tid == 255) carry = min(carry + scan[255], S + 1);
-        __syncthreads();
+        carry = min(carry + all, S + 1);
     }
     if (bad) atomicOr(err_flag, RELIBRA_ERR_GROUP_TABLE);
     __syncthreads();

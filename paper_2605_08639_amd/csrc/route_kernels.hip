@@ -113,26 +113,16 @@ perm_count_kernel(const int32_t *__restrict__ ids, int N, int E, int32_t *__rest
 // One block per expert: exclusive scan of that expert's counts over the units.
 __global__ void __launch_bounds__(256) perm_scan_kernel(int32_t *unit_cnt, int n_units, int E)
 {
-    __shared__ int32_t scan[256];
-    __shared__ int32_t carry;
+    __shared__ int32_t sums[4];
     const int e = blockIdx.x, tid = threadIdx.x;
-    if (tid == 0) carry = 0;
-    __syncthreads();
+    int carry = 0;
     for (int base = 0; base < n_units; base += 256) {
         const int u = base + tid;
         const int c = u < n_units ? unit_cnt[(size_t)u * E + e] : 0;
-        scan[tid] = c;
-        __syncthreads();
-        for (int off = 1; off < 256; off <<= 1) {
-            const int v = tid >= off ? scan[tid - off] : 0;
-            __syncthreads();
-            scan[tid] += v;
-            __syncthreads();
-        }
-        if (u < n_units) unit_cnt[(size_t)u * E + e] = carry + scan[tid] - c;
-        __syncthreads();
-        if (tid == 255) carry += scan[255];
-        __syncthreads();
+        int all;
+        const int upto = block_scan256(c, sums, all);
+        if (u < n_units) unit_cnt[(size_t)u * E + e] = carry + upto - c;
+        carry += all;
     }
 }
 
