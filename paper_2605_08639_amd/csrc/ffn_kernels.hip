@@ -744,29 +744,89 @@ __device__ __forceinline__ void wgrad_epilogue(typename KL::Acc &acc, char *lds,
         }
 }
 
+// The same for the eight-wave tiles.  When adding, a block's old values are requested one block ahead: with one
+// workgroup per unit nobody else covers the round trip, and the registers are free.  (Four small workgroups
+// per unit lose a fourth of their waves to the registers and 17 % of their time.)
+template <class KL, int NA, int BA, int NWV>
+__device__ __forceinline__ void wgrad_epilogue_ahead(typename KL::Acc &acc, char *lds, float *out0, float *out1, size_t base,
+                                               int m0, int n0, int m_dim, int n_dim, bool add, bool stream, int wave, int lane)
+{
+    static_assert(KL::TB % 2 == 0, "a wave owns a multiple of 64 columns");
+    constexpr int BLOCKS = (KL::TB / 2) * NA * KL::TA;        // 32 x 64 blocks of the wave: columns, operands, tiles
+    typedef float f32x4_t __attribute__((ext_vector_type(4)));
+    float *buf = reinterpret_cast<float *>(lds + wave * 8192);
+    const int wm0 = m0 + (wave / (NWV / 2)) * (BA / 2), wn0 = n0 + (wave % (NWV / 2)) * (KL::TB * 32);
+    const int col4 = lane & 15, row4 = lane >> 4;
+    auto tensor = [&](int i) __attribute__((always_inline)) { return ((i / KL::TA) % NA == 0 ? out0 : out1) + base; };
+    auto row_of = [&](int i, int p) __attribute__((always_inline)) { return wm0 + (i % KL::TA) * 32 + p * 4 + row4; };
+    auto col_of = [&](int i) __attribute__((always_inline)) { return wn0 + i / (NA * KL::TA) * 64 + col4 * 4; };
+    f32x4_t old[2][8];
+    auto request = [&](int i, f32x4_t (&o)[8]) __attribute__((always_inline)) {      // clamped: what lies outside is not stored
+#pragma unroll
+        for (int p = 0; p < 8; ++p)
+            o[p] = *reinterpret_cast<const f32x4_t *>(tensor(i) + (size_t)min(row_of(i, p), m_dim - 1) * n_dim + min(col_of(i), n_dim - 4));
+    };
+    if (add) request(0, old[0]);
+    __syncthreads();                                          // every wave is done with the operand slabs
+#pragma unroll
+    for (int i = 0; i < BLOCKS; ++i) {
+        const int half = i / (NA * KL::TA), a = (i / KL::TA) % NA, ta = i % KL::TA;
+#pragma unroll
+        for (int tb = 0; tb < 2; ++tb)
+#pragma unroll
+            for (int v = 0; v < 16; ++v)
+                buf[(8 * (v >> 2) + 4 * (lane >> 5) + (v & 3)) * 64 + tb * 32 + (lane & 31)] = acc[a][ta][half * 2 + tb][v];
+        if (add && i + 1 < BLOCKS) request(i + 1, old[(i + 1) % 2]);
+        wave_lds_fence();
+        f32x4_t val[8];
+#pragma unroll
+        for (int p = 0; p < 8; ++p) val[p] = *reinterpret_cast<const f32x4_t *>(buf + (p * 4 + row4) * 64 + col4 * 4);
+        if (add) {
+#pragma unroll
+            for (int p = 0; p < 8; ++p) val[p] += old[i % 2][p];
+        }
+        auto store = [&](auto streaming) __attribute__((always_inline)) {
+#pragma unroll
+            for (int p = 0; p < 8; ++p) {
+                const int r = row_of(i, p), c = col_of(i);
+                f32x4_t *to = reinterpret_cast<f32x4_t *>(tensor(i) + (size_t)r * n_dim + c);
+                if (r < m_dim && c < n_dim) {
+                    if (decltype(streaming)::value) __builtin_nontemporal_store(val[p], to);
+                    else *to = val[p];
+                }
+            }
+        };
+        if (stream) store(std::true_type{});
+        else store(std::false_type{});
+        wave_lds_fence();
+    }
+}
+
 // Weight gradients: out[slot][m][n] (+)= sum over the group's rows of L[row][m] * R[row][n].
 // NA = 2 computes two left operands against one right operand (dGt and dU against X).
-// Tile: (NA x BA) x WGN with BA = WGM / NA.  Two geometries: WGM = 256 (three slabs, two
-// workgroups per compute unit) for long groups, where the MFMA rate matters, and WGM = 128 (two
+// Tile: (NA x BA) x WN with BA = WGM / NA.  Three geometries: 256 x 256 (eight waves, see wgrad_tiles_wide);
+// for outputs narrower than that WGM = 256 (three slabs, two
+// workgroups per compute unit) for long groups, where the MFMA rate matters; and WGM = 128 (two
 // slabs, four workgroups per compute unit) for short groups, where the kernel is a stream of
 // fp32 read-add-writes and more waves in flight mean more HBM bandwidth.  DEEP, for calls of few
 // tiles: a unit has one or two workgroups at most, so nothing but a workgroup's own ring hides the
 // latency of its slabs.  24 groups of 130 rows, 256 x 192: both calls 27.6 -> 24.8 us (of which 9 are launches).
-template <int WGM, bool DEEP> struct WgradCfg {
-    static constexpr int STAGES = DEEP ? 4 : WGM == 256 ? NSTAGES : 2;
-    static constexpr int OCC = DEEP || WGM == 256 ? 2 : 4;          // waves per SIMD aimed at
-    static constexpr int SLABS = STAGES * (WGM + WGN) * BK * 2;
-    static constexpr int LDS = SLABS > NWAVES * 8192 ? SLABS : NWAVES * 8192;
+template <int WGM, bool DEEP, int WN = WGN> struct WgradCfg {
+    static constexpr int NWV = WN == 256 ? 8 : NWAVES;
+    static constexpr int STAGES = DEEP || WN == 256 ? 4 : WGM == 256 ? NSTAGES : 2;
+    static constexpr int OCC = WN == 256 ? 1 : DEEP || WGM == 256 ? 2 : 4;          // waves per SIMD aimed at
+    static constexpr int SLABS = STAGES * (WGM + WN) * BK * 2;
+    static constexpr int LDS = SLABS > NWV * 8192 ? SLABS : NWV * 8192;
 };
-template <int NA, int WGM, bool DEEP>
+template <int NA, int WGM, bool DEEP, int WN = WGN>
 __device__ __forceinline__ void wgrad_tile(const Sched &s, const bf16_t *__restrict__ L0, const bf16_t *__restrict__ L1,
                                            const bf16_t *__restrict__ R, int m_dim, int n_dim, int E, int accumulate, int stream,
                                            int total, float *__restrict__ out0, float *__restrict__ out1, int block, char *lds)
 {
     constexpr int BA = WGM / NA;
-    using KL = KLoop<KsTile<BA>, KsTile<WGN>, NA, 1, BA, WGN, 2, NWAVES / 2, 1, true, WgradCfg<WGM, DEEP>::STAGES,
-                     (kSpreadLoads && WgradCfg<WGM, DEEP>::STAGES >= 3)>;
-    const int n_nt = (n_dim + WGN - 1) / WGN, n_mt = (m_dim + BA - 1) / BA;
+    using CF = WgradCfg<WGM, DEEP, WN>;
+    using KL = KLoop<KsTile<BA>, KsTile<WN>, NA, 1, BA, WN, 2, CF::NWV / 2, 1, true, CF::STAGES, (kSpreadLoads && CF::STAGES >= 3)>;
+    const int n_nt = (n_dim + WN - 1) / WN, n_mt = (m_dim + BA - 1) / BA;
     const int per_group = n_nt * n_mt;
     const int per_xcd = (total + 7) >> 3;
     const int logical = (block & 7) * per_xcd + (block >> 3);
@@ -781,7 +841,7 @@ __device__ __forceinline__ void wgrad_tile(const Sched &s, const bf16_t *__restr
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     int mt, nt;
     band_order(rem, n_mt, n_nt, mt, nt);
-    const int m0 = mt * BA, n0 = nt * WGN;
+    const int m0 = mt * BA, n0 = nt * WN;
     Operand A[1][NA], B[1][1];
     A[0][0] = {L0 + (size_t)row0 * m_dim, m_dim, m0, m_dim - 1};
     if (NA == 2) A[0][NA - 1] = {L1 + (size_t)row0 * m_dim, m_dim, m0, m_dim - 1};
@@ -789,16 +849,18 @@ __device__ __forceinline__ void wgrad_tile(const Sched &s, const bf16_t *__restr
     typename KL::Acc acc;
     KL::zero(acc);
     KL::run(acc, A, B, (rows + BK - 1) / BK, rows, lds, tid);
-    wgrad_epilogue<KL, NA, BA>(acc, lds, out0, out1, (size_t)slot * m_dim * n_dim, m0, n0, m_dim, n_dim, add, stream != 0, wave, lane);
+    const size_t at = (size_t)slot * m_dim * n_dim;
+    if constexpr (WN == 256) wgrad_epilogue_ahead<KL, NA, BA, CF::NWV>(acc, lds, out0, out1, at, m0, n0, m_dim, n_dim, add, stream != 0, wave, lane);
+    else wgrad_epilogue<KL, NA, BA>(acc, lds, out0, out1, at, m0, n0, m_dim, n_dim, add, stream != 0, wave, lane);
 }
-template <int NA, int WGM>
-__global__ void __launch_bounds__(THREADS, (WgradCfg<WGM, false>::OCC))
+template <int NA, int WGM, int WN = WGN>
+__global__ void __launch_bounds__((WgradCfg<WGM, false, WN>::NWV * 64), (WgradCfg<WGM, false, WN>::OCC))
 wgrad_kernel(Sched s, const bf16_t *__restrict__ L0, const bf16_t *__restrict__ L1,
              const bf16_t *__restrict__ R, int m_dim, int n_dim, int E, int accumulate, int stream, int total,
              float *__restrict__ out0, float *__restrict__ out1)
 {
     extern __shared__ __attribute__((aligned(1024))) char lds[];
-    wgrad_tile<NA, WGM, false>(s, L0, L1, R, m_dim, n_dim, E, accumulate, stream, total, out0, out1, blockIdx.x, lds);
+    wgrad_tile<NA, WGM, false, WN>(s, L0, L1, R, m_dim, n_dim, E, accumulate, stream, total, out0, out1, blockIdx.x, lds);
 }
 // dWd and dWg, dWu in one launch, for calls of few tiles: neither fills the chip, and both take the time of
 // one tile, which they then spend side by side.  Blocks 0 .. blocks_gu - 1 do dWg, dWu.  24 groups of 130 rows,
@@ -1049,7 +1111,9 @@ __device__ __forceinline__ void wgrad_batched_tile(int E, int m_dim, int n_dim, 
                               (const_i32_ptr)(uintptr_t)((NA == 1 ? w.rec_down + (size_t)s0 * kRecDownInts : w.rec_gu + (size_t)s0 * kRecGuInts)),
                               m_dim, n_dim, m0, n0};
     KL::run_pieces(acc, src, w.piece_ptr[e + 1] - s0, w.exp_slabs[e], lds, tid);
-    wgrad_epilogue<KL, NA, BA, NWV>(acc, lds, out0, out1, (size_t)e * m_dim * n_dim, m0, n0, m_dim, n_dim, add, stream != 0, wave, lane);
+    const size_t at = (size_t)e * m_dim * n_dim;
+    if constexpr (WN == 256) wgrad_epilogue_ahead<KL, NA, BA, NWV>(acc, lds, out0, out1, at, m0, n0, m_dim, n_dim, add, stream != 0, wave, lane);
+    else wgrad_epilogue<KL, NA, BA>(acc, lds, out0, out1, at, m0, n0, m_dim, n_dim, add, stream != 0, wave, lane);
 }
 template <int NA, int WN, int NWV = NWAVES>
 __global__ void __launch_bounds__(NWV * 64, WgradWide<WN>::OCC)
@@ -1145,7 +1209,9 @@ static int set_lds_limits()
     RELIBRA_HIP_TRY(hipFuncSetAttribute((const void *)fwd_down_kernel<true, 512>, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytesWide));
     RELIBRA_HIP_TRY(hipFuncSetAttribute((const void *)bwd_dx_kernel<false, 512>, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytesWide));
     RELIBRA_HIP_TRY(hipFuncSetAttribute((const void *)bwd_dx_kernel<true, 512>, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytesWide));
+    RELIBRA_HIP_TRY(hipFuncSetAttribute((const void *)wgrad_kernel<1, 256, 256>, hipFuncAttributeMaxDynamicSharedMemorySize, (WgradCfg<256, false, 256>::LDS)));
     RELIBRA_HIP_TRY(hipFuncSetAttribute((const void *)wgrad_kernel<1, 256>, hipFuncAttributeMaxDynamicSharedMemorySize, (WgradCfg<256, false>::LDS)));
+    RELIBRA_HIP_TRY(hipFuncSetAttribute((const void *)wgrad_kernel<2, 256, 256>, hipFuncAttributeMaxDynamicSharedMemorySize, (WgradCfg<256, false, 256>::LDS)));
     RELIBRA_HIP_TRY(hipFuncSetAttribute((const void *)wgrad_kernel<2, 256>, hipFuncAttributeMaxDynamicSharedMemorySize, (WgradCfg<256, false>::LDS)));
     RELIBRA_HIP_TRY(hipFuncSetAttribute((const void *)wgrad_batched_kernel<1, 128>, hipFuncAttributeMaxDynamicSharedMemorySize, WgradWide<128>::LDS));
     RELIBRA_HIP_TRY(hipFuncSetAttribute((const void *)wgrad_batched_kernel<2, 128>, hipFuncAttributeMaxDynamicSharedMemorySize, WgradWide<128>::LDS));
@@ -1281,6 +1347,19 @@ extern "C" int relibra_moe_ffn_fwd_gated(const void *X, int T, const int32_t *ro
                         Gt_save, U_save, A_save, Yrows, flags, ws, ws_bytes, err_flag, stream_, row_gate, Ag_save);
 }
 
+// Per-micro-batch weight gradients in 256 x 256 tiles of eight waves: half the operand bytes per flop and 1 KiB of
+// a row per store, but one workgroup per compute unit, whose reads of old gradients nobody covers.  From 192 rows
+// per group on when the gradients are written, from 448 when they are added to; outputs of at least 256 each way,
+// and at least one tile per unit.  128 experts of 2048 x 768, dWg and dWu, small (from 512 rows on: 256 x 128)
+// tiles -> these: written, 64 rows per group 294 -> 305 us, 128 404 -> 366, 256 565 -> 476, 512 765 -> 633; added,
+// 256 rows 677 -> 698, 512 845 -> 792, 1024 1170 -> 1082.  8 of 4096 x 14336: written, 128 rows 784 -> 806, 256
+// 1148 -> 1051, 512 1957 -> 1614.
+static inline bool wgrad_tiles_wide(int n_rows, int groups, int h, int hff, bool add)
+{
+    const long long down = (long long)groups * ((h + 255) / 256) * ((hff + 255) / 256);
+    return h >= 256 && hff >= 256 && (long long)n_rows >= (add ? 448LL : 192LL) * groups && down >= kComputeUnits;
+}
+
 // Whether the gradient tensors (fp32, `values` in each) are larger than the 256 MB last-level cache together.
 static inline int streams_dw(size_t values) { return 3 * values * sizeof(float) > ((size_t)256 << 20) ? 1 : 0; }
 
@@ -1379,22 +1458,26 @@ static int ffn_bwd_impl(const void *dYrows, const void *Xrows,
     }
     if (defer) return RELIBRA_OK;                                  // dGt, dU stay in the workspace
     // short groups (few rows per group on average): the small, high-occupancy geometry
-    const bool small_tiles = (long long)n_rows < 512LL * Gr;
-    const int wgm = small_tiles ? 128 : 256;
-    const long long t_down = (long long)Gr * ((h + wgm - 1) / wgm) * ((hff + WGN - 1) / WGN);              // dWd: m in h, n in h'
-    const long long t_gu = (long long)Gr * ((hff + wgm / 2 - 1) / (wgm / 2)) * ((h + WGN - 1) / WGN);      // dWg, dWu: m in h', n in h
+    const bool wide_tiles = wgrad_tiles_wide(n_rows, Gr, h, hff, accumulate != 0);
+    const bool small_tiles = !wide_tiles && (long long)n_rows < 512LL * Gr;
+    const int wgm = small_tiles ? 128 : 256, wgn = wide_tiles ? 256 : WGN;
+    const long long t_down = (long long)Gr * ((h + wgm - 1) / wgm) * ((hff + wgn - 1) / wgn);              // dWd: m in h, n in h'
+    const long long t_gu = (long long)Gr * ((hff + wgm / 2 - 1) / (wgm / 2)) * ((h + wgn - 1) / wgn);      // dWg, dWu: m in h', n in h
     const int stream_dw = streams_dw((size_t)n_dw_slots * h * hff);
-#define RELIBRA_WGRAD(WGM_)                                                                                                                \
+#define RELIBRA_WGRAD(WGM_, WN_)                                                                                                           \
     do {                                                                                                                                   \
-        RELIBRA_LAUNCH(RELIBRA_K_WGRAD_DOWN, stream, (wgrad_kernel<1, WGM_><<<grid8(t_down), THREADS, (WgradCfg<WGM_, false>::LDS), stream>>>( \
+        using CF = WgradCfg<WGM_, false, WN_>;                                                                                             \
+        RELIBRA_LAUNCH(RELIBRA_K_WGRAD_DOWN, stream, (wgrad_kernel<1, WGM_, WN_><<<grid8(t_down), CF::NWV * 64, CF::LDS, stream>>>(        \
             s, (const bf16_t *)dYrows, nullptr, (const bf16_t *)A_save, h, hff, E, accumulate, stream_dw, (int)t_down, dWd, nullptr)));    \
         RELIBRA_HIP_TRY(launch_check());                                                                                                   \
-        RELIBRA_LAUNCH(RELIBRA_K_WGRAD_GATE_UP, stream, (wgrad_kernel<2, WGM_><<<grid8(t_gu), THREADS, (WgradCfg<WGM_, false>::LDS), stream>>>( \
+        RELIBRA_LAUNCH(RELIBRA_K_WGRAD_GATE_UP, stream, (wgrad_kernel<2, WGM_, WN_><<<grid8(t_gu), CF::NWV * 64, CF::LDS, stream>>>(       \
             s, s.dGt, s.dU, (const bf16_t *)Xrows, hff, h, E, accumulate, stream_dw, (int)t_gu, dWg, dWu)));                               \
         RELIBRA_HIP_TRY(launch_check());                                                                                                   \
     } while (0)
-    if (!small_tiles) {
-        RELIBRA_WGRAD(256);
+    if (wide_tiles) {
+        RELIBRA_WGRAD(256, 256);
+    } else if (!small_tiles) {
+        RELIBRA_WGRAD(256, 128);
     } else if (std::max(t_down, t_gu) <= 2 * kComputeUnits) {
         const unsigned blocks_gu = grid8(t_gu);
         RELIBRA_LAUNCH(RELIBRA_K_WGRAD_GATE_UP, stream, (wgrad_pair_kernel<128><<<blocks_gu + grid8(t_down), THREADS, (WgradCfg<128, true>::LDS), stream>>>(
@@ -1402,7 +1485,7 @@ static int ffn_bwd_impl(const void *dYrows, const void *Xrows,
             (int)blocks_gu, dWg, dWu, dWd)));
         RELIBRA_HIP_TRY(launch_check());
     } else {
-        RELIBRA_WGRAD(128);
+        RELIBRA_WGRAD(128, 128);
     }
 #undef RELIBRA_WGRAD
     if (!(flags & RELIBRA_BWD_NO_REPLICA_SUM) && n_dw_slots > E) {

@@ -838,6 +838,33 @@ def test_weight_gradients_of_short_groups(groups):
             assert rel_l2(got[e], want[e]) <= TOL
 
 
+def test_weight_gradients_of_many_rows_per_group():
+    """The 256 x 256 tiles of the per-micro-batch weight gradients: written from about 200 rows per group on (ragged
+    rows and outputs), added to from about 450 on."""
+    E, h, hff, err = 66, 320, 448, rl.new_err_flag()
+    rng = np.random.default_rng(5)
+    for lo, hi in ((129, 290), (380, 580)):
+        rows = rng.integers(lo, hi, E)
+        go, ge, X, dY, Wg, Wu, Wd = ffn_case(seed=lo, E=E, h=h, hff=hff, rows=rows, experts=range(E))
+        go_d, ge_d, W_d = dev_i32(go), dev_i32(ge), [W.to(DEV) for W in (Wg, Wu, Wd)]
+        Xd, dYd = X.to(DEV), dY.to(DEV)
+        Gt, U, A, _ = rl.relibra_moe_ffn_fwd(Xd, go_d, ge_d, *W_d, err_flag=err)
+        dW = [torch.full(W.shape, 3.0, dtype=torch.float32, device=DEV) for W in (Wg, Wu, Wd)]
+        run = lambda flags: rl.relibra_moe_ffn_bwd(dYd, Xd, Gt, U, A, go_d, ge_d, ge_d, *W_d, *dW, err_flag=err, flags=flags)
+        run(0)
+        once = [w.double() for w in dW]
+        run(rl.BWD_ACCUMULATE)
+        assert err.item() == 0
+        g, u, dA = Gt.double(), U.double(), torch.cat([dYd[go[e]:go[e + 1]].double() @ W_d[2][e].double() for e in range(E)])
+        sg = torch.sigmoid(g)
+        dG, dU = dA * u * sg * (1 + g * (1 - sg)), dA * g * sg
+        for e in range(E):
+            at = slice(go[e], go[e + 1])
+            for got, twice, want in zip(once, dW, (dG[at].T @ Xd[at].double(), dU[at].T @ Xd[at].double(), dYd[at].double().T @ A[at].double())):
+                assert rel_l2(got[e], want.cpu().numpy()) <= TOL
+                assert rel_l2(twice[e], 2 * got[e].cpu().numpy()) <= 1e-6
+
+
 @pytest.mark.parametrize("h,hff", [(512, 1024), (960, 1472), (512, 960)])
 def test_gate_fused_backward_on_wide_tiles(h, hff):
     """Gates that are powers of two scale without rounding: the gate-fused data gradients then equal, bit for bit,
