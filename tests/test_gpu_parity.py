@@ -731,6 +731,14 @@ def test_transpose_experts_is_exact(n, a, b):
     assert torch.equal(got, W.transpose(1, 2).contiguous())
 
 
+@pytest.mark.parametrize("a,b", [(128, 128), (120, 136), (264, 8), (8, 248), (136, 392)])
+def test_transpose_experts_at_tile_edges(a, b):
+    W = torch.randn((3, a, b), generator=torch.Generator().manual_seed(a * b)).to(torch.bfloat16).to(DEV)
+    out = torch.full((4, b, a), 7.0, dtype=torch.bfloat16, device=DEV)
+    rl.relibra_transpose_experts(W, out[:3])
+    assert torch.equal(out[:3], W.transpose(1, 2).contiguous()) and (out[3] == 7.0).all()
+
+
 @pytest.mark.parametrize("case", [FFN_CASES[0], FFN_CASES[3], FFN_CASES[4]])
 def test_backward_with_transposed_weights_matches_oracle_and_the_plain_layout(case):
     """The data gradients read their weights from transposed copies: same mathematics, so the
