@@ -92,8 +92,9 @@ Cost cost_of(const std::vector<i64> &L)
 // all integer d the change is at least -floor((L_p - L_q)^2 / 4): a pair of ranks that cannot
 // lower the peak and whose bound cannot reach the best change found so far is skipped whole.  The pairs
 // with a rank at the peak come first; if one of their swaps lowers it, no other pair can do better, else the
-// others follow by descending gap, whose bounds rise, until one cannot reach the best change: a handful
-// once the loads are nearly level.  (The best swap does not depend on the order of the pairs.)
+// others follow by descending gap (a heap), whose bounds rise, until one cannot reach the best change.  In
+// the last step, where no swap gains, that never ends it: the best change is not negative, every bound is at
+// most 0, all pairs are visited.  (The best swap does not depend on the order of the pairs.)
 // D = the integer type of the change: 64 bits when the loads are small enough, else 128.
 template <class D>
 Cost swap_descent_t(const std::vector<i64> &load_of, int EP, std::vector<int> &where)
@@ -134,12 +135,12 @@ Cost swap_descent_t(const std::vector<i64> &load_of, int EP, std::vector<int> &w
                 if (L[p] == cur.peak || L[q] == cur.peak) visit(p, q);
                 else pairs.push_back({p, q, L[p] > L[q] ? L[p] - L[q] : L[q] - L[p]});
             }
-        while (!pairs.empty() && (!have || best_peak >= cur.peak)) {
-            size_t at = 0;
-            for (size_t i = 1; i < pairs.size(); ++i)
-                if (pairs[i].gap > pairs[at].gap) at = i;
-            const RankPair rp = pairs[at];
-            pairs[at] = pairs.back();
+        const auto smaller_gap = [](const RankPair &x, const RankPair &y) { return x.gap < y.gap; };
+        const bool more = !have || best_peak >= cur.peak;                    // no swap with a rank at the peak lowers it
+        if (more) std::make_heap(pairs.begin(), pairs.end(), smaller_gap);
+        while (more && !pairs.empty()) {
+            std::pop_heap(pairs.begin(), pairs.end(), smaller_gap);
+            const RankPair rp = pairs.back();
             pairs.pop_back();
             const D bound = -((D)(rp.gap / 2) * (D)(rp.gap - rp.gap / 2));
             if (have && bound > best_delta) break;                           // cannot reach the best change

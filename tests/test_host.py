@@ -4,6 +4,7 @@ No kernel is launched here."""
 import ctypes
 import os
 import re
+import time
 
 import numpy as np
 import pytest
@@ -92,6 +93,24 @@ def test_planner_equals_oracle_on_paper_shaped_configs(idx):
     got = _assert_same_plan(cfg, _counts(cfg))
     assert (got["max_load_after"] <= got["max_load_before"]).all() or cfg.n_mb > 1
     assert got["max_load_after"].sum() <= got["max_load_before"].sum()
+
+
+@pytest.mark.parametrize("E,EP", [(64, 64), (96, 32), (128, 64), (256, 128)])
+def test_planner_equals_oracle_with_many_ranks(E, EP):
+    """Many pairs of ranks.  The oracle evaluates every swap in every step without any selection of pairs: the
+    library, which selects them, must not be the slower one (it takes a tenth of the oracle's time at 128 ranks)."""
+    cfg = wl.small_config(E=E, EP=EP, k=2, r=1, n_mb=1, ranks_per_node=8)
+    counts = (np.random.default_rng(E + EP).pareto(1.2, (1, E)) * 100).astype(np.int32)
+    _assert_same_plan(cfg, counts)
+    if EP == 128:
+        best = lambda fn: min(_seconds(fn) for _ in range(2))
+        assert best(lambda: rl.relibra_plan(counts, cfg.k, EP, cfg.rpn, 1)) < best(lambda: oracle.plan(counts, EP, cfg.rpn, 1))
+
+
+def _seconds(fn):
+    t = time.perf_counter()
+    fn()
+    return time.perf_counter() - t
 
 
 def test_plan_argument_errors():
