@@ -91,10 +91,12 @@ Cost cost_of(const std::vector<i64> &L)
 // changes by 2 d (L_p - L_q + d), so candidates are compared by (new peak, that change).  Over
 // all integer d the change is at least -floor((L_p - L_q)^2 / 4): a pair of ranks that cannot
 // lower the peak and whose bound cannot reach the best change found so far is skipped whole.  The pairs
-// with a rank at the peak come first; if one of their swaps lowers it, no other pair can do better, else the
-// others follow by descending gap (a heap), whose bounds rise, until one cannot reach the best change.  In
-// the last step, where no swap gains, that never ends it: the best change is not negative, every bound is at
-// most 0, all pairs are visited.  (The best swap does not depend on the order of the pairs.)
+// with a rank at the peak come first; if one of their swaps lowers it, no other pair can do better.  Else the
+// others follow, for every rank from the heaviest on against the lightest first: its gaps fall, so its
+// first pair that cannot reach the best change ends its turn.  In the last step, where no swap gains, all
+// pairs are visited.  Ordering the ranks and not the pairs matters with many ranks: sorting the pairs
+// took more than their swaps did (256 experts on 128 ranks, one micro-batch: 35 ms, 9 ms like this; on 16
+// ranks 6.5 and 6).  The best swap does not depend on the order of the pairs.
 // D = the integer type of the change: 64 bits when the loads are small enough, else 128.
 template <class D>
 Cost swap_descent_t(const std::vector<i64> &load_of, int EP, std::vector<int> &where)
@@ -104,8 +106,7 @@ Cost swap_descent_t(const std::vector<i64> &load_of, int EP, std::vector<int> &w
     for (int e = 0; e < E; ++e) L[where[e]] += load_of[e];
     std::vector<std::vector<int>> on(EP);
     for (int e = 0; e < E; ++e) on[where[e]].push_back(e);
-    struct RankPair { int p, q; i64 gap; };
-    std::vector<RankPair> pairs;
+    std::vector<int> by_load(EP);
     Top3 top;
     for (;;) {
         const Cost cur = cost_of(L);
@@ -114,37 +115,30 @@ Cost swap_descent_t(const std::vector<i64> &load_of, int EP, std::vector<int> &w
         i64 best_peak = 0;
         D best_delta = 0;
         int pa = -1, pb = -1;
-        auto visit = [&](int p, int q) {
-            const i64 rest = top.max_excluding(p, q);
-            for (int x : on[p])
-                for (int y : on[q]) {
-                    const int a = x < y ? x : y, b = x < y ? y : x;
-                    const int ga = x < y ? p : q, gb = x < y ? q : p;
-                    const i64 d = load_of[b] - load_of[a];                  // rank ga gains d, rank gb loses d
-                    const i64 peak = std::max(std::max(L[ga] + d, L[gb] - d), rest);
-                    if (have && peak > best_peak) continue;
-                    const D delta = (D)d * (D)(L[ga] - L[gb] + d);           // half the change of the sum of squares
-                    const bool better = !have || peak < best_peak || delta < best_delta ||
-                                        (delta == best_delta && (a < pa || (a == pa && b < pb)));
-                    if (better) { have = true; best_peak = peak; best_delta = delta; pa = a; pb = b; }
-                }
-        };
-        pairs.clear();
-        for (int p = 0; p < EP; ++p)
-            for (int q = p + 1; q < EP; ++q) {
-                if (L[p] == cur.peak || L[q] == cur.peak) visit(p, q);
-                else pairs.push_back({p, q, L[p] > L[q] ? L[p] - L[q] : L[q] - L[p]});
+        std::iota(by_load.begin(), by_load.end(), 0);
+        std::sort(by_load.begin(), by_load.end(), [&](int x, int y) { return L[x] > L[y]; });
+        for (int i = 0; i < EP; ++i) {
+            const int p = by_load[i];
+            const bool at_peak = L[p] == cur.peak;
+            if (!at_peak && have && best_peak < cur.peak) break;
+            for (int j = EP - 1; j > i; --j) {
+                const int q = by_load[j];
+                const i64 gap = L[p] - L[q];
+                if (!at_peak && have && -((D)(gap / 2) * (D)(gap - gap / 2)) > best_delta) break;
+                const i64 rest = top.max_excluding(p, q);
+                for (int x : on[p])
+                    for (int y : on[q]) {
+                        const int a = x < y ? x : y, b = x < y ? y : x;
+                        const int ga = x < y ? p : q, gb = x < y ? q : p;
+                        const i64 d = load_of[b] - load_of[a];               // rank ga gains d, rank gb loses d
+                        const i64 peak = std::max(std::max(L[ga] + d, L[gb] - d), rest);
+                        if (have && peak > best_peak) continue;
+                        const D delta = (D)d * (D)(L[ga] - L[gb] + d);        // half the change of the sum of squares
+                        const bool better = !have || peak < best_peak || delta < best_delta ||
+                                            (delta == best_delta && (a < pa || (a == pa && b < pb)));
+                        if (better) { have = true; best_peak = peak; best_delta = delta; pa = a; pb = b; }
+                    }
             }
-        const auto smaller_gap = [](const RankPair &x, const RankPair &y) { return x.gap < y.gap; };
-        const bool more = !have || best_peak >= cur.peak;                    // no swap with a rank at the peak lowers it
-        if (more) std::make_heap(pairs.begin(), pairs.end(), smaller_gap);
-        while (more && !pairs.empty()) {
-            std::pop_heap(pairs.begin(), pairs.end(), smaller_gap);
-            const RankPair rp = pairs.back();
-            pairs.pop_back();
-            const D bound = -((D)(rp.gap / 2) * (D)(rp.gap - rp.gap / 2));
-            if (have && bound > best_delta) break;                           // cannot reach the best change
-            visit(rp.p, rp.q);
         }
         if (!have || !(best_peak < cur.peak || (best_peak == cur.peak && best_delta < 0))) return cur;
         const int ga = where[pa], gb = where[pb];
