@@ -13,6 +13,7 @@
 
 #include <algorithm>
 #include <atomic>
+#include <condition_variable>
 #include <cstdint>
 #include <cstring>
 #include <exception>
@@ -352,8 +353,6 @@ int workers_for(int tasks, double us)
     return std::max(1, std::min({want, (int)(hw ? hw : 1u), tasks, 16}));
 }
 
-// 32 micro-batches, 128 experts on 16 ranks, histogram and copies included: 1566 us with two pools of 16 threads
-// and a descent that sorted all pairs of ranks in every step, 550 us like this.
 // Runs fn on `workers` threads, the calling one among them.  An exception of a worker (std::bad_alloc) is
 // handed to the caller after all threads have ended.
 template <class Fn> void run_workers(int workers, const Fn &fn)
@@ -379,8 +378,38 @@ template <class Fn> void run_workers(int workers, const Fn &fn)
     if (failed) std::rethrow_exception(failed);
 }
 
+// A count that workers wait for, asleep, until it has come down to zero.
+class Latch {
+public:
+    explicit Latch(int n) : left(n) {}
+    struct Arrive {
+        Latch &latch;
+        explicit Arrive(Latch &l) : latch(l) {}
+        ~Arrive()
+        {
+            std::lock_guard<std::mutex> lock(latch.m);
+            if (--latch.left == 0) latch.cv.notify_all();
+        }
+    };
+    void wait()
+    {
+        std::unique_lock<std::mutex> lock(m);
+        cv.wait(lock, [&]() { return left == 0; });
+    }
+
+private:
+    std::mutex m;
+    std::condition_variable cv;
+    int left;
+};
+
 // About what one micro-batch costs in stage 2.
 double replicate_us(int E, int EP, int r) { return 2.0 + 0.02 * E + 0.06 * EP * r * 8; }
+
+// Whether the two descents of stage 1 are worth a second thread even if stage 2 is not: from about 200 us each on.
+// Both in a row / side by side, one micro-batch: 64 experts on 8 ranks 150 / 195 us, 128 on 8 295 / 340, 256 on 8
+// 730 / 700, 512 on 2 860 / 670, 256 on 16 7.9 / 5.9 ms.
+bool descents_side_by_side(int E, int EP) { return EP > 1 && (long long)E * std::max(EP, E / 128) >= 1500; }
 
 std::vector<MbPlan> replicate_batch(const int32_t *counts, int n_mb, const std::vector<int> &where,
                                     int E, int EP, int rpn, int r)
@@ -588,24 +617,20 @@ static int plan_impl(const int32_t *counts, int n_mb, int E, int k, int EP, int 
         std::vector<MbPlan> with_new(n_mb);
         chosen = unplanned;
         chosen_plans.resize(n_mb);
-        std::atomic<int> first{0}, second{0}, descents{0};
-        const double us = replicate_us(E, EP, r);
-        run_workers(workers_for(2 * n_mb + 2, us), [&]() {
-            struct Done {                                  // also when a descent throws: nobody waits for ever
-                std::atomic<int> *n = nullptr;
-                ~Done() { if (n) n->fetch_add(1, std::memory_order_release); }
-            };
+        std::atomic<int> first{0}, second{0};
+        Latch descents(2);
+        const int workers = std::max(workers_for(2 * n_mb, replicate_us(E, EP, r)), descents_side_by_side(E, EP) ? 2 : 1);
+        run_workers(workers, [&]() {
             for (int i; (i = first.fetch_add(1)) < n_mb + 2;) {
                 if (i < 2) {
-                    Done done;
-                    done.n = &descents;
+                    const Latch::Arrive done(descents);    // also when a descent throws: nobody waits for ever
                     if (i == 0) c_id = swap_descent(batch_load, EP, from_id);
                     else c_lpt = swap_descent(batch_load, EP, from_lpt);
                 } else {
                     chosen_plans[i - 2] = replicate_microbatch(counts + (size_t)(i - 2) * E, unplanned, E, EP, rpn, r);
                 }
             }
-            while (descents.load(std::memory_order_acquire) < 2) std::this_thread::yield();
+            descents.wait();
             const std::vector<int> &to = (c_lpt < c_id) ? from_lpt : from_id;
             if (to == unplanned) return;
             for (int mb; (mb = second.fetch_add(1)) < n_mb;)

@@ -4,6 +4,7 @@ No kernel is launched here."""
 import ctypes
 import os
 import re
+import threading
 import time
 
 import numpy as np
@@ -105,6 +106,28 @@ def test_planner_equals_oracle_with_many_ranks(E, EP):
     if EP == 128:
         best = lambda fn: min(_seconds(fn) for _ in range(2))
         assert best(lambda: rl.relibra_plan(counts, cfg.k, EP, cfg.rpn, 1)) < best(lambda: oracle.plan(counts, EP, cfg.rpn, 1))
+
+
+def test_planner_runs_long_descents_side_by_side_and_waits_asleep():
+    """Few micro-batches: stage 2 alone is not worth a thread, the two descents are.  Many: the workers that wait
+    for the descents use no processor time (a call of 16 micro-batches on 128 ranks is nearly all descent)."""
+    rng = np.random.default_rng(0)
+    hist = lambda n_mb: (rng.pareto(1.2, (n_mb, 256)) * 100).astype(np.int32)
+    counts, seen, done = hist(1), [], threading.Event()
+    watch = threading.Thread(target=lambda: [seen.append(len(os.listdir("/proc/self/task"))) for _ in iter(done.is_set, True)])
+    watch.start()
+    alone = len(os.listdir("/proc/self/task"))
+    for _ in range(10):
+        rl.relibra_plan(counts, 2, 16, 8, 1)
+    done.set()
+    watch.join()
+    assert os.cpu_count() == 1 or max(seen) == alone + 1
+    counts = hist(16)
+    wall, cpu = time.perf_counter(), time.process_time()
+    for _ in range(4):
+        rl.relibra_plan(counts, 2, 128, 8, 0)
+    wall, cpu = time.perf_counter() - wall, time.process_time() - cpu
+    assert cpu < 2.4 * wall, (cpu, wall)                   # two descents at a time, and a little of stage 2
 
 
 def _seconds(fn):
