@@ -180,7 +180,6 @@ struct Node {
     Shares share;
     std::vector<i64> L;                    // rank loads
     std::vector<int> spread;               // balance(): experts with more than one rank
-    std::vector<char> tried;               // solve(): candidates without a feasible target
 
     void recompute_loads()
     {
@@ -269,22 +268,17 @@ struct Node {
         for (;;) {
             const int gb = (int)(std::max_element(L.begin(), L.end()) - L.begin());   // first max
             if (L[gb] <= floor_load) break;
-            // experts served on gb, most tokens first (ties: lower id), until one has a feasible target
-            int e_pick = -1, g_pick = -1;
-            tried.assign(ne, 0);
-            for (;;) {
-                int e = -1;
-                for (int i = 0; i < ne; ++i)
-                    if (!tried[i] && share[i][gb] > 0 && (e < 0 || share[i][gb] > share[e][gb])) e = i;
-                if (e < 0) break;
-                for (int g = 0; g < n; ++g) {
-                    if ((allowed[e] >> g & 1) || slots_used[g] >= r) continue;
-                    if (g_pick < 0 || L[g] < L[g_pick]) g_pick = g;
-                }
-                if (g_pick >= 0) { e_pick = e; break; }
-                tried[e] = 1;
-            }
+            // the expert with most tokens on gb (ties: lower id) among those that a rank with a free slot does not serve yet
+            uint32_t open = 0;
+            for (int g = 0; g < n; ++g)
+                if (slots_used[g] < r) open |= 1u << g;
+            int e_pick = -1;
+            for (int e = 0; open && e < ne; ++e)
+                if ((open & ~allowed[e]) && share[e][gb] > 0 && (e_pick < 0 || share[e][gb] > share[e_pick][gb])) e_pick = e;
             if (e_pick < 0) break;
+            int g_pick = -1;
+            for (int g = 0; g < n; ++g)
+                if ((open & ~allowed[e_pick]) >> g & 1 && (g_pick < 0 || L[g] < L[g_pick])) g_pick = g;
             allowed[e_pick] |= 1u << g_pick;
             ++slots_used[g_pick];
             balance();

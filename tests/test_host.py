@@ -130,6 +130,15 @@ def test_planner_runs_long_descents_side_by_side_and_waits_asleep():
     assert cpu < 2.4 * wall, (cpu, wall)                   # two descents at a time, and a little of stage 2
 
 
+def test_replication_without_free_slots_looks_at_every_expert_once():
+    """No rank has a slot left: nothing can be placed, which takes one look at the experts and not one per expert."""
+    E, counts = 16384, (np.random.default_rng(3).pareto(1.2, (1, 16384)) * 100).astype(np.int32)
+    rank = np.repeat(np.arange(2, dtype=np.int32), E // 2)
+    assert np.array_equal(rl.relibra_plan(counts, 2, 2, 2, 1, expert_rank=rank)["inst_rows"], oracle.plan(counts, 2, 2, 1, placed=rank)["inst_rows"])
+    none, one = (min(_seconds(lambda: rl.relibra_plan(counts, 2, 2, 2, r, expert_rank=rank)) for _ in range(3)) for r in (0, 1))
+    assert none < 10 * one
+
+
 def _seconds(fn):
     t = time.perf_counter()
     fn()
