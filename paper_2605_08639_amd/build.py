@@ -2,7 +2,9 @@
 from __future__ import annotations
 
 import os
+import re
 import subprocess
+import sys
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
@@ -17,14 +19,37 @@ FLAGS = ["-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC",
          "-Wall", "-Wno-unused-function"]
 
 
+def compile_source(src: str, obj: str) -> None:
+    """Compiles one source.  A kernel that needs scratch memory is an error: the GEMM kernels count their loads in
+    flight by hand, and the reload of a spilled register, counted by the compiler, waits for all of them."""
+    report = ["-Rpass-analysis=kernel-resource-usage"] if src.endswith(".hip") else []
+    run = subprocess.run([HIPCC, *FLAGS, *report, "-c", src, "-o", obj], stderr=subprocess.PIPE, text=True)
+    remark, name, spilled = False, "", []
+    for line in run.stderr.splitlines():
+        if "[-Rpass-analysis=kernel-resource-usage]" in line:
+            remark = True
+            found = re.search(r"(Function Name|ScratchSize \[bytes/lane\]): (\S+)", line)
+            if found and found[1] == "Function Name":
+                name = found[2]
+            elif found and found[2] != "0":
+                spilled.append(f"{name} ({found[2]} bytes per lane)")
+        elif not (remark and re.match(r"\s*\d*\s*\|", line)):      # (source excerpts follow the remarks)
+            remark = False
+            print(line, file=sys.stderr)
+    if run.returncode:
+        raise subprocess.CalledProcessError(run.returncode, run.args)
+    if spilled:
+        os.remove(obj)
+        raise RuntimeError("kernels use scratch memory: " + ", ".join(spilled))
+
+
 def build(verbose: bool = False) -> str:
     objs = []
     for src in SOURCES:
         obj = os.path.join(CSRC, os.path.splitext(src)[0] + ".o")
-        cmd = [HIPCC, *FLAGS, "-c", os.path.join(CSRC, src), "-o", obj]
         if verbose:
-            print(" ".join(cmd))
-        subprocess.check_call(cmd)
+            print(" ".join([HIPCC, *FLAGS, "-c", os.path.join(CSRC, src), "-o", obj]), flush=True)
+        compile_source(os.path.join(CSRC, src), obj)
         objs.append(obj)
     cmd = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs, "-lpthread"]
     if verbose:

@@ -662,15 +662,15 @@ struct KLoop {
         }
     }
 
-    // One trip of the steady state: slabs t .. t+TRIP-1 in ring slots 1, 2, .., 0 (t % TRIP == 1).  ALT: a trip
-    // is a whole turn of both rings, so that every place in them is a constant.
-    static constexpr int TRIP = ALT ? 2 * STAGES : STAGES;
+    // One trip of the steady state: slabs t .. t+TRIP-1, where t % TRIP == TRIP0.  ALT: a trip is a whole turn of
+    // both rings, so that every place in them is a constant.
+    static constexpr int TRIP = ALT ? 2 * STAGES : STAGES, TRIP0 = ALT ? 2 : 1;
     static_assert(!ALT || TRIP == 2 * SB, "a trip turns both rings");
     template <class Slab, int U>
     static __device__ __forceinline__ void steady_trip(const Slab &slab, int t, std::integral_constant<int, U>)
     {
         if constexpr (U < TRIP) {
-            slab(std::true_type{}, std::integral_constant<int, (1 + U) % TRIP>{}, std::integral_constant<int, ALT ? (1 + U) & 1 : 0>{}, t + U);
+            slab(std::true_type{}, std::integral_constant<int, (TRIP0 + U) % TRIP>{}, std::integral_constant<int, ALT ? (TRIP0 + U) & 1 : 0>{}, t + U);
             steady_trip(slab, t, std::integral_constant<int, U + 1>{});
         }
     }
@@ -777,17 +777,27 @@ struct KLoop {
             constexpr auto dyn = std::integral_constant<int, -1>{};
             constexpr auto even = std::integral_constant<int, 0>{};
             constexpr auto odd = std::integral_constant<int, ALT ? 1 : 0>{};
-            slab(std::false_type{}, dyn, even, 0);
-            int t = 1;
-            // Steady trips: slab t sits in ring slot t % STAGES (t = 1 in slot 1); a trip leaves `slot`
-            // and `prv` as they are.  The loads a steady slab issues are those of slabs t-1+STAGES and
-            // t+STAGES, which must be whole (no clamped k-rows): the last slab of a ragged contraction
-            // is left to the general copy; so is ALT's last period, which loads no new B tile.
+            // Steady trips: slab t sits in ring slot t % STAGES; a trip leaves `slot` and `prv` as they are.  The
+            // loads a steady slab issues are those of slabs t-1+STAGES and t+STAGES, which must be whole (no
+            // clamped k-rows): the last slab of a ragged contraction is left to the general copy; so is ALT's
+            // last period, which loads no new B tile.
             const int steady_end = n - STAGES - (RAGGED_K || ALT ? 1 : 0);
-            for (; t + TRIP <= steady_end; t += TRIP) steady_trip(slab, t, std::integral_constant<int, 0>{});
-            for (; t < n; ++t) {
-                if (ALT && (t & 1)) slab(std::false_type{}, dyn, odd, t);
-                else slab(std::false_type{}, dyn, even, t);
+            int t = 0;
+            if constexpr (ALT) {
+                // The general copy in pairs (n is even), the same code before and after the trips.  A branch on
+                // the parity of t would join two paths of which each changes one operand's accumulators: the
+                // compiler then keeps a second set of them, copies it every time, and is out of registers.  64 experts
+                // of 768 x 2048, 300 rows each, that way -> like this: forward 311 -> 304 us.
+                do {
+                    slab(std::false_type{}, dyn, even, t);
+                    slab(std::false_type{}, dyn, odd, t + 1);
+                    t += 2;
+                    for (; t + TRIP <= steady_end; t += TRIP) steady_trip(slab, t, std::integral_constant<int, 0>{});
+                } while (t < n);
+            } else {
+                slab(std::false_type{}, dyn, even, t++);
+                for (; t + TRIP <= steady_end; t += TRIP) steady_trip(slab, t, std::integral_constant<int, 0>{});
+                for (; t < n; ++t) slab(std::false_type{}, dyn, even, t);
             }
         } else {
         for (int t = 0; t < n; ++t) {

@@ -29,6 +29,18 @@ def test_library_exports_every_declared_symbol():
     assert set(rl.EXPORTS) == declared
 
 
+def test_build_refuses_a_kernel_that_needs_scratch_memory(tmp_path):
+    from paper_2605_08639_amd import build
+    source = "#include <hip/hip_runtime.h>\n__global__ void spills(float *p, const int *at) { %s }\n"
+    plain, spills = tmp_path / "plain.hip", tmp_path / "spills.hip"
+    plain.write_text(source % "p[threadIdx.x] = 1.0f;")
+    spills.write_text(source % "volatile float v[64]; for (int i = 0; i < 64; ++i) v[i] = p[i]; p[threadIdx.x] = v[at[threadIdx.x] & 63];")
+    build.compile_source(str(plain), str(tmp_path / "plain.o"))
+    assert (tmp_path / "plain.o").exists()
+    with pytest.raises(RuntimeError, match="spills.*bytes per lane"):
+        build.compile_source(str(spills), str(tmp_path / "spills.o"))
+
+
 def _counts(cfg):
     ids = np.stack([wl.make_routing(cfg, mb)[0] for mb in range(cfg.n_mb)])
     return oracle.route_hist(ids, cfg.E)[0]
