@@ -19,28 +19,32 @@ FLAGS = ["-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC",
          "-Wall", "-Wno-unused-function"]
 
 
-def compile_source(src: str, obj: str) -> None:
-    """Compiles one source.  A kernel that needs scratch memory is an error: the GEMM kernels count their loads in
-    flight by hand, and the reload of a spilled register, counted by the compiler, waits for all of them."""
+def compile_source(src: str, obj: str) -> dict:
+    """Compiles one source and returns what each of its kernels takes ({kernel: {"VGPRs": .., "LDS Size": .., ..}}).
+    A kernel that needs scratch memory is an error: the GEMM kernels count their loads in flight by hand, and
+    the reload of a spilled register, counted by the compiler, waits for all of them."""
     report = ["-Rpass-analysis=kernel-resource-usage"] if src.endswith(".hip") else []
     run = subprocess.run([HIPCC, *FLAGS, *report, "-c", src, "-o", obj], stderr=subprocess.PIPE, text=True)
-    remark, name, spilled = False, "", []
+    remark, kernel, usage = False, {}, {}
     for line in run.stderr.splitlines():
         if "[-Rpass-analysis=kernel-resource-usage]" in line:
             remark = True
-            found = re.search(r"(Function Name|ScratchSize \[bytes/lane\]): (\S+)", line)
-            if found and found[1] == "Function Name":
-                name = found[2]
-            elif found and found[2] != "0":
-                spilled.append(f"{name} ({found[2]} bytes per lane)")
+            name = re.search(r"Function Name: (\S+)", line)
+            value = re.search(r"remark:\s+([A-Za-z ]+?)(?: \[\S+\])?: (\d+) ", line)
+            if name:
+                kernel = usage.setdefault(name[1], {})
+            elif value:
+                kernel[value[1]] = int(value[2])
         elif not (remark and re.match(r"\s*\d*\s*\|", line)):      # (source excerpts follow the remarks)
             remark = False
             print(line, file=sys.stderr)
     if run.returncode:
         raise subprocess.CalledProcessError(run.returncode, run.args)
+    spilled = [f"{name} ({k['ScratchSize']} bytes per lane)" for name, k in usage.items() if k["ScratchSize"]]
     if spilled:
         os.remove(obj)
         raise RuntimeError("kernels use scratch memory: " + ", ".join(spilled))
+    return usage
 
 
 def build(verbose: bool = False) -> str:

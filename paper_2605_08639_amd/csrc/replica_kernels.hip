@@ -5,23 +5,51 @@
 // a small, caller-chosen number of workgroups (the counterpart of the paper's few-SM persistent
 // copy kernel).
 //
-// What bounds them is how many bytes one compute unit keeps in flight: the caller gives 16 units by
-// default, and a unit's rate is its outstanding loads over the memory latency.  A workgroup is
-// therefore as large as a compute unit takes (1024 threads) and every thread issues all its loads of
-// a chunk before it stores.  The table of slots is compacted into LDS in parallel first: read entry by
-// entry it costs a memory round trip per slot and position.  Measured with 16 workgroups, 8 live slots
-// of 3 x 2048 x 768 parameters: push (151 MB moved) 125 us, 153 us with 256 threads and four loads each;
-// pull (453 MB) 425 us, 1384 us with 256 threads and one position at a time.  Both then move about 70 GB/s
-// per compute unit; half the loads per thread cost 12 and 1 %, half the threads 12 and 5 %.
+// What bounds them is how many bytes one compute unit keeps in flight (the caller gives 16 units by default, and a
+// unit's rate is its outstanding loads over the memory latency) and, beside compute, when a workgroup gets to start.
+// Every thread issues all its loads of a chunk before it stores.  A workgroup is 512 threads of at most 128
+// registers: it fits on a unit next to one workgroup of the narrow row tiles (two to a unit, 232 registers,
+// 72 KiB of LDS), so it starts when one of the two ends.  1024 threads, which a unit takes only when it is
+// empty, waited for that as long as tiles were queued.  The table of slots is compacted into LDS in parallel first:
+// read entry by entry it costs a memory round trip per slot and position.
+// Measured with 8 live slots of 3 x 2048 x 768 parameters, 16 and 64 workgroups, us; in turn 256 threads with four
+// loads each (pull: one position at a time), 1024 threads (16 and 8 loads), this:
+//                                       push 16        push 64        pull 16           pull 64
+//   alone                               98  86  88     32  31  28     1085  334  332    293  114  114
+//   beside narrow tiles, 64 experts
+//     of 3136 x 1408, 400 rows each    525 770 289    209 637 157     2898 1114  698    794  751  277
+//   beside wide tiles, 2048 x 1536     437 241 242    158 105 106     2685  633  637    754  217  212
+//   beside short groups' weight
+//     gradients, 2048 x 1408           686 271 272    251 107 104     4525  904  925   1213  292  280
+// Alone on larger blocks 1024 threads are 5 % faster (8 slots of 3 x 4096 x 1536, push 16: 485 against 510).
 #include "common.h"
+#include <type_traits>
 
 namespace relibra {
 
-constexpr int kReplicaThreads = 1024;
-constexpr int kPushLoads = 16, kPullLoads = 8;             // 16-byte pieces per thread and chunk (pull: of both operands)
+constexpr int kReplicaThreads = 512;
+constexpr int kPushLoads = 24, kPullLoads = 12;            // 16-byte pieces per thread and chunk (pull: of both operands)
 constexpr int kTableChunk = kReplicaThreads;               // slots listed at a time
+constexpr int kReplicaWaves = 4;                           // waves per SIMD that the registers leave room for: at most 128 each
+// Sizes inside a block are 32-bit: 64 GiB, and three tensors of at least two blocks do not fit the card.  (Besides, a
+// 64-bit chunk length used both as a branch condition and as a value has come out of the compiler as a select on
+// a condition code that something else had set.)
+constexpr size_t kMaxVec = 0xffff0000u;
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
+// A wave-uniform pointer as a scalar base of its own: a lane's address is that base and one 32-bit offset, the same for
+// all its loads.  (Otherwise the compiler forms a 64-bit address per load, two more registers each.)
+#define RELIBRA_GLOBAL __attribute__((address_space(1)))
+template <class T> __device__ __forceinline__ RELIBRA_GLOBAL T *scalar_base(T *p)
+{
+    RELIBRA_GLOBAL T *g = (RELIBRA_GLOBAL T *)p;
+#ifdef __HIP_DEVICE_COMPILE__
+    asm("" : "+s"(g));
+#endif
+    return g;
+}
 
 // The live ones of table entries base .. base + kTableChunk - 1, in ascending slot order.
 struct LiveSlots {
@@ -57,55 +85,54 @@ __device__ __forceinline__ void list_live(const int32_t *__restrict__ replica_ex
 }
 
 // For every live slot s (replica_expert[s] = e >= 0): the three parameter blocks of expert e
-// (per_expert_vec 16-byte vectors each) are copied to slot E + s.  The (slot, tensor, chunk) units
+// (vec 16-byte vectors each) are copied to slot E + s.  The (slot, tensor, chunk) units
 // are dealt to the workgroups round robin.
-__global__ void __launch_bounds__(kReplicaThreads)
+__global__ void __launch_bounds__(kReplicaThreads, kReplicaWaves)
 replica_push_kernel(u32x4_t *__restrict__ Wg, u32x4_t *__restrict__ Wu, u32x4_t *__restrict__ Wd,
-                    const int32_t *__restrict__ replica_expert, int n_slots, int E, size_t per_expert_vec,
+                    const int32_t *__restrict__ replica_expert, int n_slots, int E, uint32_t vec,
                     int32_t *__restrict__ err_flag)
 {
     __shared__ LiveSlots l;
-    constexpr size_t CHUNK = (size_t)kReplicaThreads * kPushLoads;
-    const size_t chunks = (per_expert_vec + CHUNK - 1) / CHUNK, units = 3 * chunks;      // per slot
+    constexpr uint32_t CHUNK = kReplicaThreads * kPushLoads;
+    const uint32_t chunks = (vec + CHUNK - 1) / CHUNK, units = 3 * chunks;      // per slot
     bool bad = false;
     for (int base = 0; base < n_slots; base += kTableChunk) {
         list_live(replica_expert, base, n_slots, E, l, bad);
-        for (size_t u = blockIdx.x; u < (size_t)l.n * units; u += gridDim.x) {
-            const int i = (int)(u / units);
-            const size_t c = u - (size_t)i * units, which = c / chunks;
+        const int live = uniform(l.n);
+        for (uint32_t u = blockIdx.x; u < (uint32_t)live * units; u += gridDim.x) {
+            const uint32_t i = u / units, c = u - i * units, which = c / chunks;
             u32x4_t *__restrict__ W = which == 0 ? Wg : which == 1 ? Wu : Wd;
-            const size_t at = (c - which * chunks) * CHUNK;
-            const int n = (int)min(CHUNK, per_expert_vec - at);
-            const u32x4_t *__restrict__ src = W + (size_t)l.expert[i] * per_expert_vec + at;
-            u32x4_t *__restrict__ dst = W + (size_t)(E + l.slot[i]) * per_expert_vec + at;
-            if (n < (int)CHUNK) {                          // the block's last chunk
-                for (int j = threadIdx.x; j < n; j += kReplicaThreads) dst[j] = src[j];
+            const uint32_t at = (c - which * chunks) * CHUNK, n = vec - at;      // vectors from here to the block's end
+            const u32x4_t *src = W + (size_t)uniform(l.expert[i]) * vec + at;
+            u32x4_t *dst = W + (size_t)(E + uniform(l.slot[i])) * vec + at;
+            if (n < CHUNK) {                               // the block's last chunk
+                for (uint32_t j = threadIdx.x; j < n; j += kReplicaThreads) dst[j] = src[j];
                 continue;
             }
             u32x4_t v[kPushLoads];
 #pragma unroll
-            for (int j = 0; j < kPushLoads; ++j) v[j] = src[threadIdx.x + j * kReplicaThreads];
+            for (int j = 0; j < kPushLoads; ++j) v[j] = scalar_base(src + j * kReplicaThreads)[threadIdx.x];
 #pragma unroll
-            for (int j = 0; j < kPushLoads; ++j) dst[threadIdx.x + j * kReplicaThreads] = v[j];
+            for (int j = 0; j < kPushLoads; ++j) scalar_base(dst + j * kReplicaThreads)[threadIdx.x] = v[j];
         }
     }
     if (bad && blockIdx.x == 0) atomicOr(err_flag, RELIBRA_ERR_ID_RANGE);
 }
 
 // Gradient return: for every live slot s (replica_expert[s] = e >= 0), in ascending slot order,
-// dW[e] += dW[E + s], for the three gradient tensors (per_expert_vec f32x4_t vectors each).  An
+// dW[e] += dW[E + s], for the three gradient tensors (vec f32x4_t vectors each).  An
 // expert's slots are added up in registers, its home block is read and written once.  The workgroup
 // that owns a chunk of an expert's block depends on the expert and the chunk only, not on the place in
 // the list, and a thread owns its elements inside the chunk: every element's sum has the same fixed
 // order as the in-line sum of the backward call, also across lists; results are identical bit for bit.
-__global__ void __launch_bounds__(kReplicaThreads)
+__global__ void __launch_bounds__(kReplicaThreads, kReplicaWaves)
 replica_pull_kernel(f32x4_t *__restrict__ dWg, f32x4_t *__restrict__ dWu, f32x4_t *__restrict__ dWd,
-                    const int32_t *__restrict__ replica_expert, int n_slots, int E, size_t per_expert_vec,
+                    const int32_t *__restrict__ replica_expert, int n_slots, int E, uint32_t vec,
                     int32_t *__restrict__ err_flag)
 {
     __shared__ LiveSlots l;
-    constexpr size_t CHUNK = (size_t)kReplicaThreads * kPullLoads;
-    const size_t chunks = (per_expert_vec + CHUNK - 1) / CHUNK, units = 3 * chunks;      // per expert
+    constexpr uint32_t CHUNK = kReplicaThreads * kPullLoads;
+    const uint32_t chunks = (vec + CHUNK - 1) / CHUNK, units = 3 * chunks;      // per expert
     bool bad = false;
     for (int base = 0; base < n_slots; base += kTableChunk) {
         list_live(replica_expert, base, n_slots, E, l, bad);
@@ -121,34 +148,38 @@ replica_pull_kernel(f32x4_t *__restrict__ dWg, f32x4_t *__restrict__ dWu, f32x4_
             l.next[threadIdx.x] = next;
         }
         __syncthreads();
-        for (int i = 0; i < l.n; ++i) {
-            if (!l.head[i]) continue;
-            const int e = l.expert[i];
-            const size_t turn = (size_t)e * units % gridDim.x;       // unit c of expert e belongs to workgroup (turn + c) % grid
-            for (size_t c = (blockIdx.x + gridDim.x - turn) % gridDim.x; c < units; c += gridDim.x) {
-                const size_t which = c / chunks;
+        const int live = uniform(l.n);
+        for (int i = 0; i < live; ++i) {
+            if (!uniform(l.head[i])) continue;
+            const int e = uniform(l.expert[i]);
+            const uint32_t turn = (uint32_t)e % gridDim.x * (units % gridDim.x) % gridDim.x;       // unit c of expert e belongs to workgroup (turn + c) % grid
+            for (uint32_t c = (blockIdx.x + gridDim.x - turn) % gridDim.x; c < units; c += gridDim.x) {
+                const uint32_t which = c / chunks;
                 f32x4_t *__restrict__ dW = which == 0 ? dWg : which == 1 ? dWu : dWd;
-                const size_t at = (c - which * chunks) * CHUNK;
-                const int n = (int)min(CHUNK, per_expert_vec - at);
-                f32x4_t *__restrict__ home = dW + (size_t)e * per_expert_vec + at;
-                int idx[kPullLoads];
-                f32x4_t d[kPullLoads];
+                const uint32_t at = (c - which * chunks) * CHUNK, n = vec - at;      // vectors from here to the block's end
+                f32x4_t *home = dW + (size_t)e * vec + at;
+                auto pull = [&](auto whole) __attribute__((always_inline)) {
+                    // past the block's end: its last vector again, not stored
+                    auto lane_at = [&](auto *p, int j) __attribute__((always_inline)) {
+                        return scalar_base(decltype(whole)::value ? p + j * kReplicaThreads : p) + (decltype(whole)::value ? threadIdx.x : min(j * kReplicaThreads + threadIdx.x, n - 1));
+                    };
+                    f32x4_t d[kPullLoads];
 #pragma unroll
-                for (int j = 0; j < kPullLoads; ++j) {     // past the end: the last vector again, not stored
-                    idx[j] = min((int)threadIdx.x + j * kReplicaThreads, n - 1);
-                    d[j] = home[idx[j]];
-                }
-                for (int k = i; k >= 0; k = l.next[k]) {
-                    const f32x4_t *__restrict__ src = dW + (size_t)(E + l.slot[k]) * per_expert_vec + at;
-                    f32x4_t v[kPullLoads];
+                    for (int j = 0; j < kPullLoads; ++j) d[j] = *lane_at(home, j);
+                    for (int k = i; k >= 0; k = uniform(l.next[k])) {
+                        const f32x4_t *src = dW + (size_t)(E + uniform(l.slot[k])) * vec + at;
+                        f32x4_t v[kPullLoads];
 #pragma unroll
-                    for (int j = 0; j < kPullLoads; ++j) v[j] = src[idx[j]];
+                        for (int j = 0; j < kPullLoads; ++j) v[j] = *lane_at(src, j);
 #pragma unroll
-                    for (int j = 0; j < kPullLoads; ++j) d[j] += v[j];
-                }
+                        for (int j = 0; j < kPullLoads; ++j) d[j] += v[j];
+                    }
 #pragma unroll
-                for (int j = 0; j < kPullLoads; ++j)
-                    if ((int)threadIdx.x + j * kReplicaThreads < n) home[idx[j]] = d[j];
+                    for (int j = 0; j < kPullLoads; ++j)
+                        if (decltype(whole)::value || j * kReplicaThreads + threadIdx.x < n) *lane_at(home, j) = d[j];
+                };
+                if (n >= CHUNK) pull(std::true_type{});
+                else pull(std::false_type{});
             }
         }
     }
@@ -169,10 +200,12 @@ extern "C" int relibra_replica_push(void *Wg_dev, void *Wu_dev, void *Wd_dev,
     if (r == 0) return RELIBRA_OK;
     if (!Wg_dev || !Wu_dev || !Wd_dev || !replica_expert_dev || !err_flag_dev) return RELIBRA_EINVAL;
     if (!aligned16(Wg_dev) || !aligned16(Wu_dev) || !aligned16(Wd_dev)) return RELIBRA_EINVAL;
-    const size_t per_expert_vec = (size_t)h * hff / 8;
+    const size_t per_expert = (size_t)h * hff / 8;
+    if (per_expert > kMaxVec) return RELIBRA_EUNSUPPORTED;
+    const uint32_t vec = (uint32_t)per_expert;
     const int grid = n_workgroups > 4096 ? 4096 : n_workgroups;
     RELIBRA_LAUNCH(RELIBRA_K_REPLICA_PUSH, stream, replica_push_kernel<<<grid, kReplicaThreads, 0, stream>>>(
-        (u32x4_t *)Wg_dev, (u32x4_t *)Wu_dev, (u32x4_t *)Wd_dev, replica_expert_dev, EP * r, E, per_expert_vec, err_flag_dev));
+        (u32x4_t *)Wg_dev, (u32x4_t *)Wu_dev, (u32x4_t *)Wd_dev, replica_expert_dev, EP * r, E, vec, err_flag_dev));
     RELIBRA_HIP_TRY(launch_check());
     return RELIBRA_OK;
 }
@@ -187,10 +220,12 @@ extern "C" int relibra_replica_pull(float *dWg_dev, float *dWu_dev, float *dWd_d
     if (r == 0) return RELIBRA_OK;
     if (!dWg_dev || !dWu_dev || !dWd_dev || !replica_expert_dev || !err_flag_dev) return RELIBRA_EINVAL;
     if (!aligned16(dWg_dev) || !aligned16(dWu_dev) || !aligned16(dWd_dev)) return RELIBRA_EINVAL;
-    const size_t per_expert_vec = (size_t)h * hff / 4;
+    const size_t per_expert = (size_t)h * hff / 4;
+    if (per_expert > kMaxVec) return RELIBRA_EUNSUPPORTED;
+    const uint32_t vec = (uint32_t)per_expert;
     const int grid = n_workgroups > 4096 ? 4096 : n_workgroups;
     RELIBRA_LAUNCH(RELIBRA_K_REPLICA_PULL, stream, replica_pull_kernel<<<grid, kReplicaThreads, 0, stream>>>(
-        (f32x4_t *)dWg_dev, (f32x4_t *)dWu_dev, (f32x4_t *)dWd_dev, replica_expert_dev, EP * r, E, per_expert_vec, err_flag_dev));
+        (f32x4_t *)dWg_dev, (f32x4_t *)dWu_dev, (f32x4_t *)dWd_dev, replica_expert_dev, EP * r, E, vec, err_flag_dev));
     RELIBRA_HIP_TRY(launch_check());
     return RELIBRA_OK;
 }

@@ -41,6 +41,17 @@ def test_build_refuses_a_kernel_that_needs_scratch_memory(tmp_path):
         build.compile_source(str(spills), str(tmp_path / "spills.o"))
 
 
+def test_replica_workgroups_fit_next_to_a_narrow_row_tile_workgroup(tmp_path):
+    """A SIMD has 512 registers and a unit 160 KiB of LDS; one narrow row-tile workgroup leaves 280 and 88 KiB.  A
+    replica workgroup that needs more starts only on an empty unit, which a queue of narrow tiles never leaves."""
+    from paper_2605_08639_amd import build
+    usage = build.compile_source(os.path.join(build.CSRC, "replica_kernels.hip"), str(tmp_path / "replica.o"))
+    threads = int(re.search(r"kReplicaThreads = (\d+);", open(os.path.join(build.CSRC, "replica_kernels.hip")).read())[1])
+    assert len(usage) == 2
+    for kernel in usage.values():
+        assert (kernel["VGPRs"] + 7) // 8 * 8 * threads // 256 <= 280 and kernel["LDS Size"] <= 88 << 10
+
+
 def _counts(cfg):
     ids = np.stack([wl.make_routing(cfg, mb)[0] for mb in range(cfg.n_mb)])
     return oracle.route_hist(ids, cfg.E)[0]
