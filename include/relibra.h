@@ -42,7 +42,8 @@ enum {
     RELIBRA_ERANGE = -2,      /* a host table holds a value outside its range             */
     RELIBRA_EWORKSPACE = -3,  /* workspace_bytes is below relibra_workspace_bytes(...)    */
     RELIBRA_EHIP = -4,        /* a HIP runtime call failed                                */
-    RELIBRA_EUNSUPPORTED = -5 /* shape outside what the kernels are built for             */
+    RELIBRA_EUNSUPPORTED = -5, /* shape outside what the kernels are built for            */
+    RELIBRA_ENOMEM = -6       /* a host entry point found no memory; its outputs are undefined */
 };
 
 /* bits OR-ed into *err_flag_dev by kernels */

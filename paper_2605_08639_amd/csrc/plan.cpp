@@ -9,20 +9,22 @@
 //
 // All arithmetic is integer; every choice has a fixed tie-break, so the plan is a pure
 // function of the histograms.
-#include "../../include/relibra.h"
+#include "host.h"
 
 #include <algorithm>
 #include <atomic>
 #include <condition_variable>
 #include <cstdint>
 #include <cstring>
-#include <exception>
 #include <iterator>
 #include <mutex>
+#include <new>
 #include <numeric>
-#include <system_error>
 #include <thread>
 #include <vector>
+
+using relibra::entry;
+using relibra::run_workers;
 
 namespace {
 
@@ -347,31 +349,6 @@ int workers_for(int tasks, double us)
     return std::max(1, std::min({want, (int)(hw ? hw : 1u), tasks, 16}));
 }
 
-// Runs fn on `workers` threads, the calling one among them.  An exception of a worker (std::bad_alloc) is
-// handed to the caller after all threads have ended.
-template <class Fn> void run_workers(int workers, const Fn &fn)
-{
-    std::exception_ptr failed;
-    std::mutex m;
-    auto guarded = [&]() {
-        try {
-            fn();
-        } catch (...) {
-            std::lock_guard<std::mutex> lock(m);
-            failed = std::current_exception();
-        }
-    };
-    std::vector<std::thread> pool;
-    pool.reserve(workers);
-    try {
-        for (int w = 1; w < workers; ++w) pool.emplace_back(guarded);
-    } catch (const std::system_error &) {      // no more threads to be had: the ones there are share the work
-    }
-    guarded();
-    for (auto &t : pool) t.join();
-    if (failed) std::rethrow_exception(failed);
-}
-
 // A count that workers wait for, asleep, until it has come down to zero.
 class Latch {
 public:
@@ -458,8 +435,9 @@ struct TimedState {
         y.resize(cells);
         ybase.resize(cells);
         double out3[3] = {0, 0, 0};
-        relibra_assign_sources(x, E, EP, rpn, ptr.data(), rank.data(), rows.data(), first.data(), y.data(), ybase.data());
-        relibra_moe_time_split(y.data(), (int)rank.size(), rank.data(), model, out3, loads.data());
+        if (relibra_assign_sources(x, E, EP, rpn, ptr.data(), rank.data(), rows.data(), first.data(), y.data(), ybase.data()) ||
+            relibra_moe_time_split(y.data(), (int)rank.size(), rank.data(), model, out3, loads.data()))
+            throw std::bad_alloc();            // the tables are consistent: nothing else can have failed
         const int64_t *comp = loads.data(), *itx = comp + EP, *irx = comp + 2 * EP, *rtx = comp + 3 * EP, *rrx = comp + 4 * EP;
         for (int g = 0; g < EP; ++g) {
             const double intra = model->sec_per_token_intra * (double)std::max(itx[g], irx[g]);
@@ -718,8 +696,10 @@ extern "C" int relibra_plan(const int32_t *counts, int n_mb, int E, int k, int E
                             int32_t *group_expert, int32_t *group_offset, int32_t *group_dw_slot,
                             int64_t *max_load_before, int64_t *max_load_after)
 {
-    return plan_impl(counts, n_mb, E, k, EP, rpn, r, nullptr, expert_to_slot, replica_expert, inst_ptr, inst_rank,
-                     inst_rows, inst_group, group_expert, group_offset, group_dw_slot, max_load_before, max_load_after);
+    return entry([&]() {
+        return plan_impl(counts, n_mb, E, k, EP, rpn, r, nullptr, expert_to_slot, replica_expert, inst_ptr, inst_rank,
+                         inst_rows, inst_group, group_expert, group_offset, group_dw_slot, max_load_before, max_load_after);
+    });
 }
 
 extern "C" int relibra_plan_placed(const int32_t *counts, int n_mb, int E, int k, int EP, int rpn, int r,
@@ -730,16 +710,18 @@ extern "C" int relibra_plan_placed(const int32_t *counts, int n_mb, int E, int k
                                    int64_t *max_load_before, int64_t *max_load_after)
 {
     if (!expert_rank) return RELIBRA_EINVAL;
-    return plan_impl(counts, n_mb, E, k, EP, rpn, r, expert_rank, expert_to_slot, replica_expert, inst_ptr, inst_rank,
-                     inst_rows, inst_group, group_expert, group_offset, group_dw_slot, max_load_before, max_load_after);
+    return entry([&]() {
+        return plan_impl(counts, n_mb, E, k, EP, rpn, r, expert_rank, expert_to_slot, replica_expert, inst_ptr, inst_rank,
+                         inst_rows, inst_group, group_expert, group_offset, group_dw_slot, max_load_before, max_load_after);
+    });
 }
 
-extern "C" int relibra_plan_timed(const int64_t *x_host, int n_mb, int E, int k, const relibra_cost_model *model, int r,
-                                  const int32_t *expert_rank,
-                                  int32_t *expert_to_slot, int32_t *replica_expert,
-                                  int32_t *inst_ptr, int32_t *inst_rank, int32_t *inst_rows, int32_t *inst_group,
-                                  int32_t *group_expert, int32_t *group_offset, int32_t *group_dw_slot,
-                                  int64_t *max_load_before, int64_t *max_load_after, double *t_before, double *t_after)
+static int plan_timed_body(const int64_t *x_host, int n_mb, int E, int k, const relibra_cost_model *model, int r,
+                           const int32_t *expert_rank,
+                           int32_t *expert_to_slot, int32_t *replica_expert,
+                           int32_t *inst_ptr, int32_t *inst_rank, int32_t *inst_rows, int32_t *inst_group,
+                           int32_t *group_expert, int32_t *group_offset, int32_t *group_dw_slot,
+                           int64_t *max_load_before, int64_t *max_load_after, double *t_before, double *t_after)
 {
     if (!x_host || !model || !expert_rank || !expert_to_slot || !inst_ptr || !inst_rank || !inst_rows || !inst_group ||
         !group_expert || !group_offset || !group_dw_slot || !max_load_before || !max_load_after || !t_before || !t_after)
@@ -768,25 +750,34 @@ extern "C" int relibra_plan_timed(const int64_t *x_host, int n_mb, int E, int k,
             counts[(size_t)mb * E + e] = (int32_t)tokens;
         }
     std::vector<MbPlan> plans(n_mb);
-    {
-        unsigned hw = std::thread::hardware_concurrency();
-        const int workers = std::max(1, std::min({(int)(hw ? hw : 1u), n_mb, 16}));
-        std::vector<std::thread> pool;
-        for (int w = 0; w < workers; ++w)
-            pool.emplace_back([&, w]() {
-                for (int mb = w; mb < n_mb; mb += workers)
-                    plans[mb] = replicate_microbatch_timed(x_host + (size_t)mb * EP * E, model, where, E, r, t_before[mb], t_after[mb]);
-            });
-        for (auto &t : pool) t.join();
-    }
+    std::atomic<int> next{0};
+    const unsigned hw = std::thread::hardware_concurrency();
+    run_workers(std::max(1, std::min({(int)(hw ? hw : 1u), n_mb, 16})), [&]() {
+        for (int mb; (mb = next.fetch_add(1)) < n_mb;)
+            plans[mb] = replicate_microbatch_timed(x_host + (size_t)mb * EP * E, model, where, E, r, t_before[mb], t_after[mb]);
+    });
     write_tables(counts.data(), n_mb, E, EP, r, where, plans, expert_to_slot, replica_expert, inst_ptr, inst_rank, inst_rows,
                  inst_group, group_expert, group_offset, group_dw_slot, max_load_before, max_load_after);
     return RELIBRA_OK;
 }
 
+extern "C" int relibra_plan_timed(const int64_t *x_host, int n_mb, int E, int k, const relibra_cost_model *model, int r,
+                                  const int32_t *expert_rank,
+                                  int32_t *expert_to_slot, int32_t *replica_expert,
+                                  int32_t *inst_ptr, int32_t *inst_rank, int32_t *inst_rows, int32_t *inst_group,
+                                  int32_t *group_expert, int32_t *group_offset, int32_t *group_dw_slot,
+                                  int64_t *max_load_before, int64_t *max_load_after, double *t_before, double *t_after)
+{
+    return entry([&]() {
+        return plan_timed_body(x_host, n_mb, E, k, model, r, expert_rank, expert_to_slot, replica_expert, inst_ptr,
+                               inst_rank, inst_rows, inst_group, group_expert, group_offset, group_dw_slot, max_load_before,
+                               max_load_after, t_before, t_after);
+    });
+}
+
 // Imbalance diagnostics of Section 2.2.
-extern "C" int relibra_load_stats(const int32_t *counts, int n_mb, int E, int top,
-                                  double *skewness, double *intersection)
+static int load_stats_body(const int32_t *counts, int n_mb, int E, int top,
+                           double *skewness, double *intersection)
 {
     if (!counts || !skewness || n_mb < 1 || E < 1 || top < 1 || top > E) return RELIBRA_EINVAL;
     if (n_mb > 1 && !intersection) return RELIBRA_EINVAL;
@@ -812,4 +803,10 @@ extern "C" int relibra_load_stats(const int32_t *counts, int n_mb, int E, int to
         intersection[mb] = (double)both.size() / top;
     }
     return RELIBRA_OK;
+}
+
+extern "C" int relibra_load_stats(const int32_t *counts, int n_mb, int E, int top,
+                                  double *skewness, double *intersection)
+{
+    return entry([&]() { return load_stats_body(counts, n_mb, E, top, skewness, intersection); });
 }

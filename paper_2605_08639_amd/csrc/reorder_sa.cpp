@@ -13,14 +13,18 @@
 // exponent has the opposite sign and would accept every worsening move); times are divided by
 // the starting state's exact T_MoE before smoothing so that beta = 20 acts on numbers of order
 // one; the random draws come from splitmix64, three per iteration (e_a, e_b, u).
-#include "../../include/relibra.h"
+#include "host.h"
 
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <cstdint>
 #include <numeric>
 #include <thread>
 #include <vector>
+
+using relibra::entry;
+using relibra::run_workers;
 
 namespace {
 
@@ -220,9 +224,9 @@ Problem make_problem(const int64_t *x, int E, const relibra_cost_model *m, doubl
 
 }  // namespace
 
-extern "C" int relibra_moe_time(const int64_t *x_host, int E, const relibra_cost_model *model,
-                                const int32_t *expert_rank, double beta, double t_ref,
-                                double *out4, int64_t *loads_out)
+static int moe_time_body(const int64_t *x_host, int E, const relibra_cost_model *model,
+                         const int32_t *expert_rank, double beta, double t_ref,
+                         double *out4, int64_t *loads_out)
 {
     if (int rc = check_model(x_host, E, model)) return rc;
     if (!expert_rank || !out4 || !(beta > 0.0) || !(t_ref > 0.0)) return RELIBRA_EINVAL;
@@ -242,6 +246,13 @@ extern "C" int relibra_moe_time(const int64_t *x_host, int E, const relibra_cost
             for (int g = 0; g < P.EP; ++g) loads_out[(size_t)i * P.EP + g] = (*rows[i])[g];
     }
     return RELIBRA_OK;
+}
+
+extern "C" int relibra_moe_time(const int64_t *x_host, int E, const relibra_cost_model *model,
+                                const int32_t *expert_rank, double beta, double t_ref,
+                                double *out4, int64_t *loads_out)
+{
+    return entry([&]() { return moe_time_body(x_host, E, model, expert_rank, beta, t_ref, out4, loads_out); });
 }
 
 extern "C" int relibra_cost_model_init(relibra_cost_model *model, int EP, int ranks_per_node, int h, int hff,
@@ -284,10 +295,10 @@ SaStart sa_start(Problem &P)
 
 }  // namespace
 
-extern "C" long long relibra_reorder_sa_trace(const int64_t *x_host, int E, const relibra_cost_model *model,
-                                              double beta, double gamma, double eps, uint64_t seed,
-                                              int trace_cap, int32_t *moves_out, double *vals_out,
-                                              int32_t *start_rank_out, int32_t *expert_rank_out, double *stats2)
+static long long reorder_sa_trace_body(const int64_t *x_host, int E, const relibra_cost_model *model,
+                                       double beta, double gamma, double eps, uint64_t seed,
+                                       int trace_cap, int32_t *moves_out, double *vals_out,
+                                       int32_t *start_rank_out, int32_t *expert_rank_out, double *stats2)
 {
     if (int rc = check_model(x_host, E, model)) return rc;
     if (!expert_rank_out || !start_rank_out || !stats2 || !(beta > 0.0) || !(gamma > 0.0 && gamma < 1.0) || !(eps > 0.0) ||
@@ -305,9 +316,20 @@ extern "C" long long relibra_reorder_sa_trace(const int64_t *x_host, int E, cons
     return res.iterations;
 }
 
-extern "C" int relibra_reorder_sa(const int64_t *x_host, int E, const relibra_cost_model *model,
-                                  double beta, double gamma, double eps, int n_seeds, uint64_t seed,
-                                  int32_t *expert_rank_out, double *stats5)
+extern "C" long long relibra_reorder_sa_trace(const int64_t *x_host, int E, const relibra_cost_model *model,
+                                              double beta, double gamma, double eps, uint64_t seed,
+                                              int trace_cap, int32_t *moves_out, double *vals_out,
+                                              int32_t *start_rank_out, int32_t *expert_rank_out, double *stats2)
+{
+    return entry([&]() {
+        return reorder_sa_trace_body(x_host, E, model, beta, gamma, eps, seed, trace_cap, moves_out, vals_out,
+                                     start_rank_out, expert_rank_out, stats2);
+    });
+}
+
+static int reorder_sa_body(const int64_t *x_host, int E, const relibra_cost_model *model,
+                           double beta, double gamma, double eps, int n_seeds, uint64_t seed,
+                           int32_t *expert_rank_out, double *stats5)
 {
     if (int rc = check_model(x_host, E, model)) return rc;
     if (!expert_rank_out || !stats5 || !(beta > 0.0) || !(gamma > 0.0 && gamma < 1.0) || !(eps > 0.0) ||
@@ -322,19 +344,12 @@ extern "C" int relibra_reorder_sa(const int64_t *x_host, int E, const relibra_co
     (void)EP;
 
     std::vector<SeedResult> results(n_seeds);
-    unsigned hw = std::thread::hardware_concurrency();
-    const int workers = std::max(1, std::min<int>({n_seeds, (int)(hw ? hw : 1u), 64}));
-    auto work = [&](int w) {
-        for (int s = w; s < n_seeds; s += workers)
+    std::atomic<int> next{0};
+    const unsigned hw = std::thread::hardware_concurrency();
+    run_workers(std::max(1, std::min<int>({n_seeds, (int)(hw ? hw : 1u), 64})), [&]() {
+        for (int s; (s = next.fetch_add(1)) < n_seeds;)
             results[s] = anneal(P, start, smooth0, gamma, eps, seed + (uint64_t)s * 0xD1342543DE82EF95ull);
-    };
-    if (workers == 1) {
-        work(0);
-    } else {
-        std::vector<std::thread> pool;
-        for (int w = 0; w < workers; ++w) pool.emplace_back(work, w);
-        for (auto &t : pool) t.join();
-    }
+    });
     int best = 0;
     for (int s = 1; s < n_seeds; ++s)
         if (results[s].exact_T < results[best].exact_T) best = s;
@@ -345,4 +360,11 @@ extern "C" int relibra_reorder_sa(const int64_t *x_host, int E, const relibra_co
     stats5[3] = results[best].smooth_T;
     stats5[4] = (double)results[n_seeds - 1].iterations;
     return RELIBRA_OK;
+}
+
+extern "C" int relibra_reorder_sa(const int64_t *x_host, int E, const relibra_cost_model *model,
+                                  double beta, double gamma, double eps, int n_seeds, uint64_t seed,
+                                  int32_t *expert_rank_out, double *stats5)
+{
+    return entry([&]() { return reorder_sa_body(x_host, E, model, beta, gamma, eps, n_seeds, seed, expert_rank_out, stats5); });
 }

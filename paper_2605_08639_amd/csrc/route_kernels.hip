@@ -697,6 +697,7 @@ extern "C" const char *relibra_status_string(int status)
     case RELIBRA_EWORKSPACE: return "workspace too small";
     case RELIBRA_EHIP: return "HIP runtime error";
     case RELIBRA_EUNSUPPORTED: return "unsupported shape";
+    case RELIBRA_ENOMEM: return "out of host memory";
     default: return "unknown status";
     }
 }

@@ -11,11 +11,13 @@
 // and only the remainder is dealt out in source order.  Because the cheap sources of different
 // instances do not overlap, this reaches the smallest intra-node volume any split with the same
 // instance sizes can have.
-#include "../../include/relibra.h"
+#include "host.h"
 
 #include <algorithm>
 #include <cstdint>
 #include <vector>
+
+using relibra::entry;
 
 namespace {
 
@@ -38,9 +40,9 @@ bool model_ok(const relibra_cost_model *m)
 
 }  // namespace
 
-extern "C" int relibra_assign_sources(const int64_t *x_host, int E, int EP, int ranks_per_node,
-                                      const int32_t *inst_ptr, const int32_t *inst_rank, const int32_t *inst_rows,
-                                      int32_t *src_first, int32_t *inst_src_rows, int32_t *inst_src_base)
+static int assign_sources_body(const int64_t *x_host, int E, int EP, int ranks_per_node,
+                               const int32_t *inst_ptr, const int32_t *inst_rank, const int32_t *inst_rows,
+                               int32_t *src_first, int32_t *inst_src_rows, int32_t *inst_src_base)
 {
     if (E < 1 || EP < 1 || ranks_per_node < 1 || EP % ranks_per_node) return RELIBRA_EINVAL;
     if (!x_host || !inst_ptr || !inst_rank || !inst_rows || !src_first || !inst_src_rows || !inst_src_base)
@@ -89,8 +91,18 @@ extern "C" int relibra_assign_sources(const int64_t *x_host, int E, int EP, int 
     return RELIBRA_OK;
 }
 
-extern "C" int relibra_moe_time_split(const int32_t *inst_src_rows, int n_inst, const int32_t *inst_rank,
-                                      const relibra_cost_model *model, double *out3, int64_t *loads_out)
+extern "C" int relibra_assign_sources(const int64_t *x_host, int E, int EP, int ranks_per_node,
+                                      const int32_t *inst_ptr, const int32_t *inst_rank, const int32_t *inst_rows,
+                                      int32_t *src_first, int32_t *inst_src_rows, int32_t *inst_src_base)
+{
+    return entry([&]() {
+        return assign_sources_body(x_host, E, EP, ranks_per_node, inst_ptr, inst_rank, inst_rows, src_first, inst_src_rows,
+                                   inst_src_base);
+    });
+}
+
+static int moe_time_split_body(const int32_t *inst_src_rows, int n_inst, const int32_t *inst_rank,
+                               const relibra_cost_model *model, double *out3, int64_t *loads_out)
 {
     if (!model_ok(model) || n_inst < 0 || !out3 || (n_inst > 0 && (!inst_src_rows || !inst_rank))) return RELIBRA_EINVAL;
     const int EP = model->EP;
@@ -121,4 +133,10 @@ extern "C" int relibra_moe_time_split(const int32_t *inst_src_rows, int n_inst, 
     out3[2] = t_comm;
     if (loads_out) std::copy(load.begin(), load.end(), loads_out);
     return RELIBRA_OK;
+}
+
+extern "C" int relibra_moe_time_split(const int32_t *inst_src_rows, int n_inst, const int32_t *inst_rank,
+                                      const relibra_cost_model *model, double *out3, int64_t *loads_out)
+{
+    return entry([&]() { return moe_time_split_body(inst_src_rows, n_inst, inst_rank, model, out3, loads_out); });
 }

@@ -4,6 +4,8 @@ No kernel is launched here."""
 import ctypes
 import os
 import re
+import subprocess
+import sys
 import threading
 import time
 
@@ -160,6 +162,39 @@ def test_replication_without_free_slots_looks_at_every_expert_once():
     assert np.array_equal(rl.relibra_plan(counts, 2, 2, 2, 1, expert_rank=rank)["inst_rows"], oracle.plan(counts, 2, 2, 1, placed=rank)["inst_rows"])
     none, one = (min(_seconds(lambda: rl.relibra_plan(counts, 2, 2, 2, r, expert_rank=rank)) for _ in range(3)) for r in (0, 1))
     assert none < 10 * one
+
+
+_SHORT_OF_MEMORY = """
+import ctypes, os, resource, sys
+import numpy as np
+import paper_2605_08639_amd as rl
+L, hp = rl.lib(), lambda a: a.ctypes.data_as(ctypes.c_void_p)
+E, EP, n_mb = 64, 16, 16
+rng = np.random.default_rng(1)
+x = rng.integers(0, 200, size=(n_mb, EP, E)).astype(np.int64)
+counts, model = x.sum(1).astype(np.int32), rl.cost_model(EP, 8, 2048, 768, 5e14, 1e12, 5e10)
+rank = np.repeat(np.arange(EP, dtype=np.int32), E // EP)
+plans = [lambda: rl.relibra_plan(counts, 8, EP, 8, 2), lambda: rl.relibra_plan_timed(x, 8, model, 2, rank)]
+want = [p() for p in plans]
+# one call whose vectors are far larger than what is left
+big = 1 << 22
+c1, o1 = np.ones((1, big), np.int32), [np.zeros(n, t) for n, t in ((big, np.int32), (1, np.int32), (big + 1, np.int32), (big, np.int32),
+       (big, np.int32), (big, np.int32), (big, np.int32), (big + 1, np.int32), (big, np.int32), (1, np.int64), (1, np.int64))]
+used = int(open("/proc/self/statm").read().split()[0]) * os.sysconf("SC_PAGE_SIZE")
+resource.setrlimit(resource.RLIMIT_AS, (used + (4 << 20), used + (4 << 20)))
+status = L.relibra_plan(hp(c1), 1, big, 1, 1, 1, 0, *[hp(o) for o in o1])
+assert status == rl.ENOMEM, status
+# no room for the stack of a thread: the plans are made all the same
+got = [p() for p in plans]
+for w, g in zip(want, got):
+    assert all(np.array_equal(w[key], g[key]) for key in w)
+print("done")
+"""
+
+
+def test_host_entries_short_of_memory_return_and_do_not_abort():
+    run = subprocess.run([sys.executable, "-c", _SHORT_OF_MEMORY], capture_output=True, text=True, cwd=ROOT, timeout=120)
+    assert run.returncode == 0 and run.stdout.strip() == "done", run.stderr[-2000:]
 
 
 def _seconds(fn):
