@@ -28,7 +28,7 @@ PEAK_BF16_TFLOPS = 2500.0     # MI355X dense bf16 MFMA
 PEAK_HBM_GBS = 8000.0
 
 GEMM_FLOP_FACTOR = {"fwd_gate_up": 4, "fwd_down": 2, "bwd_act": 2, "bwd_dx": 4, "wgrad_down": 2,
-                    "wgrad_gate_up": 4}          # x h*h'*N per launch (2hh' per row per GEMM, Eq. 4)
+                    "wgrad_gate_up": 4, "wgrad_pair": 6}          # x h*h'*N per launch (2hh' per row per GEMM, Eq. 4)
 TABLES = ("inst_ptr", "inst_rows", "inst_group", "group_offset", "group_expert", "group_dw_slot")
 
 
@@ -232,6 +232,8 @@ def run_config(args, config_index, steps, warmup, extras_level, cpu_seconds):
     # a group's weights once per live group, weight gradients written per live group and, when
     # accumulating, the home slots read first.  Averaged over the micro-batches of the step.
     def alg_bytes(name):
+        if name == "wgrad_pair":                 # both weight gradients in one launch
+            return alg_bytes("wgrad_down") + alg_bytes("wgrad_gate_up")
         w1 = 2.0 * h * hff                       # one bf16 weight matrix
         act_h, act_ff = 2.0 * h * N, 2.0 * hff * N
         act_x = 2.0 * h * T + 4.0 * N if fused_gather else act_h      # the layer's input rows: tokens + row table, or the gathered copy
@@ -321,6 +323,7 @@ def run_config(args, config_index, steps, warmup, extras_level, cpu_seconds):
             "perm_count": 8.0 * N + 4.0 * n_units * E,
             "perm_scan": 8.0 * n_units * E,
             "perm_rank": 12.0 * N + 4.0 * n_units * E,
+            "perm_small": 12.0 * N,
             "row_tokens": 8.0 * N,
             "row_gates": 12.0 * N,
             "dgate_reduce": 4.0 * parts * N + 8.0 * N,

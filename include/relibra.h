@@ -581,7 +581,10 @@ int relibra_unpermute_combine(int mode, const void *rows_dev, const void *tok_de
 /*
  * Per-kernel timing for benchmarks (not part of the method).  Between relibra_prof_start and
  * relibra_prof_stop every kernel launch of the chosen level is bracketed by two HIP events on
- * its launch stream: level 1 = the six grouped-GEMM kernels, level 2 = every kernel, 0 = off.
+ * its launch stream: level 1 = the grouped-GEMM kernels, level 2 = every kernel, 0 = off.
+ * Calls of few tiles do both weight gradients in one launch, recorded as RELIBRA_K_WGRAD_PAIR instead of
+ * _WGRAD_DOWN and _WGRAD_GATE_UP; small permutations run as one kernel, RELIBRA_K_PERM_SMALL instead of
+ * _PERM_COUNT, _SCAN and _RANK.
  * At most max_records launches are recorded (events are created in relibra_prof_start, host
  * side only).  relibra_prof_stop waits for the recorded events and returns, per kernel id
  * (RELIBRA_K_*), the summed milliseconds and the launch count in two host arrays of
@@ -593,7 +596,7 @@ enum {
     RELIBRA_K_FWD_GATE_UP, RELIBRA_K_FWD_DOWN, RELIBRA_K_BWD_ACT, RELIBRA_K_BWD_DX,
     RELIBRA_K_WGRAD_DOWN, RELIBRA_K_WGRAD_GATE_UP, RELIBRA_K_REPLICA_SUM, RELIBRA_K_REPLICA_PUSH,
     RELIBRA_K_WGRAD_ORDER, RELIBRA_K_TRANSPOSE, RELIBRA_K_ROW_TOKENS, RELIBRA_K_ROW_GATES, RELIBRA_K_DGATE_REDUCE,
-    RELIBRA_K_REPLICA_PULL, RELIBRA_K_COUNT
+    RELIBRA_K_REPLICA_PULL, RELIBRA_K_WGRAD_PAIR, RELIBRA_K_PERM_SMALL, RELIBRA_K_COUNT
 };
 int relibra_prof_start(int level, int max_records);
 int relibra_prof_stop(double *ms_by_kernel_host, int64_t *launches_by_kernel_host);

@@ -37,7 +37,7 @@ EXPORTS = ("relibra_route_hist", "relibra_plan", "relibra_plan_placed", "relibra
 KERNELS = ("hist", "perm_count", "perm_scan", "perm_rank", "gather", "combine_fwd", "combine_bwd",
            "combine_sum", "sched", "fwd_gate_up", "fwd_down", "bwd_act", "bwd_dx", "wgrad_down",
            "wgrad_gate_up", "replica_sum", "replica_push", "wgrad_order", "transpose", "row_tokens", "row_gates",
-           "dgate_reduce", "replica_pull")
+           "dgate_reduce", "replica_pull", "wgrad_pair", "perm_small")
 
 _lib = None
 

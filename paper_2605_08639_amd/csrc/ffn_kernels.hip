@@ -1500,7 +1500,7 @@ static int ffn_bwd_impl(const void *dYrows, const void *Xrows,
         RELIBRA_WGRAD(256, 128);
     } else if (std::max(t_down, t_gu) <= 2 * kComputeUnits) {
         const unsigned blocks_gu = grid8(t_gu);
-        RELIBRA_LAUNCH(RELIBRA_K_WGRAD_GATE_UP, stream, (wgrad_pair_kernel<128><<<blocks_gu + grid8(t_down), THREADS, (WgradCfg<128, true>::LDS), stream>>>(
+        RELIBRA_LAUNCH(RELIBRA_K_WGRAD_PAIR, stream, (wgrad_pair_kernel<128><<<blocks_gu + grid8(t_down), THREADS, (WgradCfg<128, true>::LDS), stream>>>(
             s, (const bf16_t *)dYrows, (const bf16_t *)A_save, (const bf16_t *)Xrows, h, hff, E, accumulate, stream_dw, (int)t_down, (int)t_gu,
             (int)blocks_gu, dWg, dWu, dWd)));
         RELIBRA_HIP_TRY(launch_check());
@@ -1618,9 +1618,9 @@ extern "C" int relibra_moe_ffn_wgrad_batched(const relibra_wgrad_mb *mbs, int n_
     const int stream_dw = streams_dw((size_t)E * h * hff);
     const long long tiles = (long long)E * ((h + 255) / 256 * ((hff + wn_down - 1) / wn_down) + (hff + 127) / 128 * ((h + wn_gu - 1) / wn_gu));
     if (wide_down == wide_gu && tiles <= kComputeUnits) {
-        if (wide_gu) RELIBRA_LAUNCH(RELIBRA_K_WGRAD_GATE_UP, stream, (wgrad_batched_pair_kernel<256, kWideWaves><<<g_gu + g_down, kWideWaves * 64, WgradWide<256>::LDS, stream>>>(
+        if (wide_gu) RELIBRA_LAUNCH(RELIBRA_K_WGRAD_PAIR, stream, (wgrad_batched_pair_kernel<256, kWideWaves><<<g_gu + g_down, kWideWaves * 64, WgradWide<256>::LDS, stream>>>(
             E, h, hff, w, accumulate, stream_dw, (int)g_gu, dWg, dWu, dWd)));
-        else RELIBRA_LAUNCH(RELIBRA_K_WGRAD_GATE_UP, stream, (wgrad_batched_pair_kernel<128><<<g_gu + g_down, THREADS, WgradWide<128>::LDS, stream>>>(
+        else RELIBRA_LAUNCH(RELIBRA_K_WGRAD_PAIR, stream, (wgrad_batched_pair_kernel<128><<<g_gu + g_down, THREADS, WgradWide<128>::LDS, stream>>>(
             E, h, hff, w, accumulate, stream_dw, (int)g_gu, dWg, dWu, dWd)));
         RELIBRA_HIP_TRY(launch_check());
         return RELIBRA_OK;

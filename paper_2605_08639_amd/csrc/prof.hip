@@ -14,7 +14,10 @@ struct ProfState {
 };
 static ProfState g_prof;
 
-static inline int prof_level_of(int id) { return (id >= RELIBRA_K_FWD_GATE_UP && id <= RELIBRA_K_WGRAD_GATE_UP) ? 1 : 2; }
+static inline int prof_level_of(int id)
+{
+    return (id >= RELIBRA_K_FWD_GATE_UP && id <= RELIBRA_K_WGRAD_GATE_UP) || id == RELIBRA_K_WGRAD_PAIR ? 1 : 2;
+}
 
 bool prof_before(int id, hipStream_t s)
 {

@@ -524,7 +524,7 @@ static int permute_impl(const int32_t *ids_dev, const int32_t *inst_ptr_dev, con
     const PlanTables tables{inst_ptr_dev, inst_rows_dev, inst_group_dev, group_offset_dev};
     if (N <= kSmallN && E <= kSmallE) {
         const size_t lds = (size_t)(kSmallWaves + 2) * E * sizeof(int32_t);
-        RELIBRA_LAUNCH(RELIBRA_K_PERM_RANK, stream, perm_small_kernel<<<1, kSmallThreads, lds, stream>>>(ids_dev, N, E, G, ebits, tables,
+        RELIBRA_LAUNCH(RELIBRA_K_PERM_SMALL, stream, perm_small_kernel<<<1, kSmallThreads, lds, stream>>>(ids_dev, N, E, G, ebits, tables,
                                                                 row_of_dev, src_of_dev, err_flag_dev, split));
         RELIBRA_HIP_TRY(launch_check());
     } else {

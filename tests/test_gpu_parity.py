@@ -839,8 +839,11 @@ def test_weight_gradients_of_short_groups(groups):
     go_d, ge_d, W_d, err = dev_i32(go), dev_i32(ge), [W.to(DEV) for W in (Wg, Wu, Wd)], rl.new_err_flag()
     Gt, U, A, _ = rl.relibra_moe_ffn_fwd(X.to(DEV), go_d, ge_d, *W_d, err_flag=err)
     dW = [torch.full((n_slots, *W.shape[1:]), 3.0, dtype=torch.float32, device=DEV) for W in (Wg, Wu, Wd)]
+    rl.prof_start(level=1, max_records=16)
     rl.relibra_moe_ffn_bwd(dY.to(DEV), X.to(DEV), Gt, U, A, go_d, ge_d, dev_i32(slots), *W_d, *dW, err_flag=err, E=3)
+    timed = set(rl.prof_stop())
     assert err.item() == 0
+    assert timed == {"bwd_act", "bwd_dx"} | ({"wgrad_pair"} if groups == 20 else {"wgrad_down", "wgrad_gate_up"})
     for got, want in zip(dW, oracle.ffn_bwd(X, dY, go, ge, Wg, Wu, Wd)[1:]):
         for e in range(3):
             assert rel_l2(got[e], want[e]) <= TOL

@@ -31,6 +31,11 @@ def test_library_exports_every_declared_symbol():
     assert set(rl.EXPORTS) == declared
 
 
+def test_timed_kernels_are_named_as_the_header_lists_them():
+    enum = re.search(r"enum \{\s*(RELIBRA_K_HIST.*?)\};", open(os.path.join(ROOT, "include", "relibra.h")).read(), re.S)[1]
+    assert [n.lower() for n in re.findall(r"RELIBRA_K_(\w+)", enum)] == [*rl.KERNELS, "count"]
+
+
 def test_build_refuses_a_kernel_that_needs_scratch_memory(tmp_path):
     from paper_2605_08639_amd import build
     source = "#include <hip/hip_runtime.h>\n__global__ void spills(float *p, const int *at) { %s }\n"
