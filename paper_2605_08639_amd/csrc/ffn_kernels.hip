@@ -114,11 +114,12 @@ constexpr int kBand = 8;
 constexpr int kMaxSchedGroups = 8192;          // groups of one call (g_end - g_begin)
 
 // One block.  Validates the group tables of [g_begin, g_end) (bad groups become empty and raise
-// the flag), lists the row tiles group by group, and lists the live replica slots.
+// the flag), lists the row tiles group by group, and lists the live replica slots.  The lists hold
+// max_tiles: enough for any table whose groups do not overlap; an overlapping one ends there, flagged.
 __global__ void __launch_bounds__(256)
 sched_kernel(const int32_t *__restrict__ group_offset, const int32_t *__restrict__ group_expert,
              const int32_t *__restrict__ group_dw_slot, int g_begin, int Gr, int n_rows, int E, int n_dw_slots,
-             Sched s, int32_t *err_flag)
+             int max_tiles, Sched s, int32_t *err_flag)
 {
     extern __shared__ int32_t prefix[];        // [Gr + 1] tile_prefix, kept in LDS for the searches below
     __shared__ int32_t sums[4];
@@ -141,12 +142,13 @@ sched_kernel(const int32_t *__restrict__ group_offset, const int32_t *__restrict
             s.grp_rows[i] = hi - lo;
             s.grp_expert[i] = e;
             s.grp_slot[i] = slot;
-            tiles = (hi - lo + BM - 1) / BM;
+            tiles = min((hi - lo + BM - 1) / BM, max_tiles + 1);
         }
         int all;
         const int upto = block_scan256(tiles, sums, all);
-        if (i < Gr) s.tile_prefix[i + 1] = prefix[i + 1] = carry + upto;
-        carry += all;
+        if (tiles > 0 && carry + upto > max_tiles) bad_any = true;
+        if (i < Gr) s.tile_prefix[i + 1] = prefix[i + 1] = min(carry + upto, max_tiles);
+        carry = min(carry + all, max_tiles);
     }
     if (bad_any) atomicOr(err_flag, RELIBRA_ERR_GROUP_TABLE);
     const int total = carry;
@@ -1317,7 +1319,8 @@ static int ffn_fwd_impl(const void *Xrows, const int32_t *row_tok, int T, int n_
     if (ws_bytes < ffn_ws_bytes(n_rows, Gr, hff, false)) return RELIBRA_EWORKSPACE;
     if (int rc = ensure_lds_limits()) return rc;
     Sched s = carve(ws, n_rows, Gr, hff, false);
-    RELIBRA_LAUNCH(RELIBRA_K_SCHED, stream, sched_kernel<<<1, 256, (size_t)(Gr + 1) * sizeof(int32_t), stream>>>(group_offset, group_expert, nullptr, g_begin, Gr, n_rows, E, 0, s, err_flag));
+    RELIBRA_LAUNCH(RELIBRA_K_SCHED, stream, sched_kernel<<<1, 256, (size_t)(Gr + 1) * sizeof(int32_t), stream>>>(group_offset, group_expert, nullptr, g_begin, Gr, n_rows, E, 0,
+                                                                                                    max_row_tiles(n_rows, Gr), s, err_flag));
     RELIBRA_HIP_TRY(launch_check());
     const long long R = max_row_tiles(n_rows, Gr);
     const bool wide1 = row_tiles_wide(hff, 256, n_rows, Gr, 2 * h), wide2 = row_tiles_wide(h, 512, n_rows, Gr, hff);
@@ -1433,7 +1436,7 @@ static int ffn_bwd_impl(const void *dYrows, const void *Xrows,
     // the slot table matters only to kernels that write dW or read replica parameters
     const int32_t *slot_table = (defer && !(flags & RELIBRA_BWD_REPLICA_WEIGHTS)) ? nullptr : group_dw_slot;
     RELIBRA_LAUNCH(RELIBRA_K_SCHED, stream, sched_kernel<<<1, 256, (size_t)(Gr + 1) * sizeof(int32_t), stream>>>(group_offset, group_expert, slot_table, g_begin, Gr, n_rows, E,
-                                        n_dw_slots, s, err_flag));
+                                        n_dw_slots, max_row_tiles(n_rows, Gr), s, err_flag));
     RELIBRA_HIP_TRY(launch_check());
     const long long R = max_row_tiles(n_rows, Gr);
     const bool wide_h = row_tiles_wide(h, 512, n_rows, Gr, 2 * hff);

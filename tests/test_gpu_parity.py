@@ -369,6 +369,20 @@ def test_ffn_flags_inconsistent_group_tables_without_faulting():
     assert err.item() & rl.ERR_GROUP_TABLE
 
 
+def test_ffn_row_tiles_of_overlapping_groups_end_with_the_lists():
+    """A corrupted table whose groups cover the same rows again and again has more row tiles than the workspace lists
+    (which hold those of every table without overlap): flagged, and nothing is written behind the workspace."""
+    rows, groups = 1024, 64
+    X, _, Wg, Wu, Wd = ffn_case(seed=12, E=2, h=64, hff=64, rows=(rows,), experts=(0,))[2:]
+    go, ge = dev_i32(np.array([0, rows] * (groups // 2) + [0], np.int32)), dev_i32(np.arange(groups) % 2)
+    need, guard = rl.workspace_bytes(rl.WS_FFN_FWD, rows, 1, 2, groups, 64, 64), 1 << 16
+    ws = torch.full((need + guard,), 99, dtype=torch.uint8, device=DEV)
+    err = rl.new_err_flag()
+    rl.relibra_moe_ffn_fwd(X.to(DEV), go, ge, Wg.to(DEV), Wu.to(DEV), Wd.to(DEV), workspace=ws[:need], err_flag=err)
+    assert err.item() == rl.ERR_GROUP_TABLE
+    assert (ws[need:] == 99).all()
+
+
 # ------------------------------------------------------------------ combine
 @pytest.mark.parametrize("T,k,h", [(97, 4, 256), (5, 1, 8), (300, 8, 2048)])
 def test_combine_modes(T, k, h):
