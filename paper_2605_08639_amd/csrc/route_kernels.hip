@@ -248,12 +248,18 @@ perm_rank_kernel(const int32_t *__restrict__ ids, int N, int E, int G, int ebits
 // The three passes in one block, for small micro-batches: the three launches cost more than the work
 // (each is a launch and a few dependent memory round trips).  Every wave takes a sixteenth of the
 // assignments; counts, their scan over the waves and the experts' first instances stay in LDS, so that a
-// round of 64 assignments reads memory only where an expert is split over several instances.  The block's
-// time grows by about 2 us per 1024 assignments: 3.5 us at 1024, 6.3 at 2048, 7.5 at 3108 against 6.5 us
-// and two more launches for the three kernels, which are the faster ones from there on (at 32768 the block
-// would take 79 us, they take 10).
+// round of 64 assignments reads memory only where an expert is split over several instances.  A wave's rounds run one
+// after the other, so the time goes in steps of 1024 assignments, and with the number of experts (the scan).  One
+// block / three kernels, us, in a captured graph and called one by one (where launches are what three kernels cost):
+//     assignments            1024       2048       3072       4096              1024        2048       3072       4096
+//     8 experts, top-2    4.6  8.6   6.4  8.6   8.4  8.7  10.0  8.7           7.4 12.3   7.5 12.9   8.1 12.8   9.7 13.0
+//     128 experts, top-8  4.0  8.4   7.0  9.6   6.2  8.9   7.2  9.1           7.4 12.7   7.3 12.7   7.4 12.7   7.3 12.8
+//     512 experts, top-8  6.3 13.4   8.8 12.9  12.2 13.5  16.2 13.9           7.4 13.3   8.5 12.8  12.0 13.5  16.0 13.9
+// (128 experts at 3584, with more experts split: 10.0 9.6 and 9.8 12.8.)  So up to 3072 assignments, and up to 4096 for
+// 256 experts, where only a captured call loses, by about 1 us.
 constexpr int kSmallThreads = 1024, kSmallWaves = kSmallThreads / 64;
-constexpr int kSmallN = 4096, kSmallE = 512;               // (kSmallWaves + 2) * kSmallE ints of LDS
+constexpr int kSmallE = 512;                               // (kSmallWaves + 2) * kSmallE ints of LDS
+inline bool perm_in_one_block(int N, int E) { return E <= kSmallE && N <= (E <= 256 ? 4096 : 3072); }
 __global__ void __launch_bounds__(kSmallThreads)
 perm_small_kernel(const int32_t *__restrict__ ids, int N, int E, int G, int ebits, PlanTables t,
                   int32_t *__restrict__ row_of, int32_t *__restrict__ src_of, int32_t *err_flag, SrcSplit sp)
@@ -522,7 +528,7 @@ static int permute_impl(const int32_t *ids_dev, const int32_t *inst_ptr_dev, con
     int ebits = 0;
     while ((1 << ebits) < E) ++ebits;
     const PlanTables tables{inst_ptr_dev, inst_rows_dev, inst_group_dev, group_offset_dev};
-    if (N <= kSmallN && E <= kSmallE) {
+    if (perm_in_one_block(N, E)) {
         const size_t lds = (size_t)(kSmallWaves + 2) * E * sizeof(int32_t);
         RELIBRA_LAUNCH(RELIBRA_K_PERM_SMALL, stream, perm_small_kernel<<<1, kSmallThreads, lds, stream>>>(ids_dev, N, E, G, ebits, tables,
                                                                 row_of_dev, src_of_dev, err_flag_dev, split));

@@ -211,7 +211,7 @@ def test_timed_plan_drives_the_device_path():
 
 
 @pytest.mark.parametrize("E,k,T,EP", [(4, 1, 1, 4), (8, 1, 1025, 4), (8, 2, 2048, 4), (8, 1, 4097, 4), (512, 4, 1024, 8),
-                                      (516, 2, 300, 4), (32, 4, 511, 8)])
+                                      (516, 2, 300, 4), (32, 4, 511, 8), (256, 2, 2048, 8), (512, 2, 1536, 8), (512, 1, 3073, 8)])
 def test_permute_at_the_one_block_limits(E, k, T, EP):
     """Sizes around a wave's share and around the largest ones that one block permutes."""
     cfg = wl.small_config(E=E, k=k, EP=EP, r=1, T=T, n_mb=1, h=8)
@@ -219,8 +219,10 @@ def test_permute_at_the_one_block_limits(E, k, T, EP):
     p = plan_both(cfg, oracle.route_hist(ids, cfg.E)[0])
     X = torch.randn((T, 8), generator=torch.Generator().manual_seed(T)).to(torch.bfloat16)
     err = rl.new_err_flag()
+    rl.prof_start(level=2, max_records=16)
     row_of, src_of, Xrows = rl.relibra_permute(torch.from_numpy(ids[0]).to(DEV), *(dev_i32(p[key][0]) for key in (
         "inst_ptr", "inst_rows", "inst_group", "group_offset")), X.to(DEV), cfg.E, cfg.G, err_flag=err)
+    assert ("perm_small" in rl.prof_stop()) == (E <= 512 and k * T <= (4096 if E <= 256 else 3072))
     want_row, want_src = oracle.permute(ids[0], cfg.E, *(p[key][0] for key in ("inst_ptr", "inst_rows", "inst_group", "group_offset")))
     assert err.item() == 0
     assert np.array_equal(row_of.cpu().numpy(), want_row) and np.array_equal(src_of.cpu().numpy(), want_src)
