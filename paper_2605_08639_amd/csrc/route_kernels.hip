@@ -311,16 +311,41 @@ inline int lanes_per_row_log2(int vec_per_row, int pieces)
     return l;
 }
 
-// Row gather: Xrows[row] = X[src_of[row] / k], 16 bytes per piece, walked token by token: a token's
-// pieces are read once into registers and stored to the rows of its k assignments.  Walked row by row
-// the same kernel fetched every token k times through the caches and ran at the copy rate; this way the
-// write stream alone bounds it.  A row is written by the assignment that src_of names for it, so rows
-// nobody claims stay untouched.  8192 tokens x 4096, k = 8 (537 MB written): 103 us, 159 us row by row;
-// 4096 x 2048: 56 against 83 us.
+// Row gather: Xrows[row] = X[src_of[row] / k], 16 bytes per piece.  Rows nobody claims stay untouched.
+// Two forms.  Token by token: a token's pieces are read once into registers and stored to the rows of its k
+// assignments (a row is written by the assignment that src_of names for it); the write stream alone bounds it, where
+// walked row by row the gather fetched every token k times through the caches and ran at the copy rate.  Row by row:
+// k times the threads and one lookup less in the chain, for copies that do not fill the chip.  Row by row / token by
+// token, us: 777 tokens x 256, k = 4 2.0 3.2; 32 x 7168, k = 8 2.0 3.0; 16384 x 128, k = 1 2.6 3.0; 4096 x 512, k = 2
+// 3.4 3.6; 128 x 7168, k = 8 4.9 5.4; 8192 x 128, k = 8 (16 MiB of rows) 4.3 5.3; 256 x 7168, k = 8 (28 MiB) 9.4 7.4;
+// 2048 x 4096, k = 2 12.0 9.1; 16384 x 4096, k = 2 83 79; 8192 x 4096, k = 8 (512 MiB) 159 103.
+constexpr size_t kGatherByRow = (size_t)16 << 20;          // bytes of rows up to which they are walked one by one
+__global__ void __launch_bounds__(kRowThreads)
+gather_by_row_kernel(const uint4 *__restrict__ X, const int32_t *__restrict__ src_of, int N, int T, int k, int vec_per_row, int lpr_log2,
+                     uint4 *__restrict__ Xrows)
+{
+    const int lpr = 1 << lpr_log2, rows_per_block = kRowThreads >> lpr_log2;
+    const int r_local = threadIdx.x >> lpr_log2, c0 = threadIdx.x & (lpr - 1);
+    for (int row = blockIdx.x * rows_per_block + r_local; row < N; row += gridDim.x * rows_per_block) {
+        const int a = src_of[row];
+        if (a < 0) continue;
+        const int t = a / k;
+        if (t >= T) continue;
+        const uint4 *__restrict__ src = X + (size_t)t * vec_per_row;
+        uint4 *__restrict__ dst = Xrows + (size_t)row * vec_per_row;
+        int c = c0;
+        for (; c + 3 * lpr < vec_per_row; c += 4 * lpr) {
+            const uint4 v0 = src[c], v1 = src[c + lpr], v2 = src[c + 2 * lpr], v3 = src[c + 3 * lpr];
+            dst[c] = v0; dst[c + lpr] = v1; dst[c + 2 * lpr] = v2; dst[c + 3 * lpr] = v3;
+        }
+        for (; c < vec_per_row; c += lpr) dst[c] = src[c];
+    }
+}
+
 constexpr int kGatherRows = 8;                             // row lookups in flight
 __global__ void __launch_bounds__(kRowThreads)
-gather_rows_kernel(const uint4 *__restrict__ X, const int32_t *__restrict__ row_of, const int32_t *__restrict__ src_of, int N, int T, int k,
-                   int vec_per_row, int lpr_log2, uint4 *__restrict__ Xrows)
+gather_by_token_kernel(const uint4 *__restrict__ X, const int32_t *__restrict__ row_of, const int32_t *__restrict__ src_of, int N, int T,
+                       int k, int vec_per_row, int lpr_log2, uint4 *__restrict__ Xrows)
 {
     const int lpr = 1 << lpr_log2, tokens_per_block = kRowThreads >> lpr_log2;
     const int t_local = threadIdx.x >> lpr_log2, c0 = threadIdx.x & (lpr - 1);
@@ -548,9 +573,12 @@ static int permute_impl(const int32_t *ids_dev, const int32_t *inst_ptr_dev, con
     }
     if (with_rows) {
         const int vpr = h / 8, lpr_log2 = lanes_per_row_log2(vpr, 4);
-        const int grid = grid_for((size_t)T, kRowThreads >> lpr_log2, 256 * 32);
-        RELIBRA_LAUNCH(RELIBRA_K_GATHER, stream, gather_rows_kernel<<<grid, kRowThreads, 0, stream>>>((const uint4 *)X_dev, row_of_dev, src_of_dev,
-                                                     N, T, k, vpr, lpr_log2, (uint4 *)Xrows_dev));
+        const bool by_row = (size_t)N * h * sizeof(bf16_t) <= kGatherByRow;
+        const int grid = grid_for((size_t)(by_row ? N : T), kRowThreads >> lpr_log2, 256 * 32);
+        if (by_row) RELIBRA_LAUNCH(RELIBRA_K_GATHER, stream, gather_by_row_kernel<<<grid, kRowThreads, 0, stream>>>((const uint4 *)X_dev, src_of_dev,
+                                                                 N, T, k, vpr, lpr_log2, (uint4 *)Xrows_dev));
+        else RELIBRA_LAUNCH(RELIBRA_K_GATHER, stream, gather_by_token_kernel<<<grid, kRowThreads, 0, stream>>>((const uint4 *)X_dev, row_of_dev,
+                                                          src_of_dev, N, T, k, vpr, lpr_log2, (uint4 *)Xrows_dev));
         RELIBRA_HIP_TRY(launch_check());
     }
     return RELIBRA_OK;

@@ -229,6 +229,22 @@ def test_permute_at_the_one_block_limits(E, k, T, EP):
     assert torch.equal(Xrows.cpu(), X[torch.from_numpy(want_src).long() // k])
 
 
+@pytest.mark.parametrize("E,k,T,h", [(8, 2, 300, 8), (16, 4, 777, 264), (8, 8, 1024, 1024), (8, 8, 1024, 1032), (16, 9, 700, 2040)])
+def test_row_gather_on_both_sides_of_its_rule(E, k, T, h):
+    """Rows of up to 16 MiB and beyond, widths that no number of threads divides, more assignments per token than are
+    looked up at a time."""
+    cfg = wl.small_config(E=E, k=k, EP=4, r=1, T=T, n_mb=1, h=8)
+    ids, _ = routing(cfg)
+    p = plan_both(cfg, oracle.route_hist(ids, cfg.E)[0])
+    tabs = [dev_i32(p[key][0]) for key in ("inst_ptr", "inst_rows", "inst_group", "group_offset")]
+    X = torch.randn((T, h), generator=torch.Generator().manual_seed(h)).to(torch.bfloat16).to(DEV)
+    Xrows = torch.full((T * k + 1, h), 7.0, dtype=torch.bfloat16, device=DEV)
+    err = rl.new_err_flag()
+    _, src_of, _ = rl.relibra_permute(torch.from_numpy(ids[0]).to(DEV), *tabs, X, cfg.E, cfg.G, Xrows=Xrows[:-1], err_flag=err)
+    assert err.item() == 0
+    assert torch.equal(Xrows[:-1], X[src_of.long() // k]) and (Xrows[-1] == 7.0).all()
+
+
 def test_permute_flags_a_plan_that_does_not_cover_the_routing():
     cfg = wl.small_config(E=8, k=2, EP=4, r=1, T=200, n_mb=1, h=64)
     ids, _ = routing(cfg)
