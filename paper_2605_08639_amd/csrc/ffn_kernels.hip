@@ -1371,16 +1371,28 @@ extern "C" int relibra_moe_ffn_fwd_gated(const void *X, int T, const int32_t *ro
 }
 
 // Per-micro-batch weight gradients in 256 x 256 tiles of eight waves: half the operand bytes per flop and 1 KiB of
-// a row per store, but one workgroup per compute unit, whose reads of old gradients nobody covers.  From 192 rows
-// per group on when the gradients are written, from 448 when they are added to; outputs of at least 256 each way,
-// and at least one tile per unit.  128 experts of 2048 x 768, dWg and dWu, small (from 512 rows on: 256 x 128)
-// tiles -> these: written, 64 rows per group 294 -> 305 us, 128 404 -> 366, 256 565 -> 476, 512 765 -> 633; added,
-// 256 rows 677 -> 698, 512 845 -> 792, 1024 1170 -> 1082.  8 of 4096 x 14336: written, 128 rows 784 -> 806, 256
-// 1148 -> 1051, 512 1957 -> 1614.
+// a row per store, but one workgroup per compute unit, whose start, reads of old gradients and stores nobody covers, and
+// whose last round is as long as the others.  `padded`: the tiles with both launches' last rounds filled up; `small`: the
+// same work in 128 x 128 tiles, four to a unit (in tiles of 256 x 256).  Small tiles (from 512 rows on: 256 x 128)
+// -> these, kernel times, by rows per group:
+//   written       padded/small   128   192   256   384   512   1024  2048      added         512   1024  1536  2048
+//   64 x 4096 x 1536      1.0   1.04  0.93  0.88  0.87  0.88                                1.11
+//   8 x 4096 x 4096       1.0   1.03  1.06  1.01  0.93  0.85  0.82  0.88                    1.05  1.03  0.95  0.95
+//   128 x 2048 x 768      1.0   0.93  0.85  0.85  0.88  0.93  0.89                          1.04  1.01  0.96
+//   20 x 2880 x 2880      1.11  1.05  0.96  0.93  0.90  0.90  0.90                          1.03  1.00  0.98
+//   18 x 1024 x 2048      1.19  0.96  0.92  0.91  0.93  0.96  0.93  0.93                    1.10  1.06  1.03  0.98
+//   40 x 896 x 1152       1.35  1.06  1.03  1.03  1.04  1.06  1.03  1.03                    1.11  1.08  1.08  1.04
+//   16 x 640 x 1536       1.78  1.22  1.22  1.21  1.24  1.15  1.06  1.01                    1.16  1.11  1.05  1.04
+// So from 192 rows per group on where gradients are written and at most a fifth is padding, and from 1536 on where they
+// are added to and next to nothing is.
 static inline bool wgrad_tiles_wide(int n_rows, int groups, int h, int hff, bool add)
 {
-    const long long down = (long long)groups * ((h + 255) / 256) * ((hff + 255) / 256);
-    return h >= 256 && hff >= 256 && (long long)n_rows >= (add ? 448LL : 192LL) * groups && down >= kComputeUnits;
+    const auto cut = [](long long n, long long by) { return (n + by - 1) / by; };
+    const long long down = groups * cut(h, 256) * cut(hff, 256), gate_up = groups * cut(hff, 128) * cut(h, 256);
+    const long long padded = (cut(down, kComputeUnits) + cut(gate_up, kComputeUnits)) * kComputeUnits;
+    const long long small4 = groups * (cut(h, 128) * cut(hff, 128) + cut(hff, 64) * cut(h, 128));     // four times `small`
+    return h >= 256 && hff >= 256 && down >= kComputeUnits && (long long)n_rows >= (add ? 1536LL : 192LL) * groups &&
+           100 * 4 * padded <= (add ? 105 : 120) * small4;
 }
 
 // Whether the gradient tensors (fp32, `values` in each) are larger than the 256 MB last-level cache together.

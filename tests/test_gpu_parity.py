@@ -881,12 +881,16 @@ def test_weight_gradients_of_short_groups(groups):
             assert rel_l2(got[e], want[e]) <= TOL
 
 
-def test_weight_gradients_of_many_rows_per_group():
-    """The 256 x 256 tiles of the per-micro-batch weight gradients: written from about 200 rows per group on (ragged
-    rows and outputs), added to from about 450 on."""
-    E, h, hff, err = 66, 320, 448, rl.new_err_flag()
+@pytest.mark.parametrize("E,h,hff,bounds", [
+    (66, 320, 448, ((129, 290), (380, 580))),              # a last round that is nearly empty: the smaller tiles
+    (64, 448, 448, ((129, 290), (380, 580))),              # 256 x 256 tiles where written, ragged rows and outputs
+    (64, 448, 512, ((1520, 1640),)),                       # 256 x 256 tiles where written and where added to
+])
+def test_weight_gradients_of_many_rows_per_group(E, h, hff, bounds):
+    """The 256 x 256 tiles of the per-micro-batch weight gradients and the smaller ones beside them."""
+    err = rl.new_err_flag()
     rng = np.random.default_rng(5)
-    for lo, hi in ((129, 290), (380, 580)):
+    for lo, hi in bounds:
         rows = rng.integers(lo, hi, E)
         go, ge, X, dY, Wg, Wu, Wd = ffn_case(seed=lo, E=E, h=h, hff=hff, rows=rows, experts=range(E))
         go_d, ge_d, W_d = dev_i32(go), dev_i32(ge), [W.to(DEV) for W in (Wg, Wu, Wd)]
