@@ -1257,13 +1257,21 @@ static int ensure_lds_limits()
 static inline unsigned grid8(long long tiles) { return (unsigned)((tiles + 7) / 8 * 8); }
 
 // The wide column tiles are taken where they pad the output's columns no further than the narrow ones do
-// (half of all widths), and where there are more narrow tiles than the compute units can take one each (and an
-// eighth): fewer tiles leave units idle that tiles of half the width would use.  Row tiles are estimated: half a
-// tile per group for its tail.  Measured, narrow -> wide, us: 64 groups, 4032 x 1472 (pads alike), 100 rows each:
+// (half of all widths), and where there are more narrow tiles than the compute units can take one each:
+// fewer tiles leave units idle that tiles of half the width would use.  Row tiles are estimated: half a
+// tile per group for its tail.  Wide / narrow over 2 to 32 groups of 64 to 700 rows, 640 to 4096 columns, mean of the
+// four kernels (smallest and largest): estimates of 200 to 255 narrow tiles 1.20 (0.95, 1.61), 256 1.21 (0.97, 1.41),
+// 257 to 287 0.91 (0.75, 1.36), 320 to 359 0.99 (0.61, 1.29: the large ones are groups of whole tiles, which the
+// estimate overstates), 360 to 449 0.91.  Measured, narrow -> wide, us: 64 groups, 4032 x 1472 (pads alike), 100 rows each:
 // gate/up 394 -> 324, down 186 -> 174, dA 200 -> 176, dX 329 -> 311; 1200 rows each: 2146 -> 1723, 1076 -> 948,
 // 1056 -> 980, 1820 -> 1694.  3136 columns (8 % more padding): down 521 -> 534.  8 groups of 512 x 1024, 200
 // rows each (few tiles): gate/up 17 -> 22, down 19 -> 26, dA 20 -> 28, dX 27 -> 42; 8 of 4096 x 14336, dX at 32
 // rows 416 -> 608, at 200 rows 536 -> 676, at 300 rows (384 narrow tiles) 918 -> 684.
+// A width that the 512-column tiles do not divide takes them only where their last round is nearly full (at most 15 %
+// idle): the narrow ones then waste less in the last round than the wide ones save.  Wide / narrow for 1408 and 1472
+// columns over contractions of 640 to 2048, idle 33 and 28 % (32 groups of 450 rows, 16 of 1000): dA 1.09 to 1.18, down
+// 1.00 to 1.12, dX 1.00 to 1.17; idle 4 % (128 groups of 100 rows): 0.92 to 1.12, 0.95 to 1.00, 0.91 to 1.01.  (Gate/up, 256
+// columns of each: 0.81 to 1.02 either way.)
 // Short contractions (k_dim, over both products where there are two) stay narrow too: two workgroups per unit
 // then hide each other's start and epilogue, which weigh more than the loads the wide tile saves.  16 groups of
 // 800 rows, 4096 columns, narrow -> wide: down over 64 28 -> 32 us, 128 38 -> 48, 256 59 -> 65, 512 82 -> 92; 64
@@ -1276,7 +1284,9 @@ static inline bool row_tiles_wide(int n_dim, int width, int n_rows, int groups, 
     if (k_dim <= kShortDot) return false;
     const long long wide = (n_dim + width - 1) / width, narrow = (n_dim + width / 2 - 1) / (width / 2);
     const long long row_tiles = std::max((long long)groups, (long long)n_rows / BM + groups / 2);
-    return n_dim >= width && 2 * wide == narrow && row_tiles * narrow > kComputeUnits + kComputeUnits / 8;
+    const long long tiles = row_tiles * wide, slots = (tiles + kComputeUnits - 1) / kComputeUnits * kComputeUnits;
+    const bool full = n_dim % width == 0 || width < 512 || 100 * slots <= 115 * tiles;
+    return n_dim >= width && 2 * wide == narrow && row_tiles * narrow > kComputeUnits && full;
 }
 
 // Launch of a row-tiled GEMM kernel template <bool WT, int AW>: narrow (four waves, two workgroups
