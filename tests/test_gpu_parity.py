@@ -283,11 +283,12 @@ FFN_CASES = [
     dict(seed=4, E=2, h=320, hff=448, rows=(200, 0, 131), experts=(0, 1, 0)),
     # long groups: the large weight-gradient tile geometry (512 or more rows per group on average)
     dict(seed=7, E=2, h=128, hff=256, rows=(1100, 700), experts=(1, 0)),
-    # widths that take the 512-column (eight-wave) tiles in every row-tiled kernel, ragged rows and a replica
+    # widths of whole 512-column tiles (calls of so few tiles stay on the 256-column ones: see
+    # test_wide_tiles_on_weights_as_stored for the others), ragged rows and a replica
     dict(seed=8, E=3, h=512, hff=512, rows=(1, 64, 65, 200, 0, 129), experts=(2, 0, 1, 0, -1, 2)),
     dict(seed=9, E=2, h=1024, hff=1536, rows=(300, 77), experts=(1, 0)),
-    # the shortest contractions the wide tiles can meet (two slabs: fewer than the ring holds): gate/up and dA
-    # over h = 64 with 512-wide outputs, then down over h' = 64 and dX over two phases of two slabs
+    # the shortest contractions (two slabs: fewer than the ring holds): gate/up and dA over h = 64 with 512-wide
+    # outputs, then down over h' = 64 and dX over two phases of two slabs
     dict(seed=10, E=2, h=64, hff=512, rows=(130, 64), experts=(1, 0)),
     dict(seed=11, E=2, h=512, hff=64, rows=(129, 3), experts=(0, 1)),
 ]
@@ -647,7 +648,7 @@ def test_replica_push_flags_bad_table_and_leaves_empty_slots():
 @pytest.mark.parametrize("E,slots,h,hff,n_wg", [
     (1, 1, 8, 8, 1),             # one vector short of a thread's share
     (5, 7, 192, 320, 3),         # chunks that the block does not fill, several slots of one expert
-    (3, 1100, 64, 72, 5),        # two lists of slots: an expert's sum goes on across them
+    (3, 1100, 64, 72, 5),        # three lists of slots: an expert's sum goes on across them
     (40, 16, 256, 520, 64),      # more workgroups than chunks of an expert
 ])
 def test_replica_push_and_pull_at_list_and_chunk_edges(E, slots, h, hff, n_wg):
@@ -912,8 +913,9 @@ def test_weight_gradients_of_many_rows_per_group(E, h, hff, bounds):
                 assert rel_l2(twice[e], 2 * got[e].cpu().numpy()) <= 1e-6
 
 
-@pytest.mark.parametrize("h,hff", [(512, 1024), (960, 1472), (512, 960)])
-def test_gate_fused_backward_on_wide_tiles(h, hff):
+@pytest.mark.parametrize("weights_t", [False, True], ids=["stored-layout", "transposed-copies"])
+@pytest.mark.parametrize("h,hff", [(512, 1024), (960, 1472), (512, 960), (576, 1024), (704, 1536)])
+def test_gate_fused_backward_on_wide_tiles(h, hff, weights_t):
     """Gates that are powers of two scale without rounding: the gate-fused data gradients then equal, bit for bit,
     the unfused ones on the scaled rows; dgate = <dOut, Y> within the bar.  Wide tiles, also where they reach
     beyond the columns."""
@@ -928,7 +930,9 @@ def test_gate_fused_backward_on_wide_tiles(h, hff):
     guard = 1 << 16
     need = rl.workspace_bytes(rl.WS_DGATE, N, 1, 3, len(ge), h, hff)
     scratch = torch.full((need + guard,), 99, dtype=torch.uint8, device=DEV)
-    got, dgate = rl.relibra_moe_ffn_bwd_gated(dO, tok, gate, Gt, U, go_d, ge_d, sl_d, *W_d, E=3, dgate_scratch=scratch, err_flag=err)
+    W_b, flags = ([rl.relibra_transpose_experts(W) for W in W_d], rl.BWD_TRANSPOSED_WEIGHTS) if weights_t else (W_d, 0)
+    got, dgate = rl.relibra_moe_ffn_bwd_gated(dO, tok, gate, Gt, U, go_d, ge_d, sl_d, *W_b, E=3, dgate_scratch=scratch, err_flag=err,
+                                              flags=flags)
     want = rl.relibra_moe_ffn_bwd((gate[:, None] * dO.float()).to(torch.bfloat16), None, Gt, U, A, go_d, ge_d, sl_d, *W_d, None, None, None,
                                   E=3, flags=rl.BWD_DEFER_WGRAD, err_flag=err)
     assert err.item() == 0
@@ -979,7 +983,7 @@ def test_forward_with_fused_row_gather_is_bit_identical():
 
 
 # ------------------------------------------------------------------ gate-side fusion of the backward
-@pytest.mark.parametrize("hff", [320, 512], ids=["narrow-dA-tiles", "wide-dA-tiles"])
+@pytest.mark.parametrize("hff", [320, 512], ids=["ragged-dA-tiles", "whole-dA-tiles"])
 @pytest.mark.parametrize("weights_t", [False, True], ids=["stored-layout", "transposed-copies"])
 def test_gate_fused_backward_matches_the_unfused_definition(weights_t, hff):
     """The combine (Section 2.1: gate-weighted sum of the selected experts' outputs) is linear, so its
