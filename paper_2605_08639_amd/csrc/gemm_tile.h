@@ -6,8 +6,8 @@
 //   KcTile: k contiguous in memory (element (row,k) at base[row*ld + k]).  LDS holds [row][BKT],
 //           64 or 128 bytes per row, 16-byte pieces XOR-swizzled by the row so that the 16-byte
 //           fragment reads of 32 consecutive rows spread over all banks.  With BKT = 64 a row
-//           is one full 128-byte line per load: the L1's outstanding requests, which bound the
-//           L2 -> LDS rate, carry twice the bytes (measured 17 against 12 TB/s, loads alone).
+//           is one full 128-byte line per load, which costs the address unit and the L1 no more
+//           than half a line does (this loop's loads alone: 17 against 12 TB/s).
 //   KsTile: k strided in memory (element (row,k) at base[k*ld + row]).  LDS holds [k][ROWS] as
 //           it lies in memory; fragments are read with the transposing LDS read
 //           (ds_read_b64_tr_b16), 16-byte pieces XOR-swizzled by k.
