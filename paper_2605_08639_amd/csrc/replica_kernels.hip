@@ -29,6 +29,7 @@ namespace relibra {
 
 constexpr int kReplicaThreads = 512;
 constexpr int kPushLoads = 24, kPullLoads = 12;            // 16-byte pieces per thread and chunk (pull: of both operands)
+constexpr int kPushTail = 8;                               // the same in a block's last, partial chunk (of a small block: its only one)
 constexpr int kTableChunk = kReplicaThreads;               // slots listed at a time
 constexpr int kReplicaWaves = 4;                           // waves per SIMD that the registers leave room for: at most 128 each
 // Sizes inside a block are 32-bit: 64 GiB, and three tensors of at least two blocks do not fit the card.  (Besides, a
@@ -105,15 +106,22 @@ replica_push_kernel(u32x4_t *__restrict__ Wg, u32x4_t *__restrict__ Wu, u32x4_t 
             const uint32_t at = (c - which * chunks) * CHUNK, n = vec - at;      // vectors from here to the block's end
             const u32x4_t *src = W + (size_t)uniform(l.expert[i]) * vec + at;
             u32x4_t *dst = W + (size_t)(E + uniform(l.slot[i])) * vec + at;
-            if (n < CHUNK) {                               // the block's last chunk
-                for (uint32_t j = threadIdx.x; j < n; j += kReplicaThreads) dst[j] = src[j];
+            if (n >= CHUNK) {
+                u32x4_t v[kPushLoads];
+#pragma unroll
+                for (int j = 0; j < kPushLoads; ++j) v[j] = scalar_base(src + j * kReplicaThreads)[threadIdx.x];
+#pragma unroll
+                for (int j = 0; j < kPushLoads; ++j) scalar_base(dst + j * kReplicaThreads)[threadIdx.x] = v[j];
                 continue;
             }
-            u32x4_t v[kPushLoads];
+            for (uint32_t from = 0; from < n; from += kPushTail * kReplicaThreads) {       // past the block's end: its last vector again, not stored
+                u32x4_t v[kPushTail];
 #pragma unroll
-            for (int j = 0; j < kPushLoads; ++j) v[j] = scalar_base(src + j * kReplicaThreads)[threadIdx.x];
+                for (int j = 0; j < kPushTail; ++j) v[j] = scalar_base(src)[min(from + j * kReplicaThreads + threadIdx.x, n - 1)];
 #pragma unroll
-            for (int j = 0; j < kPushLoads; ++j) scalar_base(dst + j * kReplicaThreads)[threadIdx.x] = v[j];
+                for (int j = 0; j < kPushTail; ++j)
+                    if (from + j * kReplicaThreads + threadIdx.x < n) scalar_base(dst)[from + j * kReplicaThreads + threadIdx.x] = v[j];
+            }
         }
     }
     if (bad && blockIdx.x == 0) atomicOr(err_flag, RELIBRA_ERR_ID_RANGE);
