@@ -534,7 +534,7 @@ int relibra_moe_ffn_wgrad_batched(const relibra_wgrad_mb *mbs_host, int n_mb, in
  * the compute units the copy may occupy, so that it can run beside other kernels on a second
  * stream (the paper overlaps it with attention and gives it few SMs).  Values >= E in the
  * table are skipped and flagged RELIBRA_ERR_ID_RANGE.
- * Limits: h*hff % 8 == 0, 16-byte aligned tensors.
+ * Limits: h*hff % 8 == 0 and below 0xffff0000 * 8 (64 GiB a matrix), 16-byte aligned tensors.
  */
 int relibra_replica_push(void *Wg_dev, void *Wu_dev, void *Wd_dev,
                          const int32_t *replica_expert_dev, int E, int EP, int r, int h, int hff,
@@ -552,7 +552,7 @@ int relibra_replica_push(void *Wg_dev, void *Wu_dev, void *Wd_dev,
  * of workgroups (n_workgroups >= 1), to run on a second stream beside other work.  The order of
  * every element's additions is the in-line sum's: results are identical bit for bit.  The slots
  * keep their contents (the next backward call overwrites them).  Entries >= E: skipped, flagged
- * RELIBRA_ERR_ID_RANGE.  Limits: h*hff % 4 == 0, 16-byte aligned tensors.
+ * RELIBRA_ERR_ID_RANGE.  Limits: h*hff % 4 == 0 and below 0xffff0000 * 4, 16-byte aligned tensors.
  */
 int relibra_replica_pull(float *dWg_dev, float *dWu_dev, float *dWd_dev,
                          const int32_t *replica_expert_dev, int E, int EP, int r, int h, int hff,
