@@ -113,54 +113,88 @@ inline Sched carve(void *ws, int n_rows, int Gr, int hff, bool bwd)
 constexpr int kBand = 8;
 constexpr int kMaxSchedGroups = 8192;          // groups of one call (g_end - g_begin)
 
-// One block.  Validates the group tables of [g_begin, g_end) (bad groups become empty and raise
-// the flag), lists the row tiles group by group, and lists the live replica slots.  The lists hold
-// max_tiles: enough for any table whose groups do not overlap; an overlapping one ends there, flagged.
-__global__ void __launch_bounds__(256)
-sched_kernel(const int32_t *__restrict__ group_offset, const int32_t *__restrict__ group_expert,
-             const int32_t *__restrict__ group_dw_slot, int g_begin, int Gr, int n_rows, int E, int n_dw_slots,
-             int max_tiles, Sched s, int32_t *err_flag)
+// The caller's group tables, for the kernel that works the schedule out (group_offset null: another one has).
+struct SchedIn {
+    const int32_t *group_offset, *group_expert, *group_dw_slot;
+    int g_begin, Gr, n_rows, E, n_dw_slots, max_tiles;
+    int32_t *err_flag;
+};
+struct SchedGroup {
+    int lo, hi, expert, slot;
+    bool bad;
+};
+// Group number i of the call, validated: a bad one is empty.
+__device__ __forceinline__ SchedGroup sched_group(const SchedIn &in, int i)
 {
-    extern __shared__ int32_t prefix[];        // [Gr + 1] tile_prefix, kept in LDS for the searches below
-    __shared__ int32_t sums[4];
+    const int g = in.g_begin + i;
+    SchedGroup r;
+    r.lo = in.group_offset[g];
+    r.hi = in.group_offset[g + 1];
+    r.expert = in.group_expert[g];
+    r.slot = in.group_dw_slot ? in.group_dw_slot[g] : 0;
+    r.bad = r.lo < 0 || r.hi < r.lo || r.hi > in.n_rows || r.expert < -1 || r.expert >= in.E;
+    if (in.group_dw_slot && r.expert >= 0 && (r.slot < 0 || r.slot >= in.n_dw_slots)) r.bad = true;
+    if (r.bad) { r.lo = r.hi = 0; r.expert = -1; }
+    if (r.expert < 0) r.hi = r.lo;
+    return r;
+}
+// 256 threads.  prefix [Gr + 1] (LDS): row tiles in front of every group; returns their number.  WRITE: the
+// groups go to the workspace too, and what is wrong with them to the flag.
+template <bool WRITE>
+__device__ __forceinline__ int sched_prefix(const SchedIn &in, const Sched &s, int32_t *prefix, int32_t *sums)
+{
     const int tid = threadIdx.x;
-    if (tid == 0) { s.tile_prefix[0] = 0; prefix[0] = 0; }
+    if (tid == 0) prefix[0] = 0;
     bool bad_any = false;
     int carry = 0;                             // tiles so far, the same in every thread
-    for (int base = 0; base < Gr; base += 256) {
+    for (int base = 0; base < in.Gr; base += 256) {
         const int i = base + tid;
         int tiles = 0;
-        if (i < Gr) {
-            const int g = g_begin + i;
-            int lo = group_offset[g], hi = group_offset[g + 1], e = group_expert[g];
-            int slot = group_dw_slot ? group_dw_slot[g] : 0;
-            bool bad = lo < 0 || hi < lo || hi > n_rows || e < -1 || e >= E;
-            if (group_dw_slot && e >= 0 && (slot < 0 || slot >= n_dw_slots)) bad = true;
-            if (bad) { bad_any = true; lo = hi = 0; e = -1; }
-            if (e < 0) hi = lo;
-            s.grp_row0[i] = lo;
-            s.grp_rows[i] = hi - lo;
-            s.grp_expert[i] = e;
-            s.grp_slot[i] = slot;
-            tiles = min((hi - lo + BM - 1) / BM, max_tiles + 1);
+        if (i < in.Gr) {
+            const SchedGroup g = sched_group(in, i);
+            bad_any |= g.bad;
+            if (WRITE) {
+                s.grp_row0[i] = g.lo;
+                s.grp_rows[i] = g.hi - g.lo;
+                s.grp_expert[i] = g.expert;
+                s.grp_slot[i] = g.slot;
+            }
+            tiles = min((g.hi - g.lo + BM - 1) / BM, in.max_tiles + 1);
         }
         int all;
         const int upto = block_scan256(tiles, sums, all);
-        if (tiles > 0 && carry + upto > max_tiles) bad_any = true;
-        if (i < Gr) s.tile_prefix[i + 1] = prefix[i + 1] = min(carry + upto, max_tiles);
-        carry = min(carry + all, max_tiles);
+        if (tiles > 0 && carry + upto > in.max_tiles) bad_any = true;
+        if (i < in.Gr) prefix[i + 1] = min(carry + upto, in.max_tiles);
+        carry = min(carry + all, in.max_tiles);
     }
-    if (bad_any) atomicOr(err_flag, RELIBRA_ERR_GROUP_TABLE);
-    const int total = carry;
-    if (tid == 0) s.hdr[0] = total;
+    if (WRITE && bad_any) atomicOr(in.err_flag, RELIBRA_ERR_GROUP_TABLE);
     __threadfence_block();
     __syncthreads();
+    return carry;
+}
+// Last group whose prefix <= t: the one that holds row tile t (0 <= t < prefix[Gr]).
+__device__ __forceinline__ int sched_group_of(const int32_t *prefix, int Gr, int t)
+{
+    int lo = 0, hi = Gr;
+    while (hi - lo > 1) {
+        const int mid = (lo + hi) >> 1;
+        if (prefix[mid] <= t) lo = mid; else hi = mid;
+    }
+    return lo;
+}
+
+// 256 threads.  Validates the group tables of [g_begin, g_end) (bad groups become empty and raise
+// the flag), lists the row tiles group by group, and lists the live replica slots.  The lists hold
+// max_tiles: enough for any table whose groups do not overlap; an overlapping one ends there, flagged.
+// prefix: Gr + 1 ints of LDS.
+__device__ __forceinline__ void sched_write(const SchedIn &in, const Sched &s, int32_t *prefix, int32_t *sums)
+{
+    const int tid = threadIdx.x, Gr = in.Gr;
+    const int total = sched_prefix<true>(in, s, prefix, sums);
+    if (tid == 0) s.hdr[0] = total;
+    for (int i = tid; i <= Gr; i += 256) s.tile_prefix[i] = prefix[i];
     for (int t = tid; t < total; t += 256) {
-        int lo = 0, hi = Gr;                 // last group whose prefix <= t
-        while (hi - lo > 1) {
-            const int mid = (lo + hi) >> 1;
-            if (prefix[mid] <= t) lo = mid; else hi = mid;
-        }
+        const int lo = sched_group_of(prefix, Gr, t);
         const int j = t - prefix[lo];
         s.tile_group[t] = lo;
         s.tile_row0[t] = s.grp_row0[lo] + j * BM;
@@ -169,11 +203,11 @@ sched_kernel(const int32_t *__restrict__ group_offset, const int32_t *__restrict
         s.tile_band[t] = (prefix[lo] + b0) | (min(kBand, m - b0) << 24);
     }
     // live replica slots, in group order (256 groups at a time)
-    carry = 0;
-    if (group_dw_slot) {
+    int carry = 0;
+    if (in.group_dw_slot) {
         for (int base = 0; base < Gr; base += 256) {
             const int i = base + tid;
-            const bool live = i < Gr && s.grp_expert[i] >= 0 && s.grp_slot[i] >= E;
+            const bool live = i < Gr && s.grp_expert[i] >= 0 && s.grp_slot[i] >= in.E;
             int all;
             const int at = carry + block_scan256(live ? 1 : 0, sums, all) - 1;
             if (live) {
@@ -184,6 +218,14 @@ sched_kernel(const int32_t *__restrict__ group_offset, const int32_t *__restrict
         }
     }
     if (tid == 0) s.hdr[1] = carry;
+}
+
+__global__ void __launch_bounds__(256)
+sched_kernel(SchedIn in, Sched s)
+{
+    extern __shared__ int32_t prefix[];        // [Gr + 1]
+    __shared__ int32_t sums[4];
+    sched_write(in, s, prefix, sums);
 }
 
 // ---------------------------------------------------------------- tile lookup
@@ -226,6 +268,51 @@ __device__ __forceinline__ RowTile find_row_tile(const Sched &s, int n_col_tiles
     t.rows = s.tile_rows[rt];
     t.expert = w_from_slot ? s.grp_slot[t.group] : s.grp_expert[t.group];   // index of the parameter block
     t.col0 = ct * col_tile_width;
+    return t;
+}
+
+// The k-loop's operand bases are scalar: says that the tile is the same in every lane, which the compiler cannot
+// see of values that came through LDS.
+__device__ __forceinline__ void make_uniform(RowTile &t)
+{
+    t.valid = __builtin_amdgcn_readfirstlane(t.valid ? 1 : 0) != 0;
+    t.group = __builtin_amdgcn_readfirstlane(t.group);
+    t.row0 = __builtin_amdgcn_readfirstlane(t.row0);
+    t.rows = __builtin_amdgcn_readfirstlane(t.rows);
+    t.expert = __builtin_amdgcn_readfirstlane(t.expert);
+    t.col0 = __builtin_amdgcn_readfirstlane(t.col0);
+}
+
+// The same from the caller's tables, for the first kernel of a call of few tiles: every block works out the part
+// of the schedule that it needs (one read of the groups and a scan, about as long as the chain of lookups above),
+// and the grid's last block, which has no tile, writes the tables for the kernels that follow.  Saves the
+// scheduling kernel and the gap behind it.  lds: 4 ints and Gr + 1 more, free again afterwards.
+__device__ __forceinline__ RowTile schedule_row_tile(const SchedIn &in, const Sched &s, int n_col_tiles, int col_tile_width, bool w_from_slot, char *lds)
+{
+    int32_t *sums = reinterpret_cast<int32_t *>(lds), *prefix = sums + 4;
+    RowTile t{};
+    if (blockIdx.x == gridDim.x - 1) {
+        sched_write(in, s, prefix, sums);
+        return t;
+    }
+    const int total = sched_prefix<false>(in, s, prefix, sums) * n_col_tiles;
+    const int per_xcd = (total + 7) >> 3;
+    const int logical = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+    t.valid = logical < total && (int)(blockIdx.x >> 3) < per_xcd;
+    if (t.valid) {
+        const int rt0 = logical / n_col_tiles, lo = sched_group_of(prefix, in.Gr, rt0);
+        const int m = prefix[lo + 1] - prefix[lo], b0 = (rt0 - prefix[lo]) / kBand * kBand;
+        const int first = prefix[lo] + b0, rows_here = min(kBand, m - b0);
+        const int within = logical - first * n_col_tiles;
+        const int ct = within / rows_here, j = b0 + within - ct * rows_here;
+        const SchedGroup g = sched_group(in, lo);
+        t.group = lo;
+        t.row0 = g.lo + j * BM;
+        t.rows = min(BM, g.hi - g.lo - j * BM);
+        t.expert = w_from_slot ? g.slot : g.expert;
+        t.col0 = ct * col_tile_width;
+    }
+    __syncthreads();                                          // the LDS goes to the operand slabs
     return t;
 }
 
@@ -423,10 +510,13 @@ __global__ void __launch_bounds__(AW == 128 ? THREADS : kWideRowWaves * 64, AW =
 fwd_gate_up_kernel(Sched s, const bf16_t *__restrict__ X, const int32_t *__restrict__ row_tok, int tok_last,
                    const bf16_t *__restrict__ Wg, const bf16_t *__restrict__ Wu, int h, int hff, int n_col_tiles,
                    bf16_t *__restrict__ Gt, bf16_t *__restrict__ U, bf16_t *__restrict__ Aout,
-                   const float *__restrict__ row_gate, bf16_t *__restrict__ Agout, int stream)
+                   const float *__restrict__ row_gate, bf16_t *__restrict__ Agout, int stream, SchedIn in)
 {
     extern __shared__ __attribute__((aligned(1024))) char lds[];
-    const RowTile t = find_row_tile(s, n_col_tiles, AW);
+    RowTile t;
+    if (AW == 128 && in.group_offset) t = schedule_row_tile(in, s, n_col_tiles, AW, false, lds);
+    else t = find_row_tile(s, n_col_tiles, AW);
+    if (AW == 128) make_uniform(t);
     if (!t.valid) return;
     if (t.rows > BM / 2) fwd_gate_up_body<BM, WT, AW>(t, X, row_tok, tok_last, Wg, Wu, h, hff, Gt, U, Aout, row_gate, Agout, stream != 0, lds);
     else fwd_gate_up_body<BM / 2, WT, AW>(t, X, row_tok, tok_last, Wg, Wu, h, hff, Gt, U, Aout, row_gate, Agout, stream != 0, lds);
@@ -608,10 +698,13 @@ template <bool WT, bool GATED = false, int AW = 256>
 __global__ void __launch_bounds__(AW == 256 ? THREADS : kWideRowWaves * 64, AW == 256 ? 2 : 1)
 bwd_act_kernel(Sched s, const bf16_t *__restrict__ dY, const bf16_t *__restrict__ Wd,
                const bf16_t *__restrict__ Gt, const bf16_t *__restrict__ U, int h, int hff, int n_col_tiles,
-               int w_from_slot, GateFusion gf, int stream)
+               int w_from_slot, GateFusion gf, int stream, SchedIn in)
 {
     extern __shared__ __attribute__((aligned(1024))) char lds[];
-    const RowTile t = find_row_tile(s, n_col_tiles, AW, w_from_slot != 0);
+    RowTile t;
+    if (AW == 256 && in.group_offset) t = schedule_row_tile(in, s, n_col_tiles, AW, w_from_slot != 0, lds);
+    else t = find_row_tile(s, n_col_tiles, AW, w_from_slot != 0);
+    if (AW == 256) make_uniform(t);
     if (!t.valid) return;
     const bf16_t *W = Wd + (size_t)t.expert * h * hff;      // (n in h', k in h) at [k*h' + n], or at [n*h + k]
     const int ldw = WT ? h : hff;
@@ -1294,6 +1387,18 @@ static inline bool row_tiles_wide(int n_dim, int width, int n_rows, int groups, 
     return n_dim >= width && 2 * wide == narrow && row_tiles * narrow > kComputeUnits && full;
 }
 
+static int launch_sched(const SchedIn &in, const Sched &s, hipStream_t stream)
+{
+    RELIBRA_LAUNCH(RELIBRA_K_SCHED, stream, sched_kernel<<<1, 256, (size_t)(in.Gr + 1) * sizeof(int32_t), stream>>>(in, s));
+    RELIBRA_HIP_TRY(launch_check());
+    return RELIBRA_OK;
+}
+// Whether the first kernel of a call works the schedule out itself: where all of its blocks (at most `tiles`) run at
+// once, two to a compute unit, each does so beside the others; with more rounds it would be done once per round.
+// Training steps with the scheduling kernel -> without: 8 experts of 128 x 256, 512 tokens (two calls) 112 -> 104 us; 16
+// of 256 x 192, 3 x 777 tokens (six calls) 263 -> 251.
+static inline bool schedules_itself(bool wide, long long tiles) { return !wide && tiles + 8 <= 2 * kComputeUnits; }
+
 // Whether a row kernel's results (`width` bf16 values a row) leave with a streaming hint: the kernel does not read
 // them again, and in the L2s they push out operands that other tiles still read (a third of the operand bytes
 // miss there, and those set the pace of the k-loop).  Where they fit the eight L2s (4 MiB each) together the
@@ -1343,15 +1448,18 @@ static int ffn_fwd_impl(const void *Xrows, const int32_t *row_tok, int T, int n_
     if (ws_bytes < ffn_ws_bytes(n_rows, Gr, hff, false)) return RELIBRA_EWORKSPACE;
     if (int rc = ensure_lds_limits()) return rc;
     Sched s = carve(ws, n_rows, Gr, hff, false);
-    RELIBRA_LAUNCH(RELIBRA_K_SCHED, stream, sched_kernel<<<1, 256, (size_t)(Gr + 1) * sizeof(int32_t), stream>>>(group_offset, group_expert, nullptr, g_begin, Gr, n_rows, E, 0,
-                                                                                                    max_row_tiles(n_rows, Gr), s, err_flag));
-    RELIBRA_HIP_TRY(launch_check());
     const long long R = max_row_tiles(n_rows, Gr);
     const bool wide1 = row_tiles_wide(hff, 256, n_rows, Gr, 2 * h), wide2 = row_tiles_wide(h, 512, n_rows, Gr, hff);
     const int ct1 = wide1 ? (hff + 255) / 256 : (hff + 127) / 128, ct2 = wide2 ? (h + 511) / 512 : (h + 255) / 256;
-    RELIBRA_ROW_LAUNCH(RELIBRA_K_FWD_GATE_UP, fwd_gate_up_kernel, wt, wide1, 128, 256, R * ct1,
+    SchedIn in{group_offset, group_expert, nullptr, g_begin, Gr, n_rows, E, 0, (int)R, err_flag};
+    const bool inside = schedules_itself(wide1, R * ct1);
+    if (!inside) {
+        if (int rc = launch_sched(in, s, stream)) return rc;
+        in.group_offset = nullptr;
+    }
+    RELIBRA_ROW_LAUNCH(RELIBRA_K_FWD_GATE_UP, fwd_gate_up_kernel, wt, wide1, 128, 256, R * ct1 + (inside ? 8 : 0),
                        s, (const bf16_t *)Xrows, row_tok, T - 1, (const bf16_t *)Wg, (const bf16_t *)Wu, h, hff, ct1,
-                       (bf16_t *)Gt_save, (bf16_t *)U_save, (bf16_t *)A_save, row_gate, (bf16_t *)Ag_save, streams_rows(n_rows, 3 * hff));
+                       (bf16_t *)Gt_save, (bf16_t *)U_save, (bf16_t *)A_save, row_gate, (bf16_t *)Ag_save, streams_rows(n_rows, 3 * hff), in);
     RELIBRA_HIP_TRY(launch_check());
     RELIBRA_ROW_LAUNCH(RELIBRA_K_FWD_DOWN, fwd_down_kernel, wt, wide2, 256, 512, R * ct2,
                        s, (const bf16_t *)A_save, (const bf16_t *)Wd, h, hff, ct2, (bf16_t *)Yrows, streams_rows(n_rows, h));
@@ -1471,14 +1579,18 @@ static int ffn_bwd_impl(const void *dYrows, const void *Xrows,
     Sched s = carve(ws, n_rows, Gr, hff, true);
     // the slot table matters only to kernels that write dW or read replica parameters
     const int32_t *slot_table = (defer && !(flags & RELIBRA_BWD_REPLICA_WEIGHTS)) ? nullptr : group_dw_slot;
-    RELIBRA_LAUNCH(RELIBRA_K_SCHED, stream, sched_kernel<<<1, 256, (size_t)(Gr + 1) * sizeof(int32_t), stream>>>(group_offset, group_expert, slot_table, g_begin, Gr, n_rows, E,
-                                        n_dw_slots, max_row_tiles(n_rows, Gr), s, err_flag));
-    RELIBRA_HIP_TRY(launch_check());
     const long long R = max_row_tiles(n_rows, Gr);
     const bool wide_h = row_tiles_wide(h, 512, n_rows, Gr, 2 * hff);
     // (the activation backward on transposed weight copies keeps whole tiles: its partial gate sums belong to columns)
     const bool wide_ff = row_tiles_wide(hff, 512, n_rows, Gr, h) && (hff % 512 == 0 || !(flags & RELIBRA_BWD_TRANSPOSED_WEIGHTS));
     const int ct_ff = wide_ff ? (hff + 511) / 512 : (hff + 255) / 256, ct_h = wide_h ? (h + 511) / 512 : (h + 255) / 256;
+    SchedIn in{group_offset, group_expert, slot_table, g_begin, Gr, n_rows, E, n_dw_slots, (int)R, err_flag};
+    const bool inside = n_rows > 0 && schedules_itself(wide_ff, R * ct_ff);
+    if (!inside) {
+        if (int rc = launch_sched(in, s, stream)) return rc;
+        in.group_offset = nullptr;
+    }
+    const long long act_blocks = R * ct_ff + (inside ? 8 : 0);
     const int accumulate = (flags & RELIBRA_BWD_ACCUMULATE) ? 1 : 0;
     const int w_from_slot = (flags & RELIBRA_BWD_REPLICA_WEIGHTS) ? 1 : 0;
     if (n_rows > 0) {
@@ -1495,10 +1607,10 @@ static int ffn_bwd_impl(const void *dYrows, const void *Xrows,
         }
 #define RELIBRA_BWD_ACT(WT_, GATED_)                                                                                              \
     do {                                                                                                                          \
-        if (wide_ff) RELIBRA_LAUNCH(RELIBRA_K_BWD_ACT, stream, (bwd_act_kernel<WT_, GATED_, 512><<<grid8(R * ct_ff), kWideRowWaves * 64, kLdsBytesWide, stream>>>( \
-            s, dy, wd, gt, us, h, hff, ct_ff, w_from_slot, gf, streams_rows(n_rows, 2 * hff))));                                                                 \
-        else RELIBRA_LAUNCH(RELIBRA_K_BWD_ACT, stream, (bwd_act_kernel<WT_, GATED_, 256><<<grid8(R * ct_ff), THREADS, kLdsBytes, stream>>>(         \
-            s, dy, wd, gt, us, h, hff, ct_ff, w_from_slot, gf, streams_rows(n_rows, 2 * hff))));                                                                 \
+        if (wide_ff) RELIBRA_LAUNCH(RELIBRA_K_BWD_ACT, stream, (bwd_act_kernel<WT_, GATED_, 512><<<grid8(act_blocks), kWideRowWaves * 64, kLdsBytesWide, stream>>>( \
+            s, dy, wd, gt, us, h, hff, ct_ff, w_from_slot, gf, streams_rows(n_rows, 2 * hff), in)));                                                                 \
+        else RELIBRA_LAUNCH(RELIBRA_K_BWD_ACT, stream, (bwd_act_kernel<WT_, GATED_, 256><<<grid8(act_blocks), THREADS, kLdsBytes, stream>>>(         \
+            s, dy, wd, gt, us, h, hff, ct_ff, w_from_slot, gf, streams_rows(n_rows, 2 * hff), in)));                                                                 \
     } while (0)
         if (wt) { if (gb) RELIBRA_BWD_ACT(true, true); else RELIBRA_BWD_ACT(true, false); }
         else { if (gb) RELIBRA_BWD_ACT(false, true); else RELIBRA_BWD_ACT(false, false); }

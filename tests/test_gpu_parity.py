@@ -402,6 +402,61 @@ def test_ffn_row_tiles_of_overlapping_groups_end_with_the_lists():
     assert (ws[need:] == 99).all()
 
 
+def _fwd_bwd(X, dY, W, counts, E, g_begin=0, g_end=None, out=None):
+    """Forward and data gradients of groups of the given sizes (experts in turn); out: earlier results to write a range into."""
+    go = dev_i32(np.concatenate([[0], np.cumsum(counts)]))
+    ge = dev_i32(np.arange(len(counts)) % E)
+    N, h, hff = X.shape[0], X.shape[1], W[0].shape[1]
+    if out is None:
+        out = [torch.full((N, w), 3.0, dtype=torch.bfloat16, device=DEV) for w in (hff, hff, hff, h, h)]
+    Gt, U, A, Y, dX = out
+    err = rl.new_err_flag()
+    rl.relibra_moe_ffn_fwd(X, go, ge, *W, g_begin=g_begin, g_end=g_end, Gt=Gt, U=U, A=A, Yrows=Y, err_flag=err)
+    rl.relibra_moe_ffn_bwd(dY, None, Gt, U, A, go, ge, ge, *W, None, None, None, g_begin=g_begin, g_end=g_end, flags=rl.BWD_DEFER_WGRAD,
+                           dXrows=dX, err_flag=err, E=E)
+    assert err.item() == 0
+    return out
+
+
+def _device_case(N, E, h, hff):
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(N + h)
+    draw = lambda std, *s: torch.empty(s, dtype=torch.bfloat16, device=DEV).normal_(0.0, std, generator=gen)
+    return draw(1.0, N, h), draw(1.0, N, h), [draw(0.05, E, hff, h), draw(0.05, E, hff, h), draw(0.05, E, h, hff)]
+
+
+@pytest.mark.parametrize("groups", [1, 251, 252, 253, 300])
+def test_schedule_inside_the_first_kernel_equals_the_scheduling_kernel(groups):
+    """Groups of up to 128 rows count as two row tiles each in the bound: 252 of them are the most that are scheduled
+    inside.  The same rows range by range (always inside) must come out bit for bit the same."""
+    counts = np.full(groups, 128)
+    counts[::7] = 0
+    counts[3::11] = 65
+    X, dY, W = _device_case(int(128 * groups), 3, 64, 64)
+    whole = _fwd_bwd(X, dY, W, counts, 3)
+    parts = None
+    for lo in range(0, groups, 100):
+        parts = _fwd_bwd(X, dY, W, counts, 3, lo, min(lo + 100, groups), parts)
+    for a, b in zip(whole, parts):
+        assert torch.equal(a, b)
+    end = int(counts.sum())
+    if end:
+        want = torch.nn.functional.silu(X[:int(counts[0] or counts[1])].float() @ W[0][0 if counts[0] else 1].float().T)
+        want = want * (X[:want.shape[0]].float() @ W[1][0 if counts[0] else 1].float().T)
+        assert rel_l2(whole[2][:want.shape[0]], want.cpu().numpy()) <= TOL
+
+
+@pytest.mark.parametrize("h,hff,rows", [(1024, 64, 16384), (64, 1024, 5376), (64, 1024, 8192)])
+def test_streamed_results_equal_the_others(h, hff, rows):
+    """Results of more than 32 MiB a kernel are stored with a streaming hint: Y and dX from 16385 rows of 1024 values on, Gt, U
+    and A from 5462, dGt and dU from 8193.  128 more rows must not change the others."""
+    X, dY, W = _device_case(rows + 128, 3, h, hff)
+    more = _fwd_bwd(X, dY, W, np.full(rows // 128 + 1, 128), 3)
+    fewer = _fwd_bwd(X[:rows].contiguous(), dY[:rows].contiguous(), W, np.full(rows // 128, 128), 3)
+    for a, b in zip(more, fewer):
+        assert torch.equal(a[:rows], b)
+
+
 # ------------------------------------------------------------------ combine
 @pytest.mark.parametrize("T,k,h", [(97, 4, 256), (5, 1, 8), (300, 8, 2048)])
 def test_combine_modes(T, k, h):
