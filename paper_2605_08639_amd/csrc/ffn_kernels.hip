@@ -358,28 +358,23 @@ struct WaveStage {
     // All LDS reads first, then the (predicated) stores: left to itself the compiler moves every
     // read into the branch of its store, and each store then waits for its own read in turn.
     // Only columns col_from <= c < n_dim are stored.
-    // stream: with a streaming hint (streams_rows).
     static __device__ __forceinline__ void flush(const char *buf, bf16_t *out, int ld, int grow0, int row_end,
-                                                 int gcol0, int n_dim, int lane, bool stream, int col_from = 0)
+                                                 int gcol0, int n_dim, int lane, int col_from = 0)
     {
-        typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
-        u32x4_t v[PASSES];
+        uint4 v[PASSES];
 #pragma unroll
         for (int p = 0; p < PASSES; ++p) {
             const int r = p * ROWS_PER_PASS + lane / PIECES, piece = lane % PIECES;
-            v[p] = *reinterpret_cast<const u32x4_t *>(buf + r * (NCOLS * 2) + (((piece ^ r) & (PIECES - 1)) << 4));
+            v[p] = *reinterpret_cast<const uint4 *>(buf + r * (NCOLS * 2) + (((piece ^ r) & (PIECES - 1)) << 4));
         }
 #pragma unroll
         for (int p = 0; p < PASSES; ++p)          // the values are needed here: the reads stay above
-            asm volatile("" : "+v"(v[p]));
+            asm volatile("" : "+v"(v[p].x), "+v"(v[p].y), "+v"(v[p].z), "+v"(v[p].w));
 #pragma unroll
         for (int p = 0; p < PASSES; ++p) {
             const int r = p * ROWS_PER_PASS + lane / PIECES, piece = lane % PIECES;
-            if (grow0 + r < row_end && gcol0 + piece * 8 < n_dim && gcol0 + piece * 8 >= col_from) {
-                u32x4_t *to = reinterpret_cast<u32x4_t *>(out + (size_t)(grow0 + r) * ld + gcol0 + piece * 8);
-                if (stream) __builtin_nontemporal_store(v[p], to);
-                else *to = v[p];
-            }
+            if (grow0 + r < row_end && gcol0 + piece * 8 < n_dim && gcol0 + piece * 8 >= col_from)
+                *reinterpret_cast<uint4 *>(out + (size_t)(grow0 + r) * ld + gcol0 + piece * 8) = v[p];
         }
     }
     // global -> stage.  Rows and columns beyond the tensor are read from clamped (valid) addresses
@@ -448,7 +443,7 @@ template <int BB, bool WT, int AW = 128>
 __device__ __forceinline__ void fwd_gate_up_body(const RowTile &t, const bf16_t *X, const int32_t *row_tok, int tok_last,
                                                  const bf16_t *Wg, const bf16_t *Wu,
                                                  int h, int hff, bf16_t *Gt, bf16_t *U, bf16_t *Aout,
-                                                 const float *row_gate, bf16_t *Agout, bool stream, char *lds)
+                                                 const float *row_gate, bf16_t *Agout, char *lds)
 {
     constexpr int NWV = AW == 128 ? NWAVES : kWideRowWaves;
     using WV = Waves<BB, NWV>;
@@ -499,7 +494,7 @@ __device__ __forceinline__ void fwd_gate_up_body(const RowTile &t, const bf16_t 
                     ST::put(buf, tb * 32 + (lane & 31), ta * 32 + q * 8 + (lane >> 5) * 4, pack4bf(v[0], v[1], v[2], v[3]));
                 }
         wave_lds_fence();
-        ST::flush(buf, which == 0 ? Gt : which == 1 ? U : which == 2 ? Aout : Agout, hff, wrow0, row_end, wcol0, hff, lane, stream, t.col0);
+        ST::flush(buf, which == 0 ? Gt : which == 1 ? U : which == 2 ? Aout : Agout, hff, wrow0, row_end, wcol0, hff, lane, t.col0);
         wave_lds_fence();
     }
 }
@@ -510,7 +505,7 @@ __global__ void __launch_bounds__(AW == 128 ? THREADS : kWideRowWaves * 64, AW =
 fwd_gate_up_kernel(Sched s, const bf16_t *__restrict__ X, const int32_t *__restrict__ row_tok, int tok_last,
                    const bf16_t *__restrict__ Wg, const bf16_t *__restrict__ Wu, int h, int hff, int n_col_tiles,
                    bf16_t *__restrict__ Gt, bf16_t *__restrict__ U, bf16_t *__restrict__ Aout,
-                   const float *__restrict__ row_gate, bf16_t *__restrict__ Agout, int stream, SchedIn in)
+                   const float *__restrict__ row_gate, bf16_t *__restrict__ Agout, SchedIn in)
 {
     extern __shared__ __attribute__((aligned(1024))) char lds[];
     RowTile t;
@@ -518,8 +513,8 @@ fwd_gate_up_kernel(Sched s, const bf16_t *__restrict__ X, const int32_t *__restr
     else t = find_row_tile(s, n_col_tiles, AW);
     if (AW == 128) make_uniform(t);
     if (!t.valid) return;
-    if (t.rows > BM / 2) fwd_gate_up_body<BM, WT, AW>(t, X, row_tok, tok_last, Wg, Wu, h, hff, Gt, U, Aout, row_gate, Agout, stream != 0, lds);
-    else fwd_gate_up_body<BM / 2, WT, AW>(t, X, row_tok, tok_last, Wg, Wu, h, hff, Gt, U, Aout, row_gate, Agout, stream != 0, lds);
+    if (t.rows > BM / 2) fwd_gate_up_body<BM, WT, AW>(t, X, row_tok, tok_last, Wg, Wu, h, hff, Gt, U, Aout, row_gate, Agout, lds);
+    else fwd_gate_up_body<BM / 2, WT, AW>(t, X, row_tok, tok_last, Wg, Wu, h, hff, Gt, U, Aout, row_gate, Agout, lds);
 }
 
 // Gate-side fusion of the activation backward (EPI = 2).  With the upstream gradient of row r
@@ -542,7 +537,7 @@ struct GateFusion {
 template <int BB, bool W_KS, int NPH, int EPI, int AW = 256>
 __device__ __forceinline__ void row_gemm_body(const RowTile &t, const bf16_t *P0, const bf16_t *P1, int ldp,
                                               const bf16_t *W0, const bf16_t *W1, int ldw, int n_dim, int k_dim,
-                                              bf16_t *out0, bf16_t *out1, const bf16_t *Gt, const bf16_t *U, bool stream, char *lds,
+                                              bf16_t *out0, bf16_t *out1, const bf16_t *Gt, const bf16_t *U, char *lds,
                                               const GateFusion &gf = GateFusion{})
 {
     constexpr int NWV = AW == 256 ? NWAVES : kWideRowWaves;
@@ -585,7 +580,7 @@ __device__ __forceinline__ void row_gemm_body(const RowTile &t, const bf16_t *P0
                             pack4bf(acc[ta / KL::TA][ta % KL::TA][tb][q * 4], acc[ta / KL::TA][ta % KL::TA][tb][q * 4 + 1],
                                     acc[ta / KL::TA][ta % KL::TA][tb][q * 4 + 2], acc[ta / KL::TA][ta % KL::TA][tb][q * 4 + 3]));
         wave_lds_fence();
-        ST::flush(buf, out0, n_dim, wrow0, row_end, wcol0, n_dim, lane, stream, t.col0);
+        ST::flush(buf, out0, n_dim, wrow0, row_end, wcol0, n_dim, lane, t.col0);
     } else {
         // dA (in the accumulators) -> dGt, dU, half of the wave's columns at a time: Gt and U come
         // in through two staging areas and are overwritten in place by dGt and dU.
@@ -645,8 +640,8 @@ __device__ __forceinline__ void row_gemm_body(const RowTile &t, const bf16_t *P0
                         }
                     }
             wave_lds_fence();
-            SH::flush(buf_g, out0, n_dim, wrow0, row_end, hcol0, n_dim, lane, stream);
-            SH::flush(buf_u, out1, n_dim, wrow0, row_end, hcol0, n_dim, lane, stream);
+            SH::flush(buf_g, out0, n_dim, wrow0, row_end, hcol0, n_dim, lane);
+            SH::flush(buf_u, out1, n_dim, wrow0, row_end, hcol0, n_dim, lane);
             wave_lds_fence();
             if (EPI == 2 && hcol0 < n_dim) {
 #pragma unroll
@@ -678,15 +673,15 @@ __device__ __forceinline__ void row_gemm_body(const RowTile &t, const bf16_t *P0
 template <bool WT, int AW = 256>
 __global__ void __launch_bounds__(AW == 256 ? THREADS : kWideRowWaves * 64, AW == 256 ? 2 : 1)
 fwd_down_kernel(Sched s, const bf16_t *__restrict__ Ain, const bf16_t *__restrict__ Wd, int h, int hff,
-                int n_col_tiles, bf16_t *__restrict__ Y, int stream)
+                int n_col_tiles, bf16_t *__restrict__ Y)
 {
     extern __shared__ __attribute__((aligned(1024))) char lds[];
     const RowTile t = find_row_tile(s, n_col_tiles, AW);
     if (!t.valid) return;
     const bf16_t *W = Wd + (size_t)t.expert * h * hff;
     const int ldw = WT ? h : hff;                             // (n in h, k in h') at [n*h' + k], or at [k*h + n]
-    if (t.rows > BM / 2) row_gemm_body<BM, WT, 1, 0, AW>(t, Ain, nullptr, hff, W, nullptr, ldw, h, hff, Y, nullptr, nullptr, nullptr, stream != 0, lds);
-    else row_gemm_body<BM / 2, WT, 1, 0, AW>(t, Ain, nullptr, hff, W, nullptr, ldw, h, hff, Y, nullptr, nullptr, nullptr, stream != 0, lds);
+    if (t.rows > BM / 2) row_gemm_body<BM, WT, 1, 0, AW>(t, Ain, nullptr, hff, W, nullptr, ldw, h, hff, Y, nullptr, nullptr, nullptr, lds);
+    else row_gemm_body<BM / 2, WT, 1, 0, AW>(t, Ain, nullptr, hff, W, nullptr, ldw, h, hff, Y, nullptr, nullptr, nullptr, lds);
 }
 
 // ---------------------------------------------------------------- backward
@@ -698,7 +693,7 @@ template <bool WT, bool GATED = false, int AW = 256>
 __global__ void __launch_bounds__(AW == 256 ? THREADS : kWideRowWaves * 64, AW == 256 ? 2 : 1)
 bwd_act_kernel(Sched s, const bf16_t *__restrict__ dY, const bf16_t *__restrict__ Wd,
                const bf16_t *__restrict__ Gt, const bf16_t *__restrict__ U, int h, int hff, int n_col_tiles,
-               int w_from_slot, GateFusion gf, int stream, SchedIn in)
+               int w_from_slot, GateFusion gf, SchedIn in)
 {
     extern __shared__ __attribute__((aligned(1024))) char lds[];
     RowTile t;
@@ -709,8 +704,8 @@ bwd_act_kernel(Sched s, const bf16_t *__restrict__ dY, const bf16_t *__restrict_
     const bf16_t *W = Wd + (size_t)t.expert * h * hff;      // (n in h', k in h) at [k*h' + n], or at [n*h + k]
     const int ldw = WT ? h : hff;
     constexpr int EPI = GATED ? 2 : 1;
-    if (t.rows > BM / 2) row_gemm_body<BM, !WT, 1, EPI, AW>(t, dY, nullptr, h, W, nullptr, ldw, hff, h, s.dGt, s.dU, Gt, U, stream != 0, lds, gf);
-    else row_gemm_body<BM / 2, !WT, 1, EPI, AW>(t, dY, nullptr, h, W, nullptr, ldw, hff, h, s.dGt, s.dU, Gt, U, stream != 0, lds, gf);
+    if (t.rows > BM / 2) row_gemm_body<BM, !WT, 1, EPI, AW>(t, dY, nullptr, h, W, nullptr, ldw, hff, h, s.dGt, s.dU, Gt, U, lds, gf);
+    else row_gemm_body<BM / 2, !WT, 1, EPI, AW>(t, dY, nullptr, h, W, nullptr, ldw, hff, h, s.dGt, s.dU, Gt, U, lds, gf);
 }
 
 // dgate of the gate-fused backward: the partial row sums of the activation backward added up in
@@ -742,15 +737,15 @@ dgate_reduce_kernel(const float *__restrict__ part, int n_slots, int n_rows, con
 template <bool WT, int AW = 256>
 __global__ void __launch_bounds__(AW == 256 ? THREADS : kWideRowWaves * 64, AW == 256 ? 2 : 1)
 bwd_dx_kernel(Sched s, const bf16_t *__restrict__ Wg, const bf16_t *__restrict__ Wu, int h, int hff,
-              int n_col_tiles, int w_from_slot, bf16_t *__restrict__ dX, int stream)
+              int n_col_tiles, int w_from_slot, bf16_t *__restrict__ dX)
 {
     extern __shared__ __attribute__((aligned(1024))) char lds[];
     const RowTile t = find_row_tile(s, n_col_tiles, AW, w_from_slot != 0);
     if (!t.valid) return;
     const size_t wofs = (size_t)t.expert * hff * h;         // (n in h, k in h') at [k*h + n], or at [n*h' + k]
     const int ldw = WT ? hff : h;
-    if (t.rows > BM / 2) row_gemm_body<BM, !WT, 2, 0, AW>(t, s.dGt, s.dU, hff, Wg + wofs, Wu + wofs, ldw, h, hff, dX, nullptr, nullptr, nullptr, stream != 0, lds);
-    else row_gemm_body<BM / 2, !WT, 2, 0, AW>(t, s.dGt, s.dU, hff, Wg + wofs, Wu + wofs, ldw, h, hff, dX, nullptr, nullptr, nullptr, stream != 0, lds);
+    if (t.rows > BM / 2) row_gemm_body<BM, !WT, 2, 0, AW>(t, s.dGt, s.dU, hff, Wg + wofs, Wu + wofs, ldw, h, hff, dX, nullptr, nullptr, nullptr, lds);
+    else row_gemm_body<BM / 2, !WT, 2, 0, AW>(t, s.dGt, s.dU, hff, Wg + wofs, Wu + wofs, ldw, h, hff, dX, nullptr, nullptr, nullptr, lds);
 }
 
 // Transposed copy of per-expert matrices, out[e][j][i] = in[e][i][j]: 128 x 128 tiles through LDS, 16-byte
@@ -1399,15 +1394,6 @@ static int launch_sched(const SchedIn &in, const Sched &s, hipStream_t stream)
 // of 256 x 192, 3 x 777 tokens (six calls) 263 -> 251.
 static inline bool schedules_itself(bool wide, long long tiles) { return !wide && tiles + 8 <= 2 * kComputeUnits; }
 
-// Whether a row kernel's results (`width` bf16 values a row) leave with a streaming hint: the kernel does not read
-// them again, and in the L2s they push out operands that other tiles still read (a third of the operand bytes
-// miss there, and those set the pace of the k-loop).  Where they fit the eight L2s (4 MiB each) together the
-// next kernel finds them there instead.  Without -> with, us: gate/up of 144 groups (65536 rows, 2048 x 768)
-// 467 -> 459, down 266 -> 263, dA 305 -> 300; of 133 experts of 7168 x 2048 (32768 rows) gate/up 2541 -> 2490, down
-// 1345 -> 1328; whole training steps 0.2 to 0.6 %.  Whole calls whose tensors fit, hinted all the same: a training step of 16 experts of 256 x 192 264 -> 275, a forward
-// pass of 2048 rows, 2048 x 768, 221 -> 228.
-static inline int streams_rows(int n_rows, int width) { return (size_t)n_rows * width * sizeof(bf16_t) > ((size_t)32 << 20) ? 1 : 0; }
-
 // Launch of a row-tiled GEMM kernel template <bool WT, int AW>: narrow (four waves, two workgroups
 // per compute unit) or wide (eight waves, one) column tiles.
 #define RELIBRA_ROW_LAUNCH(kid, kern, wt_, wide_, AWN, AWW, tiles, ...)                                                      \
@@ -1459,10 +1445,10 @@ static int ffn_fwd_impl(const void *Xrows, const int32_t *row_tok, int T, int n_
     }
     RELIBRA_ROW_LAUNCH(RELIBRA_K_FWD_GATE_UP, fwd_gate_up_kernel, wt, wide1, 128, 256, R * ct1 + (inside ? 8 : 0),
                        s, (const bf16_t *)Xrows, row_tok, T - 1, (const bf16_t *)Wg, (const bf16_t *)Wu, h, hff, ct1,
-                       (bf16_t *)Gt_save, (bf16_t *)U_save, (bf16_t *)A_save, row_gate, (bf16_t *)Ag_save, streams_rows(n_rows, 3 * hff), in);
+                       (bf16_t *)Gt_save, (bf16_t *)U_save, (bf16_t *)A_save, row_gate, (bf16_t *)Ag_save, in);
     RELIBRA_HIP_TRY(launch_check());
     RELIBRA_ROW_LAUNCH(RELIBRA_K_FWD_DOWN, fwd_down_kernel, wt, wide2, 256, 512, R * ct2,
-                       s, (const bf16_t *)A_save, (const bf16_t *)Wd, h, hff, ct2, (bf16_t *)Yrows, streams_rows(n_rows, h));
+                       s, (const bf16_t *)A_save, (const bf16_t *)Wd, h, hff, ct2, (bf16_t *)Yrows);
     RELIBRA_HIP_TRY(launch_check());
     return RELIBRA_OK;
 }
@@ -1608,18 +1594,18 @@ static int ffn_bwd_impl(const void *dYrows, const void *Xrows,
 #define RELIBRA_BWD_ACT(WT_, GATED_)                                                                                              \
     do {                                                                                                                          \
         if (wide_ff) RELIBRA_LAUNCH(RELIBRA_K_BWD_ACT, stream, (bwd_act_kernel<WT_, GATED_, 512><<<grid8(act_blocks), kWideRowWaves * 64, kLdsBytesWide, stream>>>( \
-            s, dy, wd, gt, us, h, hff, ct_ff, w_from_slot, gf, streams_rows(n_rows, 2 * hff), in)));                                                                 \
+            s, dy, wd, gt, us, h, hff, ct_ff, w_from_slot, gf, in)));                                                                 \
         else RELIBRA_LAUNCH(RELIBRA_K_BWD_ACT, stream, (bwd_act_kernel<WT_, GATED_, 256><<<grid8(act_blocks), THREADS, kLdsBytes, stream>>>(         \
-            s, dy, wd, gt, us, h, hff, ct_ff, w_from_slot, gf, streams_rows(n_rows, 2 * hff), in)));                                                                 \
+            s, dy, wd, gt, us, h, hff, ct_ff, w_from_slot, gf, in)));                                                                 \
     } while (0)
         if (wt) { if (gb) RELIBRA_BWD_ACT(true, true); else RELIBRA_BWD_ACT(true, false); }
         else { if (gb) RELIBRA_BWD_ACT(false, true); else RELIBRA_BWD_ACT(false, false); }
 #undef RELIBRA_BWD_ACT
         RELIBRA_HIP_TRY(launch_check());
         if (wt) RELIBRA_ROW_LAUNCH(RELIBRA_K_BWD_DX, bwd_dx_kernel, true, wide_h, 256, 512, R * ct_h,
-                                   s, wg, wu, h, hff, ct_h, w_from_slot, (bf16_t *)dXrows, streams_rows(n_rows, h));
+                                   s, wg, wu, h, hff, ct_h, w_from_slot, (bf16_t *)dXrows);
         else RELIBRA_ROW_LAUNCH(RELIBRA_K_BWD_DX, bwd_dx_kernel, false, wide_h, 256, 512, R * ct_h,
-                                s, wg, wu, h, hff, ct_h, w_from_slot, (bf16_t *)dXrows, streams_rows(n_rows, h));
+                                s, wg, wu, h, hff, ct_h, w_from_slot, (bf16_t *)dXrows);
         RELIBRA_HIP_TRY(launch_check());
         if (gb) {
             RELIBRA_LAUNCH(RELIBRA_K_DGATE_REDUCE, stream, dgate_reduce_kernel<<<std::min(1024, (n_rows + 255) / 256), 256, 0, stream>>>(

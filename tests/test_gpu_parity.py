@@ -447,9 +447,9 @@ def test_schedule_inside_the_first_kernel_equals_the_scheduling_kernel(groups):
 
 
 @pytest.mark.parametrize("h,hff,rows", [(1024, 64, 16384), (64, 1024, 5376), (64, 1024, 8192)])
-def test_streamed_results_equal_the_others(h, hff, rows):
-    """Results of more than 32 MiB a kernel are stored with a streaming hint: Y and dX from 16385 rows of 1024 values on, Gt, U
-    and A from 5462, dGt and dU from 8193.  128 more rows must not change the others."""
+def test_more_rows_do_not_change_the_others(h, hff, rows):
+    """128 more rows, up to which the results of a kernel fit the L2s (32 MiB) and beyond which they do not, must not change
+    the others."""
     X, dY, W = _device_case(rows + 128, 3, h, hff)
     more = _fwd_bwd(X, dY, W, np.full(rows // 128 + 1, 128), 3)
     fewer = _fwd_bwd(X[:rows].contiguous(), dY[:rows].contiguous(), W, np.full(rows // 128, 128), 3)
