@@ -388,16 +388,32 @@ def test_ffn_flags_inconsistent_group_tables_without_faulting():
     assert err.item() & rl.ERR_GROUP_TABLE
 
 
-def test_ffn_row_tiles_of_overlapping_groups_end_with_the_lists():
+class _ScheduleLaunches:
+    """The calls inside launch the scheduling kernel this many times (each call without it schedules in its first kernel)."""
+
+    def __init__(self, launches):
+        self.launches = launches
+
+    def __enter__(self):
+        rl.prof_start(2, 256)
+
+    def __exit__(self, kind, *_):
+        seen = rl.prof_stop().get("sched", (0.0, 0))[1]
+        assert kind is not None or seen == self.launches
+
+
+@pytest.mark.parametrize("rows", [1024, 65536])                       # scheduled inside the first kernel, by the scheduling kernel
+def test_ffn_row_tiles_of_overlapping_groups_end_with_the_lists(rows):
     """A corrupted table whose groups cover the same rows again and again has more row tiles than the workspace lists
     (which hold those of every table without overlap): flagged, and nothing is written behind the workspace."""
-    rows, groups = 1024, 64
+    groups = 64
     X, _, Wg, Wu, Wd = ffn_case(seed=12, E=2, h=64, hff=64, rows=(rows,), experts=(0,))[2:]
     go, ge = dev_i32(np.array([0, rows] * (groups // 2) + [0], np.int32)), dev_i32(np.arange(groups) % 2)
     need, guard = rl.workspace_bytes(rl.WS_FFN_FWD, rows, 1, 2, groups, 64, 64), 1 << 16
     ws = torch.full((need + guard,), 99, dtype=torch.uint8, device=DEV)
     err = rl.new_err_flag()
-    rl.relibra_moe_ffn_fwd(X.to(DEV), go, ge, Wg.to(DEV), Wu.to(DEV), Wd.to(DEV), workspace=ws[:need], err_flag=err)
+    with _ScheduleLaunches(0 if rows == 1024 else 1):
+        rl.relibra_moe_ffn_fwd(X.to(DEV), go, ge, Wg.to(DEV), Wu.to(DEV), Wd.to(DEV), workspace=ws[:need], err_flag=err)
     assert err.item() == rl.ERR_GROUP_TABLE
     assert (ws[need:] == 99).all()
 
@@ -425,25 +441,110 @@ def _device_case(N, E, h, hff):
     return draw(1.0, N, h), draw(1.0, N, h), [draw(0.05, E, hff, h), draw(0.05, E, hff, h), draw(0.05, E, h, hff)]
 
 
+SPARE_ROWS = 65536      # a buffer of so many rows may hold more than 504 row tiles, whatever its groups: the scheduling kernel's
+
+
+def _with_spare_rows(t):
+    return torch.cat([t, t.new_zeros((SPARE_ROWS - t.shape[0],) + t.shape[1:])])
+
+
 @pytest.mark.parametrize("groups", [1, 251, 252, 253, 300])
 def test_schedule_inside_the_first_kernel_equals_the_scheduling_kernel(groups):
     """Groups of up to 128 rows count as two row tiles each in the bound: 252 of them are the most that are scheduled
-    inside.  The same rows range by range (always inside) must come out bit for bit the same."""
+    inside.  The same rows range by range (always inside) and in a larger buffer (never inside) must come out bit for bit the
+    same."""
     counts = np.full(groups, 128)
-    counts[::7] = 0
-    counts[3::11] = 65
+    if groups > 1:
+        counts[::7] = 0
+        counts[3::11] = 65
     X, dY, W = _device_case(int(128 * groups), 3, 64, 64)
-    whole = _fwd_bwd(X, dY, W, counts, 3)
+    with _ScheduleLaunches(0 if groups <= 252 else 2):
+        whole = _fwd_bwd(X, dY, W, counts, 3)
     parts = None
-    for lo in range(0, groups, 100):
-        parts = _fwd_bwd(X, dY, W, counts, 3, lo, min(lo + 100, groups), parts)
-    for a, b in zip(whole, parts):
+    with _ScheduleLaunches(0):
+        for lo in range(0, groups, 100):
+            parts = _fwd_bwd(X, dY, W, counts, 3, lo, min(lo + 100, groups), parts)
+    with _ScheduleLaunches(2):
+        spare = _fwd_bwd(_with_spare_rows(X), _with_spare_rows(dY), W, counts, 3)
+    for a, b, c in zip(whole, parts, spare):
         assert torch.equal(a, b)
-    end = int(counts.sum())
-    if end:
-        want = torch.nn.functional.silu(X[:int(counts[0] or counts[1])].float() @ W[0][0 if counts[0] else 1].float().T)
-        want = want * (X[:want.shape[0]].float() @ W[1][0 if counts[0] else 1].float().T)
-        assert rel_l2(whole[2][:want.shape[0]], want.cpu().numpy()) <= TOL
+        assert torch.equal(a, c[:a.shape[0]]) and (c[a.shape[0]:] == 3.0).all()
+    first = int(np.argmax(counts > 0))
+    want = torch.nn.functional.silu(X[:int(counts[first])].float() @ W[0][first % 3].float().T)
+    want = want * (X[:want.shape[0]].float() @ W[1][first % 3].float().T)
+    assert rel_l2(whole[2][:want.shape[0]], want.cpu().numpy()) <= TOL
+
+
+def _every_form(X, dY, gate, W, E, go, ge, slot, g_begin, g_end, rows):
+    """Forward and data gradients in a buffer of `rows` rows: plain, gate-fused, with the replica slots' parameters."""
+    go, ge, slot = dev_i32(go), dev_i32(ge), dev_i32(slot)
+    N, h, hff, G = X.shape[0], X.shape[1], W[0].shape[1], len(ge)
+    fill = lambda *widths: [torch.full((rows, w), 3.0, dtype=torch.bfloat16, device=DEV) for w in widths]
+    pad = lambda t: torch.cat([t, t.new_zeros((rows - N,) + t.shape[1:])])
+    own = [w[:E] for w in W]
+    tok = (torch.arange(rows, dtype=torch.int32, device=DEV) * 7) % N
+    dgate = torch.full((rows,), 3.0, device=DEV)
+    scratch = torch.zeros(rl.workspace_bytes(rl.WS_DGATE, rows, 1, E, G, h, hff), dtype=torch.uint8, device=DEV)
+    plain, gated, slots = fill(hff, hff, hff, h, h), fill(hff, hff, hff, h, h), fill(h)
+    errs = [rl.new_err_flag() for _ in range(5)]
+    share = dict(g_begin=g_begin, g_end=g_end)
+    Gt, U, A, Y, dX = plain
+    rl.relibra_moe_ffn_fwd(pad(X), go, ge, *own, Gt=Gt, U=U, A=A, Yrows=Y, err_flag=errs[0], **share)
+    rl.relibra_moe_ffn_bwd(pad(dY), None, Gt, U, A, go, ge, slot, *own, None, None, None, flags=rl.BWD_DEFER_WGRAD, dXrows=dX, err_flag=errs[1], E=E, **share)
+    rl.relibra_moe_ffn_bwd(pad(dY), None, Gt, U, A, go, ge, slot, *W, None, None, None, flags=rl.BWD_DEFER_WGRAD | rl.BWD_REPLICA_WEIGHTS, dXrows=slots[0],
+                           err_flag=errs[2], E=E, **share)
+    Gt, U, A, Y, dX = gated
+    rl.relibra_moe_ffn_fwd_gated(X, tok, pad(gate), go, ge, *own, Gt=Gt, U=U, A=A, Ag=A, Yrows=Y, err_flag=errs[3], **share)
+    rl.relibra_moe_ffn_bwd_gated(dY, tok, pad(gate), Gt, U, go, ge, slot, *own, dXrows=dX, dgate=dgate, dgate_scratch=scratch, err_flag=errs[4], E=E, **share)
+    return plain + gated + slots + [dgate], [e.item() for e in errs]
+
+
+BANDS = [0, 1, 129, 1153, 64, 65, 1024, 128, 2176, 0, 3]            # one row tile, bands of eight, a remainder of one and of two bands
+SCHEDULE_CASES = [  # rows of the groups, expert width, first and last group of the call
+    pytest.param([1], 320, 0, None, id="one-row"), pytest.param([129], 320, 0, None, id="two-row-tiles"),
+    pytest.param(BANDS, 64, 0, None, id="bands-one-column-tile"), pytest.param(BANDS, 320, 0, None, id="bands-three-column-tiles"),
+    pytest.param(BANDS, 320, 3, 9, id="bands-of-a-range"), pytest.param([(37 * i) % 97 for i in range(300)], 64, 0, None, id="more-than-256-groups")]
+
+
+@pytest.mark.parametrize("counts,hff,g_begin,g_end", SCHEDULE_CASES)
+def test_schedule_inside_the_first_kernel_over_bands_columns_and_forms(counts, hff, g_begin, g_end):
+    """The same table in a buffer with spare rows goes through the scheduling kernel: bit for bit the same results, with several
+    column tiles (of 128 in gate/up, of 256 in the activation backward), groups of more row tiles than a band has,
+    gate-fused and with parameter blocks chosen by replica slot."""
+    E, h, N, G = 5, 128, sum(counts), len(counts)
+    X, dY, W = _device_case(N, E + 3, h, hff)
+    gate = torch.linspace(0.1, 0.9, N, device=DEV)
+    go, ge = np.concatenate([[0], np.cumsum(counts)]), np.arange(G) % E
+    slot = np.where(np.arange(G) % 3 == 1, E + np.arange(G) % 3, ge)
+    with _ScheduleLaunches(0):
+        inside, err_in = _every_form(X, dY, gate, W, E, go, ge, slot, g_begin, g_end, N)
+    with _ScheduleLaunches(5):
+        outside, err_out = _every_form(X, dY, gate, W, E, go, ge, slot, g_begin, g_end, SPARE_ROWS)
+    assert err_in == err_out == [0] * 5
+    for a, b in zip(inside, outside):
+        assert torch.equal(a, b[:N]) and (b[N:] == 3.0).all()
+    assert not torch.equal(inside[4], inside[10]) or not (slot != ge)[np.asarray(counts) > 0].any()      # replica slots' parameters were read
+
+
+def test_schedule_inside_the_first_kernel_skips_and_flags_the_same_groups():
+    """Falling and negative offsets, experts and replica slots out of range: the same groups are skipped and the same calls flagged
+    whichever kernel works the schedule out."""
+    E, h, hff, N = 3, 64, 320, 900
+    X, dY, W = _device_case(N, E + 2, h, hff)
+    gate = torch.linspace(0.1, 0.9, N, device=DEV)
+    good = dict(go=np.array([0, 40, 100, 300, 500, 700, 900]), ge=np.array([0, 1, 2, 0, -1, 2]), slot=np.array([0, 3, 2, 0, 0, 4]))
+    bad = {"offset": dict(go=np.array([0, 40, -5, 300, 500, 700, 900])), "expert": dict(ge=np.array([0, 1, 7, -2, -1, 2])),
+           "slot": dict(slot=np.array([0, 3, 5, -1, 99, 4]))}
+    for what, change in [("none", {}), *bad.items()]:
+        table = {**good, **change}
+        with _ScheduleLaunches(0):
+            inside, err_in = _every_form(X, dY, gate, W, E, *table.values(), 0, None, N)
+        with _ScheduleLaunches(5):
+            outside, err_out = _every_form(X, dY, gate, W, E, *table.values(), 0, None, SPARE_ROWS)
+        flagged = {"none": [], "slot": [2]}.get(what, range(5))          # the slot table is read with the replica slots' parameters only
+        assert err_in == err_out == [rl.ERR_GROUP_TABLE if i in flagged else 0 for i in range(5)], what
+        for a, b in zip(inside, outside):
+            assert torch.equal(a, b[:N]) and (b[N:] == 3.0).all(), what
 
 
 @pytest.mark.parametrize("h,hff,rows", [(1024, 64, 16384), (64, 1024, 5376), (64, 1024, 8192)])
