@@ -584,7 +584,8 @@ int relibra_unpermute_combine(int mode, const void *rows_dev, const void *tok_de
  * its launch stream: level 1 = the grouped-GEMM kernels, level 2 = every kernel, 0 = off.
  * Calls of few tiles do both weight gradients in one launch, recorded as RELIBRA_K_WGRAD_PAIR instead of
  * _WGRAD_DOWN and _WGRAD_GATE_UP; small permutations run as one kernel, RELIBRA_K_PERM_SMALL instead of
- * _PERM_COUNT, _SCAN and _RANK.
+ * _PERM_COUNT, _SCAN and _RANK; calls whose row buffer holds few tiles work their schedule out in their first kernel and
+ * launch no RELIBRA_K_SCHED.
  * At most max_records launches are recorded (events are created in relibra_prof_start, host
  * side only).  relibra_prof_stop waits for the recorded events and returns, per kernel id
  * (RELIBRA_K_*), the summed milliseconds and the launch count in two host arrays of
