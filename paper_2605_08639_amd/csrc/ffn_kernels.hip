@@ -1388,10 +1388,16 @@ static int launch_sched(const SchedIn &in, const Sched &s, hipStream_t stream)
     RELIBRA_HIP_TRY(launch_check());
     return RELIBRA_OK;
 }
-// Whether the first kernel of a call works the schedule out itself: where all of its blocks (at most `tiles`) run at
-// once, two to a compute unit, each does so beside the others; with more rounds it would be done once per round.
-// Training steps with the scheduling kernel -> without: 8 experts of 128 x 256, 512 tokens (two calls) 112 -> 104 us; 16
-// of 256 x 192, 3 x 777 tokens (six calls) 263 -> 251.
+// Whether the first kernel of a call works the schedule out itself: where all of its blocks run at once, two to a
+// compute unit, each does so beside the others, however many groups it reads; beyond that it is done once per round and
+// soon costs more than the launch it saves.  `tiles` is what a row buffer of this size could hold (the groups are
+// known on the device only): a call over a few groups of a large buffer counts as a large one.  With the scheduling
+// kernel -> without, us a call, repeated in a captured graph, spread 1 to 6 %: 24 tiles (8 groups of 64 rows, 128 x
+// 256) forward 12.9 -> 11.6, data gradients 17.7 -> 16.3; 384 (32 of 128, 256 x 768) 31.6 -> 29.3, 40.7 -> 38.5; 281 (250 of 16, 256 x 128)
+// 14.4 -> 12.8, 18.0 -> 16.3; 495 (440 of 16, 256 x 128) 19.7 -> 17.1, 24.6 -> 21.9; all of 16 forward and 22 backward sizes of up to 504 gain.
+// Beyond: 1566 (440 of 100, 256 x 256) 52.6 -> 50.5, 2248 (500 of 16, 256 x 512) 57.7 -> 62.2, 2250 (1000 of 16, 256 x 256) 57.0 ->
+// 65.6.  Whole training steps: 8 experts of 128 x 256, 512 tokens (two calls) 111.5 -> 106.5, spread 7 %; 16 of 256 x 192, 3 x 777
+// tokens (six calls) 262 -> 251, spread 4 %.
 static inline bool schedules_itself(bool wide, long long tiles) { return !wide && tiles + 8 <= 2 * kComputeUnits; }
 
 // Launch of a row-tiled GEMM kernel template <bool WT, int AW>: narrow (four waves, two workgroups
